@@ -44,6 +44,32 @@ lipz_status lipz_test_gemm(void* hip_stream, void* d_desc, int32_t M, int32_t N,
                            float eps, int32_t tile_rows, int32_t variant);
 
 /*
+ * One 4x4, stride-2, pad-1 (transposed) convolution of the DCGAN-style networks
+ * or one of its gradients, on one of their kernels, NHWC tensors, weights
+ * [16 taps (kh, kw)][cin][cout].  With S = 2^side_log:
+ *   kind 0: convolution, x [n][S][S][cin] -> out [n][S/2][S/2][cout] =
+ *           act(conv + bias) (bias may be NULL)
+ *   kind 1: transposed convolution, x [n][S][S][cin] -> out [n][2S][2S][cout]
+ *   kind 2: input gradient of kind 0, x = its output gradient -> out
+ *           [n][S][S][cin] times act'(aux), act' taken from the value aux
+ *   kind 3: input gradient of kind 1, x = its output gradient [n][2S][2S][cout]
+ *           -> out [n][S][S][cin] times act'(aux)
+ *   kind 4: weight gradient of kind 0, x its input, w its output gradient ->
+ *           partial sums out [ceil(n (S/2)^2 / 1024)][16 cin + 1][cout], the
+ *           last row the bias gradient, split s over positions 1024 s ..
+ *   kind 5: weight gradient of kind 1, partial sums
+ *           [ceil(n S^2 / 1024)][16 cin][cout]
+ * kernel: 0 = 64 x 64 fp32 tiles, any shape; 1 = wide fp32 tiles, bit for bit
+ * the sums of 0: channels multiples of 4, more than 16 output columns, grids
+ * of a weight gradient at most 32 wide, tiles 128 x 128, 128 x 64 or 64 x 64
+ * (else LIPZ_E_INVAL).
+ * d_desc: device scratch of at least 2048 bytes.
+ */
+lipz_status lipz_test_conv(void* hip_stream, void* d_desc, int32_t kind, int32_t n_img, int32_t side_log, int32_t cin,
+                           int32_t cout, const float* d_x, const float* d_w, float* d_out, const float* d_bias,
+                           const float* d_aux, int32_t act, float slope, int32_t kernel, int32_t tile_m, int32_t tile_n);
+
+/*
  * Host-only check of a configuration's launch plan (no GPU, no device
  * memory): the library lays the plan out over placeholder addresses and
  * recomputes, for every GEMM, convolution, batch-norm, reduction and dot

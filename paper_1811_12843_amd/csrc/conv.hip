@@ -24,90 +24,16 @@
 // D[4 (l / 16) + r][l % 16].
 #include <hip/hip_ext.h>
 
-#include "lipz_internal.h"
+#include "conv_tile.h"
 
 namespace lipz {
 
-typedef float v4f __attribute__((ext_vector_type(4)));
-typedef unsigned int v4u __attribute__((ext_vector_type(4)));
-
 namespace {
 
-constexpr int NT = 256;
 constexpr int TM = 64, TK = 32;           // tile rows, K slice (tile columns: ConvProb::tn)
 constexpr int SK = TK + 4;                // row stride of [row][k] LDS tiles
 constexpr int SM = TM + 4;                // row stride of [k][m] tiles
 constexpr int TILE_FLOATS = (TM * SK > TK * SM) ? TM * SK : TK * SM;
-// A byte offset past every operand extent the host accepts: such a buffer
-// load returns 0.
-constexpr uint32_t OOB = 0x7FFFFFF0u;
-
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const float* p, uint32_t bytes) {
-  // dword 3 = 0x00020000: raw 32-bit data format on gfx9-family parts
-  return __builtin_amdgcn_make_buffer_rsrc((void*)p, (short)0, (int)bytes, 0x00020000);
-}
-__device__ __forceinline__ float4 ld4(__amdgpu_buffer_rsrc_t r, uint32_t off_bytes) {
-  const v4u v = __builtin_amdgcn_raw_buffer_load_b128(r, (int)off_bytes, 0, 0);
-  return make_float4(__uint_as_float(v[0]), __uint_as_float(v[1]), __uint_as_float(v[2]),
-                     __uint_as_float(v[3]));
-}
-__device__ __forceinline__ float ld1(__amdgpu_buffer_rsrc_t r, uint32_t off_bytes) {
-  return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, (int)off_bytes, 0, 0));
-}
-
-// Blocks are dispatched round-robin over the 8 XCDs; give each XCD a
-// contiguous range of logical tiles so neighbouring tiles share its L2.
-__device__ __forceinline__ int xcd_remap(int b, int nb) {
-  const int q = nb >> 3, r = nb & 7;
-  const int x = b & 7, i = b >> 3;
-  return x * q + (x < r ? x : r) + i;
-}
-
-struct Pos {
-  int img, y, x;
-};
-__device__ __forceinline__ Pos grid_pos(int p, int gh, int gw) {
-  return {p >> (gh + gw), (p >> gw) & ((1 << gh) - 1), p & ((1 << gw) - 1)};
-}
-
-// Tap t -> (row shift, column shift) of the gathered operand, and its
-// weight-tap index kh * kw_full + kw.
-struct Tap {
-  int dy, dx, wt;
-};
-__device__ __forceinline__ Tap tap_of(const ConvProb& P, int t) {
-  const int a = t >> P.tw_log, b = t & ((1 << P.tw_log) - 1);
-  return {a * P.tys + P.ty0, b * P.tys + P.tx0, (a * P.khs + P.kh0) * P.kw_full + (b * P.khs + P.kw0)};
-}
-
-// k index of the tap-expanded operand -> (tap, channel).
-__device__ __forceinline__ void split_k(const ConvProb& P, int k, int& t, int& c) {
-  if (P.cs_log >= 0) {
-    t = k >> P.cs_log;
-    c = k & (P.cs - 1);
-  } else if (P.taps <= 1) {
-    t = 0;
-    c = k;
-  } else {
-    t = k / P.cs;
-    c = k - t * P.cs;
-  }
-}
-
-// Byte offset of channel c of S at grid position q shifted by tap d, or OOB.
-__device__ __forceinline__ uint32_t src_off(const ConvProb& P, Pos q, Tap d, int c) {
-  const int sy = q.y * P.smap.sy + d.dy;
-  const int sx = q.x * P.smap.sx + d.dx;
-  if ((unsigned)sy >= (1u << P.smap.h_log) || (unsigned)sx >= (1u << P.smap.w_log)) return OOB;
-  const int pos = (((q.img << P.smap.h_log) + sy) << P.smap.w_log) + sx;
-  return (uint32_t)(pos * P.smap.ld + c) * 4u;
-}
-
-// Element offset (floats) of grid position q under a position map.
-__device__ __forceinline__ int map_off(const PosMap& m, Pos q) {
-  const int y = q.y * m.sy + m.y0, x = q.x * m.sx + m.x0;
-  return ((((q.img << m.h_log) + y) << m.w_log) + x) * m.ld;
-}
 
 // ---------------------------------------------------------------------------
 // Slice loads.  Thread tid loads two float4 groups of A and two of B per

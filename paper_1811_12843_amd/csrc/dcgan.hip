@@ -23,6 +23,7 @@
 #include <string.h>
 
 #include "grid.h"
+#include "lipz_testing.h"
 
 namespace lipz {
 
@@ -48,6 +49,7 @@ struct DcNet {
 struct ConvPhase {
   int first = 0, count = 0, tiles = 0;  // tiles: blocks of the launch
   ConvGroups grp;
+  ConvVariant var;
   double flops = 0.0;
   double bytes = 0.0;  // algorithmic: each tensor read or written once
 };
@@ -602,17 +604,50 @@ void dc_carve_tables(lipz_grid* g, Carver& cv) {
 
 namespace {
 
-int add_conv_phase(DcPlan& P, const std::vector<ConvProb>& ps) {
+// The kernels of the wide tiles take the problems that read whole float4s and
+// are wider than 16 columns (weight gradients: over grids at most 32 wide, a
+// slice's 32 positions being whole rows).  Their outputs (and auxiliary
+// operands) are addressed as float4 too.
+bool conv_tile_ok(const ConvProb& p) {
+  if (p.gen || p.N <= 16 || p.taps <= 0 || p.N % 4 || p.cs % 4 || !aligned16(p.C)) return false;
+  if (p.mode == CONV_WG) return p.ldc % 4 == 0 && p.split_stride % 4 == 0 && p.gw_log <= 5;
+  return p.omap.ld % 4 == 0 && (p.epi != EPI_DACT || aligned16(p.aux));
+}
+
+// Tile of a set of like problems: the largest one that still gives the chip
+// two workgroups per CU (512), without more than an eighth of padded columns.
+void conv_tile_size(const std::vector<ConvProb>& ps, ConvVariant& v) {
+  auto tiles = [&](int tm, int tn) {
+    int64_t t = 0;
+    for (const ConvProb& p : ps) {
+      const int M = p.mode == CONV_WG ? p.taps * p.cs : p.M;
+      t += (int64_t)((M + tm - 1) / tm) * ((p.N + tn - 1) / tn) * (p.mode == CONV_WG ? p.splits : 1);
+    }
+    return t;
+  };
+  const int N = ps[0].N, pad128 = (N + 127) / 128 * 128, pad64 = (N + 63) / 64 * 64;
+  v.tm = 128;
+  v.tn = pad128 * 8 <= pad64 * 9 ? 128 : 64;
+  if (v.tn == 128 && tiles(128, 128) < 512) v.tn = 64;
+  if (v.tn == 64 && tiles(128, 64) < 512) v.tm = 64;
+}
+
+// One launch: problems `ps`, all run as variant v.
+int add_conv_launch(DcPlan& P, const std::vector<ConvProb>& ps, const ConvVariant& v) {
   ConvPhase ph;
   ph.first = (int)P.conv_h.size();
   ph.count = (int)ps.size();
+  ph.var = v;
   memset(&ph.grp, 0, sizeof(ph.grp));
   auto round8 = [](int v) { return (v + 7) & ~7; };
   int blocks = 0, prev = -1;
   for (size_t k = 0; k < ps.size(); ++k) {
     ConvProb p = ps[k];
-    p.tn = p.N <= 16 ? 16 : 64;
-    p.tiles_m = (p.M + 63) / 64;
+    p.tn = v.kernel != CONV_K_ANY ? v.tn : (p.N <= 16 ? 16 : 64);
+    const int tm = v.kernel != CONV_K_ANY ? v.tm : 64;
+    // the wide tiles' first row tile adds up the ones row, which has no tile of its own there
+    const int rows = v.kernel != CONV_K_ANY && p.mode == CONV_WG ? p.taps * p.cs : p.M;
+    p.tiles_m = (rows + tm - 1) / tm;
     p.tiles_n = (p.N + p.tn - 1) / p.tn;
     if (p.mode != CONV_WG) p.splits = 1;
     const int tpp = p.tiles_m * p.tiles_n * p.splits;
@@ -638,6 +673,32 @@ int add_conv_phase(DcPlan& P, const std::vector<ConvProb>& ps) {
   ph.tiles = ph.grp.n ? ph.grp.first_block[ph.grp.n - 1] + ph.grp.blocks[ph.grp.n - 1] : 0;
   P.cph.push_back(ph);
   return (int)P.cph.size() - 1;
+}
+
+// The problems of one dependent phase as launches: those of one variant
+// (kernel, operand layouts and width) together, the rest on conv_kernel.
+void add_conv_phase(DcPlan& P, const std::vector<ConvProb>& ps, std::vector<DcOp>& ops) {
+  std::vector<std::pair<ConvVariant, std::vector<ConvProb>>> sets;
+  for (const ConvProb& p : ps) {
+    ConvVariant v;
+    memset(&v, 0, sizeof(v));
+    const bool bt = p.mode == CONV_FWD && p.wsn != 1;
+    if (conv_tile_ok(p)) {
+      v.kernel = CONV_K_WIDE;
+      v.mode = p.mode;
+      v.bt = bt;
+      v.tap1 = p.mode == CONV_FWD && p.cs % 32 == 0;
+    }
+    size_t k = 0;
+    while (k < sets.size() && !(sets[k].first == v && (v.kernel == CONV_K_ANY || sets[k].second[0].N == p.N))) ++k;
+    if (k == sets.size()) sets.push_back({v, {}});
+    sets[k].second.push_back(p);
+  }
+  for (auto& s : sets) {
+    ConvVariant v = s.first;
+    if (v.kernel != CONV_K_ANY) conv_tile_size(s.second, v);
+    ops.push_back({DC_CONV, add_conv_launch(P, s.second, v)});
+  }
 }
 
 int add_bn_op(DcPlan& P, const std::vector<BnProb>& bs) {
@@ -760,7 +821,7 @@ void dc_build(lipz_grid* g) {
     std::vector<DcOp>& ops = P.train_ops[par];
     ops.clear();
     auto gemm = [&](const std::vector<GemmProb>& ps) { ops.push_back({DC_GEMM, add_phase(g, ps)}); };
-    auto conv = [&](const std::vector<ConvProb>& ps) { ops.push_back({DC_CONV, add_conv_phase(P, ps)}); };
+    auto conv = [&](const std::vector<ConvProb>& ps) { add_conv_phase(P, ps, ops); };
     auto Gw = [&](int c, int l) { return S.Gp + c * sG + G.L[l].off_w; };
     auto Dw = [&](int c, int l) { return S.Dp + c * sD + D.L[l].off_w; };
     auto gsz = [&](int k) { return (int64_t)B * side_sq(G.L[k].out_log) * G.L[k].nb; };
@@ -1087,7 +1148,7 @@ void dc_build(lipz_grid* g) {
               ps.push_back(convT_phase(P.gex[k - 1] + (c * 5 + i) * egsz(k - 1), B, L.in_log, L.cin, Gw(own, k), L.cout,
                                        P.gex[k] + (c * 5 + i) * egsz(k), r, q, EPI_STORE, 0, nullptr));
         }
-      ev.push_back({DC_CONV, add_conv_phase(P, ps)});
+      add_conv_phase(P, ps, ev);
       ebn(k);
     }
     {
@@ -1102,7 +1163,7 @@ void dc_build(lipz_grid* g) {
           cs.push_back(col_prob(cols, P.Xe + (size_t)c * 6 * B * xd + (size_t)(1 + i) * B * xd, B, P.img_log, P.ic,
                                 EPI_BIAS_ACT, Lg.act, S.Gp + own * sG + Lg.off_b, nullptr));
         }
-      ev.push_back({DC_CONV, add_conv_phase(P, ps)});
+      add_conv_phase(P, ps, ev);
       col2im(ev, cs);
     }
     {
@@ -1127,7 +1188,7 @@ void dc_build(lipz_grid* g) {
             ps.push_back(conv_fwd(P.dey[(k - 1) & 1] + (c * 5 + j) * NIe * dsz(k - 1), NIe, L.in_log, L.cin, Dw(own, k),
                                   L.cout, out, EPI_BIAS_ACT, L.act, S.Dp + own * sD + L.off_b));
         }
-      ev.push_back({DC_CONV, add_conv_phase(P, ps)});
+      add_conv_phase(P, ps, ev);
     }
     {
       std::vector<DotProb> ds;
@@ -1189,13 +1250,21 @@ hipError_t dc_init_params(lipz_grid* g, const StateBuf& S, hipStream_t s) {
 
 namespace {
 
+hipError_t launch_conv(const ConvPhase& ph, const ConvProb* d, float slope, hipStream_t s, hipEvent_t e0 = nullptr,
+                       hipEvent_t e1 = nullptr) {
+  switch (ph.var.kernel) {
+    case CONV_K_WIDE: return launch_conv_wide(d, ph.grp, ph.tiles, ph.var, slope, s, e0, e1);
+    default: return launch_conv_grouped(d, ph.grp, ph.tiles, slope, s, e0, e1);
+  }
+}
+
 hipError_t run_conv_phase(lipz_grid* g, int idx, hipStream_t s) {
   DcPlan& P = *g->dc;
   const ConvPhase& ph = P.cph[idx];
   hipEvent_t e0, e1;
   hipError_t e = timing_events(g, &e0, &e1);
   if (e != hipSuccess) return e;
-  e = launch_conv_grouped(P.conv_d + ph.first, ph.grp, ph.tiles, g->slope, s, e0, e1);
+  e = launch_conv(ph, P.conv_d + ph.first, g->slope, s, e0, e1);
   timing_record(g, e0, e1, ph.flops, ph.bytes);
   return e;
 }
@@ -1473,3 +1542,48 @@ int dc_check_bounds(const lipz_grid* g, const char* const* lo, const char* const
 }
 
 }  // namespace lipz
+
+using namespace lipz;
+
+// Test hook of include/lipz_testing.h: one convolution.
+extern "C" lipz_status lipz_test_conv(void* hip_stream, void* d_desc, int32_t kind, int32_t n_img, int32_t side_log,
+                                      int32_t cin, int32_t cout, const float* d_x, const float* d_w, float* d_out,
+                                      const float* d_bias, const float* d_aux, int32_t act, float slope, int32_t kernel,
+                                      int32_t tile_m, int32_t tile_n) {
+  if (!d_desc || !d_x || !d_w || !d_out || kind < 0 || kind > 5 || n_img < 1 || side_log < 1 || side_log > 6 || cin < 1 ||
+      cout < 1 || cin > 1024 || cout > 1024 || act < LIPZ_ACT_LINEAR || act > LIPZ_ACT_TANH)
+    return LIPZ_E_INVAL;
+  if ((kind == 2 || kind == 3) && !d_aux) return LIPZ_E_INVAL;
+  if (((int64_t)n_img << (2 * (side_log + 1))) * (cin > cout ? cin : cout) >= ((int64_t)1 << 28)) return LIPZ_E_INVAL;
+  std::vector<ConvProb> ps;
+  if (kind == 0) ps.push_back(conv_fwd(d_x, n_img, side_log, cin, d_w, cout, d_out, EPI_BIAS_ACT, act, d_bias));
+  if (kind == 3) ps.push_back(convT_dgrad(d_x, n_img, side_log, cin, cout, d_w, d_out, d_aux, act));
+  if (kind == 4) ps.push_back(conv_wgrad(d_x, n_img, side_log, cin, d_w, cout, d_out));
+  for (int r = 0; r < 2; ++r)
+    for (int q = 0; q < 2; ++q) {
+      if (kind == 1) ps.push_back(convT_phase(d_x, n_img, side_log, cin, d_w, cout, d_out, r, q, EPI_STORE, 0, nullptr));
+      if (kind == 2) ps.push_back(conv_dgrad_phase(d_x, n_img, side_log, cin, cout, d_w, d_out, d_aux, act, r, q));
+      if (kind == 5)
+        ps.push_back(convT_wgrad_phase(d_x, n_img, side_log, cin, d_w, cout, d_out, 16 * cin, r, q));
+    }
+  ConvVariant v;
+  memset(&v, 0, sizeof(v));
+  v.kernel = kernel;
+  if (kernel != CONV_K_ANY) {
+    if (kernel != CONV_K_WIDE) return LIPZ_E_INVAL;
+    if (!((tile_m == 128 && (tile_n == 128 || tile_n == 64)) || (tile_m == 64 && tile_n == 64))) return LIPZ_E_INVAL;
+    for (const ConvProb& p : ps)
+      if (!conv_tile_ok(p)) return LIPZ_E_INVAL;
+    v.tm = tile_m;
+    v.tn = tile_n;
+    v.mode = ps[0].mode;
+    v.bt = ps[0].mode == CONV_FWD && ps[0].wsn != 1;
+    v.tap1 = ps[0].mode == CONV_FWD && ps[0].cs % 32 == 0;
+  }
+  DcPlan P;
+  const ConvPhase& ph = P.cph[add_conv_launch(P, ps, v)];
+  static_assert(4 * sizeof(ConvProb) <= 2048, "the caller's descriptor scratch is 2048 bytes");
+  if (!P.plan_ok || hipMemcpy(d_desc, P.conv_h.data(), P.conv_h.size() * sizeof(ConvProb), hipMemcpyHostToDevice) != hipSuccess)
+    return LIPZ_E_HIP;
+  return launch_conv(ph, (const ConvProb*)d_desc, slope, (hipStream_t)hip_stream) == hipSuccess ? LIPZ_OK : LIPZ_E_HIP;
+}

@@ -430,6 +430,23 @@ struct ConvGroups {
   int32_t tiles_per_prob[GEMM_MAX_GROUPS];
 };
 
+// How a convolution launch runs.
+//   CONV_K_ANY: conv_kernel (conv.hip), fp32 MFMAs, 64 x 64 or 64 x 16 tiles,
+//     problems of any kind side by side;
+//   CONV_K_WIDE: conv_wide_kernel (conv_wide.hip), tm x tn tiles, the sums of
+//     conv_kernel in its order, bit for bit;
+//     It has one tile, mode and operand layout per launch: tm x tn outputs,
+//     mode, transposed weights (bt), whole slices within one tap (tap1).
+enum ConvKernel : int32_t { CONV_K_ANY = 0, CONV_K_WIDE = 1 };
+struct ConvVariant {
+  int32_t kernel, tm, tn, mode, bt, tap1;
+  bool operator==(const ConvVariant& o) const {
+    return kernel == o.kernel && tm == o.tm && tn == o.tn && mode == o.mode && bt == o.bt && tap1 == o.tap1;
+  }
+};
+hipError_t launch_conv_wide(const ConvProb* d_probs, const ConvGroups& grp, int total_blocks, const ConvVariant& v,
+                            float slope, hipStream_t s, hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);
+
 // Launch every problem of one phase (problems in device memory).
 hipError_t launch_conv_grouped(const ConvProb* d_probs, const ConvGroups& grp, int total_blocks, float slope,
                                hipStream_t s, hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);

@@ -120,6 +120,8 @@ _SIGS = {
     "lipz_test_gemm": (_i32, [_vp, _vp, _i32, _i32, _i32, _vp, _i32, _i32, _i32, _vp, _i32, _i32,
                               _vp, _i32, _i32, _i32, _f32, _vp, _vp, _vp, _vp, _vp, _vp, _i32,
                               _f32, _f32, _f32, _i32, _i32]),
+    "lipz_test_conv": (_i32, [_vp, _vp, _i32, _i32, _i32, _i32, _i32, _vp, _vp, _vp, _vp, _vp, _i32, _f32, _i32, _i32,
+                              _i32]),
     "lipz_test_es_select": (_i32, [_vp, _vp, _vp, _vp, _i32, _i32, _i64, _i64, _f32]),
     "lipz_test_tile_map": (_i32, [_i32, _vp, _i32, _vp]),
 }
@@ -291,6 +293,13 @@ def lipz_test_gemm(stream, d_desc, M, N, K, d_A, lda, a_trans, ones_row, d_B, ld
                                                 slope, _p(d_bias), _p(d_aux), _p(d_m), _p(d_v), _p(d_lr),
                                                 _p(d_t), step_local, beta1, beta2, eps, tile_rows, variant),
                   "lipz_test_gemm")
+
+
+def lipz_test_conv(stream, d_desc, kind, n_img, side_log, cin, cout, d_x, d_w, d_out, d_bias=None, d_aux=None, act=0,
+                   slope=0.2, kernel=0, tile_m=0, tile_n=0):
+    return _check(load_library().lipz_test_conv(_p(stream), _p(d_desc), kind, n_img, side_log, cin, cout, _p(d_x), _p(d_w),
+                                                _p(d_out), _p(d_bias), _p(d_aux), act, slope, kernel, tile_m, tile_n),
+                  "lipz_test_conv")
 
 
 def lipz_test_es_select(stream, d_fit, d_sets, d_params, n_units, n_pairs, P, stride, clip=0.0):

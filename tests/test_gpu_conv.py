@@ -1,0 +1,121 @@
+"""The convolution kernels on the GPU, one convolution at a time
+(lipz_test_conv), at sizes that leave tiles, slices and splits partly filled:
+against torch's fp64 convolutions on the CPU, and the wide fp32 tiles bit for
+bit against the 64 x 64 ones."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+if not torch.cuda.is_available():  # pragma: no cover - collected on CPU, skipped there
+    pytest.skip("no GPU", allow_module_level=True)
+
+import torch.nn.functional as F  # noqa: E402
+
+import paper_1811_12843_amd as L  # noqa: E402
+
+ANY, WIDE = 0, 1
+SLOPE = 0.2
+KINDS = ["conv", "convT", "conv_dgrad", "convT_dgrad", "conv_wgrad", "convT_wgrad"]
+# (images, log2 side, c_in, c_out): channels a multiple of 32 (a slice within one tap) and not, one and several
+# 128- and 64-wide column tiles, whole and partial rows, last splits of a few positions
+SHAPES = [(3, 3, 32, 64), (1, 2, 36, 132), (5, 2, 20, 68), (2, 4, 64, 128), (9, 3, 44, 192), (7, 1, 128, 20)]
+TILES = [(128, 128), (128, 64), (64, 64)]
+
+
+def _nchw(t):
+    return t.permute(0, 3, 1, 2)
+
+
+def _reference(kind, x, w, aux, bias):
+    """fp64 results of a kind in lipz_test_conv's layout, and the sums of |a b| that bound their rounding."""
+    out = []
+    for f in (lambda t: t, torch.abs):
+        X, W = f(x), f(w)
+        ci, co = W.shape[-2], W.shape[-1]
+        if kind == "conv":
+            y = F.conv2d(_nchw(X), W.view(4, 4, ci, co).permute(3, 2, 0, 1), f(bias), stride=2, padding=1)
+        elif kind == "convT":
+            y = F.conv_transpose2d(_nchw(X), W.view(4, 4, ci, co).permute(2, 3, 0, 1), stride=2, padding=1)
+        elif kind == "conv_dgrad":
+            y = F.conv_transpose2d(_nchw(X), W.view(4, 4, ci, co).permute(3, 2, 0, 1), stride=2, padding=1)
+        else:
+            y = F.conv2d(_nchw(X), W.view(4, 4, ci, co).permute(2, 3, 0, 1), stride=2, padding=1)
+        out.append(y.permute(0, 2, 3, 1).contiguous())
+    if kind in ("conv_dgrad", "convT_dgrad"):
+        out = [y * torch.where(aux > 0, 1.0, SLOPE) for y in out]
+    elif kind == "conv":
+        out[0] = torch.where(out[0] > 0, out[0], SLOPE * out[0])
+    return out
+
+
+def _wgrad_reference(kind, x, dy):
+    out = []
+    for f in (lambda t: t, torch.abs):
+        X, D = f(x), f(dy)
+        small, big = (D, X) if kind == "conv_wgrad" else (X, D)  # the big map is gathered by the 16 taps
+        n, S = small.shape[0], small.shape[1]
+        cols = F.unfold(_nchw(big), 4, stride=2, padding=1).view(n, big.shape[3], 16, S * S)  # [n][c][tap][pos]
+        sm = small.reshape(n, S * S, -1)
+        g = torch.stack([sum(cols[i, :, t] @ sm[i] for i in range(n)) for t in range(16)])  # [tap][big c][small c]
+        if kind == "conv_wgrad":
+            out.append(torch.cat([g.reshape(-1, g.shape[2]), D.sum((0, 1, 2))[None]]))
+        else:
+            out.append(g.transpose(1, 2).reshape(-1, g.shape[1]))
+    return out
+
+
+def _problem(kind, shape, seed):
+    n, h, ci, co = shape
+    rng = np.random.default_rng(seed)
+    t = {k: torch.from_numpy(rng.standard_normal(s).astype(np.float32)) for k, s in dict(
+        big=(n, 2 << h, 2 << h, co), inp=(n, 1 << h, 1 << h, ci), half=(n, max(1, 1 << h >> 1), max(1, 1 << h >> 1), co),
+        w=(16, ci, co), bias=(co,), aux=(n, 1 << h, 1 << h, ci)).items()}
+    x = {"conv": "inp", "convT": "inp", "conv_dgrad": "half", "convT_dgrad": "big", "conv_wgrad": "inp", "convT_wgrad": "inp"}
+    w = {"conv_wgrad": "half", "convT_wgrad": "big"}
+    return t[x[kind]], t[w.get(kind, "w")], t["bias"], t["aux"]
+
+
+def _run(kind, shape, kernel, tile, x, w, bias, aux):
+    n, h, ci, co = shape
+    K = KINDS.index(kind)
+    splits = -(-(n << (2 * (h - 1 if kind == "conv_wgrad" else h))) // 1024)
+    size = {"conv": (n, 1 << h >> 1, 1 << h >> 1, co), "convT": (n, 2 << h, 2 << h, co), "conv_dgrad": (n, 1 << h, 1 << h, ci),
+            "convT_dgrad": (n, 1 << h, 1 << h, ci), "conv_wgrad": (splits, 16 * ci + 1, co),
+            "convT_wgrad": (splits, 16 * ci, co)}[kind]
+    dx, dw, db, da = (t.cuda().contiguous() for t in (x, w, bias, aux))
+    out = torch.full(size, float("nan"), device="cuda")
+    desc = torch.zeros(2048, dtype=torch.uint8, device="cuda")
+    L.lipz_test_conv(torch.cuda.current_stream().cuda_stream, desc.data_ptr(), K, n, h, ci, co, dx.data_ptr(),
+                     dw.data_ptr(), out.data_ptr(), db.data_ptr() if kind == "conv" else None, da.data_ptr(),
+                     L.ACTS["lrelu"], SLOPE, kernel, *tile)
+    torch.cuda.synchronize()
+    return out.cpu()
+
+
+@pytest.mark.parametrize("kind", KINDS)
+@pytest.mark.parametrize("shape", SHAPES)
+def test_kernels_match_fp64(kind, shape):
+    x, w, bias, aux = _problem(kind, shape, seed=sum(shape) * 7 + KINDS.index(kind))
+    if kind.endswith("wgrad"):
+        ref, mag = _wgrad_reference(kind, x.double(), w.double())
+    else:
+        ref, mag = _reference(kind, x.double(), w.double(), aux.double(), bias.double())
+    n, h, ci, co = shape
+    depth = {"conv": 16 * ci, "convT": 4 * ci, "conv_dgrad": 4 * co, "convT_dgrad": 16 * co}.get(kind, n << (2 * h))
+    # a chain of fp32 multiply-adds over K products is off by at most K 2^-24 of the sum of |a b|; then bias,
+    # activation and the sum of splits
+    bound = (depth + 8) * 2.0 ** -24 * mag + 1e-30
+    if (co if kind in ("conv", "convT", "conv_wgrad", "convT_wgrad") else ci) <= 16:
+        pytest.skip("no wide tile is that narrow")
+    base = None
+    for kernel, tile in [(ANY, (0, 0))] + [(WIDE, t) for t in TILES]:
+        print(f"[case] {kind} {shape} kernel {kernel} tile {tile}", flush=True)
+        got = _run(kind, shape, kernel, tile, x, w, bias, aux)
+        full = got.double().sum(0) if kind.endswith("wgrad") else got.double()
+        assert torch.all((full - ref).abs() <= bound), (kernel, tile, float(((full - ref).abs() / bound).max()))
+        if kernel == ANY:
+            base = got
+        elif kernel == WIDE:
+            assert torch.equal(got, base), (tile, float((got - base).abs().max()))
