@@ -60,8 +60,9 @@ lipz_status lipz_test_gemm(void* hip_stream, void* d_desc, int32_t M, int32_t N,
  *   kind 5: weight gradient of kind 1, partial sums
  *           [ceil(n S^2 / 1024)][16 cin][cout]
  * kernel: 0 = 64 x 64 fp32 tiles, any shape; 1 = wide fp32 tiles, bit for bit
- * the sums of 0: channels multiples of 4, more than 16 output columns, grids
- * of a weight gradient at most 32 wide, tiles 128 x 128, 128 x 64 or 64 x 64
+ * the sums of 0; 2 = bf16 matrix cores at fp32 accuracy.  1 and 2: channels
+ * multiples of 4, more than 16 output columns, grids of a weight gradient at
+ * most 32 wide, tiles 128 x 128, 128 x 64 or 64 x 64; 2: kinds 0 and 1 only
  * (else LIPZ_E_INVAL).
  * d_desc: device scratch of at least 2048 bytes.
  */

@@ -1,0 +1,325 @@
+// The forward convolutions of the evaluation on the bf16 matrix cores, at fp32
+// accuracy (split.h): the same implicit GEMMs, position maps and taps as
+// conv_kernel, for problems whose operand rows are read as float4 (ConvProb::gen
+// == 0), with row-major weights and outputs wider than 16.  (Training keeps the
+// fp32 sums: conv_wide.hip.)
+//
+// A 256-thread workgroup (4 wave64, 2 x 2) owns a TM x TN output tile.  K
+// advances in 32-deep slices: the fp32 operands of the next slice are in
+// registers while the current one is multiplied; a slice is split into its
+// three bf16 pieces on the way into LDS (single buffer, two barriers per
+// slice; the two or three workgroups of a CU fill each other's barriers), and
+// the six piece products go through v_mfma_f32_32x32x16_bf16.
+//
+// What bounds it: the split's VALU work beside the MFMAs (about 240 VALU
+// instructions per 48 MFMAs and wave).  Measured, 80 problems of 98304 x 128 x
+// 1024 (2.06 TFLOP): 12.4 ms (166 TFLOP/s) against 15.8 on fp32 MFMAs
+// (conv_wide_kernel) and 20.9 on conv_kernel; 24576 x 256 x 2048: 11.2 ms.  A
+// loop of these MFMAs alone on random data runs at 1.77 PFLOP/s, 295 for six
+// products.
+//
+// TAP1: the channels per tap are a multiple of 32, so a slice lies within one
+// tap and its shift and weight row are scalars; otherwise every float4
+// carries its own (tap, channel), advanced without divisions.
+#include <hip/hip_ext.h>
+
+#include "conv_tile.h"
+
+namespace lipz {
+
+namespace {
+
+template <int TM, int TN>
+struct SplitTile {
+  static constexpr int A_PIECE = TM * RK_PITCH, B_PIECE = SK_DEEP * km_pitch(TN);
+  static constexpr int A_F4 = TM / 32, B_F4 = TN / 32;  // float4 of a slice per thread
+  static constexpr int TI = TM / 64, TJ = TN / 64;      // 32 x 32 MFMA tiles per wave
+  static constexpr int SPLIT_BYTES = 3 * (A_PIECE + B_PIECE);
+  static constexpr int WRITE_BYTES = 4 * 32 * (TN / 2 + 4) * 4;  // the epilogue's strips
+  static constexpr int LDS = SPLIT_BYTES > WRITE_BYTES ? SPLIT_BYTES : WRITE_BYTES;
+};
+
+// Operand loads of a slice.  A: thread t takes k 8 (t % 4) .. + 7 of rows
+// t / 4 + 64 h; B (k rows): one column quad of k rows t / (TN / 4) +
+// (1024 / TN) h.
+template <int TM, int TN, bool TAP1>
+struct SplitCtx {
+  __amdgpu_buffer_rsrc_t ra, rb;
+  int y[TM / 64], x[TM / 64], off[TM / 64];  // source coordinates and element offset of the thread's rows
+  uint32_t va[TM / 64];                      // TAP1: byte offsets of the rows under the slice's tap
+  KPos ka[2], kb[TN / 32];                   // not TAP1
+  int dt, dc;                                // not TAP1: 32 = dt * cs + dc
+  int t, c;                                  // TAP1: the slice's tap and first channel
+  uint32_t bcol;                             // byte offset of the thread's B columns (TAP1: and k row), FAR past N
+};
+
+template <int TM, int TN, bool TAP1>
+__device__ __forceinline__ void split_setup(const ConvProb& P, int m0, int n0, SplitCtx<TM, TN, TAP1>& X) {
+  const int tid = threadIdx.x;
+  X.ra = rsrc(P.S, P.s_bytes);
+  X.rb = rsrc(P.W, P.w_bytes);
+#pragma unroll
+  for (int h = 0; h < TM / 64; ++h) {
+    const int p = m0 + (tid >> 2) + 64 * h;
+    const Pos q = grid_pos(p < P.M ? p : 0, P.gh_log, P.gw_log);
+    X.y[h] = q.y * P.smap.sy;
+    X.x[h] = q.x * P.smap.sx;
+    X.off[h] = ((((q.img << P.smap.h_log) + X.y[h]) << P.smap.w_log) + X.x[h]) * P.smap.ld;
+    if (p >= P.M) X.y[h] = 0x40000000;  // no tap brings it inside
+  }
+  const int kr = tid / (TN / 4);
+  const int n = n0 + ((tid % (TN / 4)) << 2);
+  X.bcol = n < P.N ? (uint32_t)(n + (TAP1 ? kr * P.N : 0)) * 4u : FAR;
+  X.t = 0;
+  X.c = 0;
+  if (!TAP1) {
+    X.dt = P.taps > 1 ? 32 / P.cs : 0;
+    X.dc = P.taps > 1 ? 32 - X.dt * P.cs : 32;
+    X.ka[0] = kpos(P, (tid & 3) << 3);
+    X.ka[1] = kpos(P, ((tid & 3) << 3) + 4);
+#pragma unroll
+    for (int h = 0; h < TN / 32; ++h) X.kb[h] = kpos(P, kr + (1024 / TN) * h);
+  }
+}
+
+// Byte offset of row h's source pixel under tap d, channel ch; FAR outside.
+template <int TM, int TN, bool TAP1>
+__device__ __forceinline__ uint32_t split_row(const ConvProb& P, const SplitCtx<TM, TN, TAP1>& X, int h, Tap d, int ch) {
+  const bool ok = ((unsigned)(X.y[h] + d.dy) < (1u << P.smap.h_log)) & ((unsigned)(X.x[h] + d.dx) < (1u << P.smap.w_log));
+  return ok ? (uint32_t)(X.off[h] + ((d.dy << P.smap.w_log) + d.dx) * P.smap.ld + ch) * 4u : FAR;
+}
+
+__device__ __forceinline__ float4 ld4s(__amdgpu_buffer_rsrc_t r, uint32_t off_bytes, uint32_t scalar_bytes) {
+  const v4u v = __builtin_amdgcn_raw_buffer_load_b128(r, (int)off_bytes, (int)scalar_bytes, 0);
+  return make_float4(__uint_as_float(v[0]), __uint_as_float(v[1]), __uint_as_float(v[2]), __uint_as_float(v[3]));
+}
+
+template <int TM, int TN, bool TAP1>
+__device__ __forceinline__ void split_load(const ConvProb& P, SplitCtx<TM, TN, TAP1>& X, int k0,
+                                           float4 (&fa)[TM / 32], float4 (&fb)[TN / 32]) {
+  const int tid = threadIdx.x, kg = (tid & 3) << 3;
+  if (TAP1) {
+    // within a tap only the scalar offsets move
+    const Tap d = tap_of(P, X.t);
+    if (X.c == 0) {
+#pragma unroll
+      for (int h = 0; h < TM / 64; ++h) X.va[h] = split_row<TM, TN, TAP1>(P, X, h, d, kg);
+    }
+#pragma unroll
+    for (int h = 0; h < TM / 64; ++h) {
+      fa[2 * h] = ld4s(X.ra, X.va[h], (uint32_t)X.c * 4u);
+      fa[2 * h + 1] = ld4s(X.ra, X.va[h], (uint32_t)X.c * 4u + 16u);
+    }
+    const int r0 = d.wt * P.cs + X.c;
+#pragma unroll
+    for (int h = 0; h < TN / 32; ++h) fb[h] = ld4s(X.rb, X.bcol, (uint32_t)((r0 + (1024 / TN) * h) * P.N) * 4u);
+    X.c += SK_DEEP;
+    if (X.c >= P.cs) {
+      X.c = 0;
+      ++X.t;
+    }
+  } else {
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      const bool kok = k0 + kg + 4 * e < P.K;
+      const Tap d = tap_of(P, X.ka[e].t);
+#pragma unroll
+      for (int h = 0; h < TM / 64; ++h) {
+        const uint32_t o = split_row<TM, TN, TAP1>(P, X, h, d, X.ka[e].c);
+        fa[2 * h + e] = ld4(X.ra, kok ? o : FAR);
+      }
+      advance(P, X.ka[e], X.dt, X.dc);
+    }
+#pragma unroll
+    for (int h = 0; h < TN / 32; ++h) {
+      const uint32_t o = X.bcol + (uint32_t)((tap_of(P, X.kb[h].t).wt * P.cs + X.kb[h].c) * P.N) * 4u;
+      fb[h] = ld4(X.rb, k0 + tid / (TN / 4) + (1024 / TN) * h < P.K ? o : FAR);
+      advance(P, X.kb[h], X.dt, X.dc);
+    }
+  }
+}
+
+// The operand slices, split, into their three LDS tiles each.
+template <int TM, int TN, bool AGAIN>
+__device__ __forceinline__ void split_store(bool lead, const float4 (&fa)[TM / 32], const float4 (&fb)[TN / 32], char* lds) {
+  using T = SplitTile<TM, TN>;
+  const int tid = threadIdx.x;
+#pragma unroll
+  for (int h = 0; h < TM / 64; ++h) {
+    const float4 u = fa[2 * h], v = fa[2 * h + 1];
+    uint4 p[3];
+    split2<AGAIN>(lead, u.x, u.y, p[0].x, p[1].x, p[2].x);
+    split2<AGAIN>(lead, u.z, u.w, p[0].y, p[1].y, p[2].y);
+    split2<AGAIN>(lead, v.x, v.y, p[0].z, p[1].z, p[2].z);
+    split2<AGAIN>(lead, v.z, v.w, p[0].w, p[1].w, p[2].w);
+    const int o = rk_off((tid >> 2) + 64 * h, tid & 3);
+#pragma unroll
+    for (int q = 0; q < 3; ++q) *reinterpret_cast<uint4*>(lds + q * T::A_PIECE + o) = p[q];
+  }
+#pragma unroll
+  for (int h = 0; h < TN / 32; ++h) {
+    uint2 p[3];
+    split2<AGAIN>(lead, fb[h].x, fb[h].y, p[0].x, p[1].x, p[2].x);
+    split2<AGAIN>(lead, fb[h].z, fb[h].w, p[0].y, p[1].y, p[2].y);
+    const int o = (tid / (TN / 4) + (1024 / TN) * h) * km_pitch(TN) + ((tid % (TN / 4)) << 3);
+#pragma unroll
+    for (int q = 0; q < 3; ++q) *reinterpret_cast<uint2*>(lds + 3 * T::A_PIECE + q * T::B_PIECE + o) = p[q];
+  }
+}
+
+// The K loop: acc = the tile's products (lead: only those of the first pieces).
+template <int TM, int TN, bool TAP1, bool AGAIN>
+__device__ __forceinline__ void split_mainloop(const ConvProb& P, int m0, int n0, bool lead, char* lds,
+                                               v16f (&acc)[TM / 64][TN / 64]) {
+  using T = SplitTile<TM, TN>;
+  const char* At = lds;
+  const char* Bt = lds + 3 * T::A_PIECE;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int wm = (wave >> 1) * (TM / 2), wn = (wave & 1) * (TN / 2);
+  SplitCtx<TM, TN, TAP1> X;
+  split_setup<TM, TN, TAP1>(P, m0, n0, X);
+  v16f low[T::TI][T::TJ];  // the five smaller piece products (AGAIN: no registers for their own sums)
+#pragma unroll
+  for (int i = 0; i < T::TI; ++i)
+#pragma unroll
+    for (int j = 0; j < T::TJ; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = low[i][j][r] = 0.f;
+  float4 fa[T::A_F4], fb[T::B_F4];
+  if (!AGAIN) split_load<TM, TN, TAP1>(P, X, 0, fa, fb);
+  for (int k0 = 0; k0 < P.K; k0 += SK_DEEP) {
+    if (AGAIN) split_load<TM, TN, TAP1>(P, X, k0, fa, fb);  // no registers for a slice in flight
+    __syncthreads();  // every wave has read the previous slice
+    split_store<TM, TN, AGAIN>(lead, fa, fb, lds);
+    if (!AGAIN && k0 + SK_DEEP < P.K) split_load<TM, TN, TAP1>(P, X, k0 + SK_DEEP, fa, fb);
+    __syncthreads();
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk) {
+      v8bf a[T::TI][3], bq[T::TJ][3];
+#pragma unroll
+      for (int q = 0; q < 3; ++q) {
+#pragma unroll
+        for (int i = 0; i < T::TI; ++i) a[i][q] = rk_frag(At + q * T::A_PIECE, wm + 32 * i, kk, lane);
+#pragma unroll
+        for (int j = 0; j < T::TJ; ++j) bq[j][q] = km_frag<TN>(Bt + q * T::B_PIECE, wn + 32 * j, kk, lane);
+      }
+#pragma unroll
+      for (int s = 2; s >= 0; --s) {
+        if (AGAIN && lead && s) continue;
+#pragma unroll
+        for (int q = 0; q <= s; ++q)
+#pragma unroll
+          for (int i = 0; i < T::TI; ++i)
+#pragma unroll
+            for (int j = 0; j < T::TJ; ++j) {
+              v16f& to = s && !AGAIN ? low[i][j] : acc[i][j];
+              to = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i][q], bq[j][s - q], to, 0, 0, 0);
+            }
+      }
+    }
+  }
+  if (!AGAIN) {
+#pragma unroll
+    for (int i = 0; i < T::TI; ++i)
+#pragma unroll
+      for (int j = 0; j < T::TJ; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[i][j][r] += low[i][j][r];
+  }
+}
+
+// Stores of the wave's 32-row strips.  Register r of lane l of a 32 x 32 MFMA
+// tile is row 8 (r / 4) + 4 (l / 32) + r % 4, column l % 32.
+template <int TM, int TN>
+__device__ __forceinline__ void split_strip(const ConvProb& P, const v16f (&acc)[TN / 64], int i, int m0, int n0,
+                                            float slope, bool rewrite, char* lds) {
+  constexpr int W = TN / 2, PITCH = W + 4;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  float* st = reinterpret_cast<float*>(lds) + wave * 32 * PITCH;
+  // the wave's own part of LDS: the previous strip's reads are issued before
+  // these writes, and LDS runs a wave's accesses in order
+  __builtin_amdgcn_wave_barrier();
+#pragma unroll
+  for (int j = 0; j < TN / 64; ++j)
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+      st[(8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)) * PITCH + 32 * j + (lane & 31)] = acc[j][r];
+  __builtin_amdgcn_wave_barrier();
+  const int m = m0 + (wave >> 1) * (TM / 2) + 32 * i, n = n0 + (wave & 1) * W;
+  if (rewrite) store_strip<32, W, CONV_FWD, true>(P, m, n, 0, slope, st);
+  else store_strip<32, W, CONV_FWD, false>(P, m, n, 0, slope, st);
+}
+
+template <int TM, int TN>
+__device__ __forceinline__ void split_write(const ConvProb P, const v16f (&acc)[TM / 64][TN / 64], int m0, int n0,
+                                            float slope, bool rewrite, char* lds) {
+  split_strip<TM, TN>(P, acc[0], 0, m0, n0, slope, rewrite, lds);
+  if (TM > 64) split_strip<TM, TN>(P, acc[TM / 64 - 1], 1, m0, n0, slope, rewrite, lds);
+}
+
+template <int TM, int TN, bool TAP1>
+__global__ __launch_bounds__(NT, 2) void conv_split_kernel(const ConvProb* __restrict__ probs, ConvGroups grp,
+                                                           float slope) {
+  using T = SplitTile<TM, TN>;
+  __shared__ __align__(16) char lds[T::LDS];
+  const int b = blockIdx.x;
+  int gi = 0;
+#pragma unroll
+  for (int q = 1; q < GEMM_MAX_GROUPS; ++q)
+    if (q < grp.n && b >= grp.first_block[q]) gi = q;
+  // first_block is a multiple of 8, so (b - first_block) % 8 is still the XCD
+  const int rel = xcd_remap(b - grp.first_block[gi], grp.blocks[gi]);
+  if (rel >= grp.real_tiles[gi]) return;
+  const int pi = grp.first_prob[gi] + rel / grp.tiles_per_prob[gi];
+  const int lt = rel % grp.tiles_per_prob[gi];
+  const ConvProb P = probs[pi];
+  const int m0 = (lt / P.tiles_n) * TM, n0 = (lt % P.tiles_n) * TN;
+  v16f acc[T::TI][T::TJ];
+  split_mainloop<TM, TN, TAP1, false>(P, m0, n0, false, lds, acc);
+  bool bad = false;
+#pragma unroll
+  for (int i = 0; i < T::TI; ++i)
+#pragma unroll
+    for (int j = 0; j < T::TJ; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) bad |= non_finite(acc[i][j][r]);
+  // the descriptor is read again: kept in scalar registers over the K loop, it
+  // would spill
+  const ConvProb* again = probs + pi;
+  asm volatile("" : "+s"(again));
+  if (__builtin_expect(__syncthreads_or(bad) == 0, 1)) {
+    split_write<TM, TN>(*again, acc, m0, n0, slope, false, lds);
+    return;
+  }
+#pragma unroll 1
+  for (int lead = 0; lead < 2; ++lead) {
+    asm volatile("" : "+s"(again));
+    __syncthreads();
+    split_mainloop<TM, TN, TAP1, true>(*again, m0, n0, lead != 0, lds, acc);
+    __syncthreads();
+    split_write<TM, TN>(*again, acc, m0, n0, slope, lead != 0, lds);
+  }
+}
+
+}  // namespace
+
+hipError_t launch_conv_split(const ConvProb* d_probs, const ConvGroups& grp, int total_blocks, const ConvVariant& v,
+                             float slope, hipStream_t s, hipEvent_t ev_start, hipEvent_t ev_stop) {
+  if (grp.n <= 0 || total_blocks <= 0) return hipSuccess;
+  if (v.mode != CONV_FWD || v.bt) return hipErrorInvalidValue;
+#define LIPZ_CS(TM, TN)                                                                                              \
+  if (v.tap1)                                                                                                        \
+    hipExtLaunchKernelGGL((conv_split_kernel<TM, TN, true>), dim3(total_blocks), dim3(NT), 0, s, ev_start, ev_stop, \
+                          0, d_probs, grp, slope);                                                                   \
+  else                                                                                                               \
+    hipExtLaunchKernelGGL((conv_split_kernel<TM, TN, false>), dim3(total_blocks), dim3(NT), 0, s, ev_start,         \
+                          ev_stop, 0, d_probs, grp, slope)
+  if (v.tm == 128 && v.tn == 128) { LIPZ_CS(128, 128); }
+  else if (v.tm == 128 && v.tn == 64) { LIPZ_CS(128, 64); }
+  else if (v.tm == 64 && v.tn == 64) { LIPZ_CS(64, 64); }
+  else return hipErrorInvalidValue;
+#undef LIPZ_CS
+  return hipGetLastError();
+}
+
+}  // namespace lipz

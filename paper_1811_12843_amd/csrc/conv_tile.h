@@ -1,9 +1,10 @@
-// Device code shared by the convolution kernels (conv.hip, conv_wide.hip):
+// Device code shared by the convolution kernels (conv.hip, conv_wide.hip, conv_split.hip):
 // bounded loads, position maps and tap shifts of a ConvProb; the stores of
 // the wide tiles.
 #pragma once
 
 #include "lipz_internal.h"
+#include "split.h"
 
 namespace lipz {
 
@@ -85,7 +86,7 @@ __device__ __forceinline__ int map_off(const PosMap& m, Pos q) {
   return ((((q.img << m.h_log) + y) << m.w_log) + x) * m.ld;
 }
 
-// The wide tiles (conv_wide.hip) run K in 32-deep slices of
+// The wide tiles (conv_wide.hip, conv_split.hip) run K in 32-deep slices of
 // whole float4s.
 constexpr int SK_DEEP = 32;              // K of one slice
 constexpr uint32_t FAR = 0x80000000u;    // a byte offset that stays past every extent when an extent is added
@@ -107,9 +108,6 @@ __device__ __forceinline__ void advance(const ConvProb& P, KPos& q, int dt, int 
     ++q.t;
   }
 }
-
-// True when x is an infinity or NaN (also under finite-math assumptions).
-__device__ __forceinline__ bool non_finite(float x) { return (__float_as_uint(x) & 0x7F800000u) == 0x7F800000u; }
 
 // Stores of a strip of ROWS rows of a wave's part of the tile, from the wave's
 // own part of LDS (rows of W + 4 floats), where the caller put its sums: as

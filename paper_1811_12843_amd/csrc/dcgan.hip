@@ -677,14 +677,17 @@ int add_conv_launch(DcPlan& P, const std::vector<ConvProb>& ps, const ConvVarian
 
 // The problems of one dependent phase as launches: those of one variant
 // (kernel, operand layouts and width) together, the rest on conv_kernel.
-void add_conv_phase(DcPlan& P, const std::vector<ConvProb>& ps, std::vector<DcOp>& ops) {
+// keep_order: a training step, whose sums keep conv_kernel's order (a
+// pre-activation near 0 that rounds to its other side changes the gradients
+// it masks); the evaluation's forwards take the bf16 matrix cores.
+void add_conv_phase(DcPlan& P, const std::vector<ConvProb>& ps, std::vector<DcOp>& ops, bool keep_order) {
   std::vector<std::pair<ConvVariant, std::vector<ConvProb>>> sets;
   for (const ConvProb& p : ps) {
     ConvVariant v;
     memset(&v, 0, sizeof(v));
     const bool bt = p.mode == CONV_FWD && p.wsn != 1;
     if (conv_tile_ok(p)) {
-      v.kernel = CONV_K_WIDE;
+      v.kernel = keep_order || p.mode != CONV_FWD || bt ? CONV_K_WIDE : CONV_K_SPLIT;
       v.mode = p.mode;
       v.bt = bt;
       v.tap1 = p.mode == CONV_FWD && p.cs % 32 == 0;
@@ -821,7 +824,7 @@ void dc_build(lipz_grid* g) {
     std::vector<DcOp>& ops = P.train_ops[par];
     ops.clear();
     auto gemm = [&](const std::vector<GemmProb>& ps) { ops.push_back({DC_GEMM, add_phase(g, ps)}); };
-    auto conv = [&](const std::vector<ConvProb>& ps) { add_conv_phase(P, ps, ops); };
+    auto conv = [&](const std::vector<ConvProb>& ps) { add_conv_phase(P, ps, ops, true); };
     auto Gw = [&](int c, int l) { return S.Gp + c * sG + G.L[l].off_w; };
     auto Dw = [&](int c, int l) { return S.Dp + c * sD + D.L[l].off_w; };
     auto gsz = [&](int k) { return (int64_t)B * side_sq(G.L[k].out_log) * G.L[k].nb; };
@@ -1148,7 +1151,7 @@ void dc_build(lipz_grid* g) {
               ps.push_back(convT_phase(P.gex[k - 1] + (c * 5 + i) * egsz(k - 1), B, L.in_log, L.cin, Gw(own, k), L.cout,
                                        P.gex[k] + (c * 5 + i) * egsz(k), r, q, EPI_STORE, 0, nullptr));
         }
-      add_conv_phase(P, ps, ev);
+      add_conv_phase(P, ps, ev, false);
       ebn(k);
     }
     {
@@ -1163,7 +1166,7 @@ void dc_build(lipz_grid* g) {
           cs.push_back(col_prob(cols, P.Xe + (size_t)c * 6 * B * xd + (size_t)(1 + i) * B * xd, B, P.img_log, P.ic,
                                 EPI_BIAS_ACT, Lg.act, S.Gp + own * sG + Lg.off_b, nullptr));
         }
-      add_conv_phase(P, ps, ev);
+      add_conv_phase(P, ps, ev, false);
       col2im(ev, cs);
     }
     {
@@ -1188,7 +1191,7 @@ void dc_build(lipz_grid* g) {
             ps.push_back(conv_fwd(P.dey[(k - 1) & 1] + (c * 5 + j) * NIe * dsz(k - 1), NIe, L.in_log, L.cin, Dw(own, k),
                                   L.cout, out, EPI_BIAS_ACT, L.act, S.Dp + own * sD + L.off_b));
         }
-      add_conv_phase(P, ps, ev);
+      add_conv_phase(P, ps, ev, false);
     }
     {
       std::vector<DotProb> ds;
@@ -1253,6 +1256,7 @@ namespace {
 hipError_t launch_conv(const ConvPhase& ph, const ConvProb* d, float slope, hipStream_t s, hipEvent_t e0 = nullptr,
                        hipEvent_t e1 = nullptr) {
   switch (ph.var.kernel) {
+    case CONV_K_SPLIT: return launch_conv_split(d, ph.grp, ph.tiles, ph.var, slope, s, e0, e1);
     case CONV_K_WIDE: return launch_conv_wide(d, ph.grp, ph.tiles, ph.var, slope, s, e0, e1);
     default: return launch_conv_grouped(d, ph.grp, ph.tiles, slope, s, e0, e1);
   }
@@ -1570,7 +1574,7 @@ extern "C" lipz_status lipz_test_conv(void* hip_stream, void* d_desc, int32_t ki
   memset(&v, 0, sizeof(v));
   v.kernel = kernel;
   if (kernel != CONV_K_ANY) {
-    if (kernel != CONV_K_WIDE) return LIPZ_E_INVAL;
+    if (kernel != CONV_K_WIDE && kernel != CONV_K_SPLIT) return LIPZ_E_INVAL;
     if (!((tile_m == 128 && (tile_n == 128 || tile_n == 64)) || (tile_m == 64 && tile_n == 64))) return LIPZ_E_INVAL;
     for (const ConvProb& p : ps)
       if (!conv_tile_ok(p)) return LIPZ_E_INVAL;
@@ -1579,6 +1583,7 @@ extern "C" lipz_status lipz_test_conv(void* hip_stream, void* d_desc, int32_t ki
     v.mode = ps[0].mode;
     v.bt = ps[0].mode == CONV_FWD && ps[0].wsn != 1;
     v.tap1 = ps[0].mode == CONV_FWD && ps[0].cs % 32 == 0;
+    if (kernel == CONV_K_SPLIT && (v.mode != CONV_FWD || v.bt)) return LIPZ_E_INVAL;
   }
   DcPlan P;
   const ConvPhase& ph = P.cph[add_conv_launch(P, ps, v)];

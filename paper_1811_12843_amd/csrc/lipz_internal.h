@@ -435,9 +435,11 @@ struct ConvGroups {
 //     problems of any kind side by side;
 //   CONV_K_WIDE: conv_wide_kernel (conv_wide.hip), tm x tn tiles, the sums of
 //     conv_kernel in its order, bit for bit;
-//     It has one tile, mode and operand layout per launch: tm x tn outputs,
-//     mode, transposed weights (bt), whole slices within one tap (tap1).
-enum ConvKernel : int32_t { CONV_K_ANY = 0, CONV_K_WIDE = 1 };
+//   CONV_K_SPLIT: conv_split_kernel (conv_split.hip), forward problems with
+//     row-major weights, fp32 products on the bf16 matrix cores.
+// The last two have one tile, mode and operand layout per launch: tm x tn
+// outputs, mode, transposed weights (bt), whole slices within one tap (tap1).
+enum ConvKernel : int32_t { CONV_K_ANY = 0, CONV_K_WIDE = 1, CONV_K_SPLIT = 2 };
 struct ConvVariant {
   int32_t kernel, tm, tn, mode, bt, tap1;
   bool operator==(const ConvVariant& o) const {
@@ -446,6 +448,8 @@ struct ConvVariant {
 };
 hipError_t launch_conv_wide(const ConvProb* d_probs, const ConvGroups& grp, int total_blocks, const ConvVariant& v,
                             float slope, hipStream_t s, hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);
+hipError_t launch_conv_split(const ConvProb* d_probs, const ConvGroups& grp, int total_blocks, const ConvVariant& v,
+                             float slope, hipStream_t s, hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);
 
 // Launch every problem of one phase (problems in device memory).
 hipError_t launch_conv_grouped(const ConvProb* d_probs, const ConvGroups& grp, int total_blocks, float slope,

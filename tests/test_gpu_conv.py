@@ -1,7 +1,8 @@
 """The convolution kernels on the GPU, one convolution at a time
 (lipz_test_conv), at sizes that leave tiles, slices and splits partly filled:
 against torch's fp64 convolutions on the CPU, and the wide fp32 tiles bit for
-bit against the 64 x 64 ones."""
+bit against the 64 x 64 ones; infinities and NaNs of the bf16 kernel against
+fp32 products."""
 import numpy as np
 import pytest
 
@@ -15,7 +16,7 @@ import torch.nn.functional as F  # noqa: E402
 
 import paper_1811_12843_amd as L  # noqa: E402
 
-ANY, WIDE = 0, 1
+ANY, WIDE, SPLIT = 0, 1, 2
 SLOPE = 0.2
 KINDS = ["conv", "convT", "conv_dgrad", "convT_dgrad", "conv_wgrad", "convT_wgrad"]
 # (images, log2 side, c_in, c_out): channels a multiple of 32 (a slice within one tap) and not, one and several
@@ -110,7 +111,8 @@ def test_kernels_match_fp64(kind, shape):
     if (co if kind in ("conv", "convT", "conv_wgrad", "convT_wgrad") else ci) <= 16:
         pytest.skip("no wide tile is that narrow")
     base = None
-    for kernel, tile in [(ANY, (0, 0))] + [(WIDE, t) for t in TILES]:
+    split = [(SPLIT, t) for t in TILES] if kind in ("conv", "convT") else []
+    for kernel, tile in [(ANY, (0, 0))] + [(WIDE, t) for t in TILES] + split:
         print(f"[case] {kind} {shape} kernel {kernel} tile {tile}", flush=True)
         got = _run(kind, shape, kernel, tile, x, w, bias, aux)
         full = got.double().sum(0) if kind.endswith("wgrad") else got.double()
@@ -119,3 +121,30 @@ def test_kernels_match_fp64(kind, shape):
             base = got
         elif kernel == WIDE:
             assert torch.equal(got, base), (tile, float((got - base).abs().max()))
+
+
+@pytest.mark.parametrize("kind", ["conv", "convT"])
+@pytest.mark.parametrize("shape", [(9, 3, 32, 64), (17, 2, 36, 132)])
+def test_split_kernel_keeps_infinities_and_nans(kind, shape):
+    """Operands with infinities, NaNs, zeros and a value next to fp32's largest: the same outputs are infinite (with
+    the same sign) and NaN as with fp32 products, and the others agree."""
+    x, w, bias, aux = _problem(kind, shape, seed=3)
+    f = x.view(-1)
+    f[::53] = 0.0
+    f[5], f[f.numel() // 2], f[f.numel() // 3] = float("inf"), float("-inf"), float("nan")
+    f[f.numel() // 4] = 3.395e38  # finite, but bf16 rounds it to infinity
+    w.view(-1)[::31] = 0.0
+    w.view(-1)[7] = float("inf")
+    print(f"[case] non-finite {kind} {shape}", flush=True)
+    # the finite outputs are sums without those operands; both sides are within the rounding of their K products
+    zeroed = [torch.nan_to_num(t, 0.0, 0.0, 0.0).double() for t in (x, w, aux, bias)]
+    bound = 2 * (16 * shape[2] + 8) * 2.0 ** -24 * _reference(kind, *zeroed)[1] + 1e-30
+    base = _run(kind, shape, ANY, (0, 0), x, w, bias, aux)
+    inf, fin = torch.isinf(base), torch.isfinite(base)
+    assert fin.any() and inf.any() and torch.isnan(base).any()
+    for tile in TILES:
+        got = _run(kind, shape, SPLIT, tile, x, w, bias, aux)
+        assert torch.equal(torch.isnan(got), torch.isnan(base)), tile
+        assert torch.equal(torch.isinf(got), inf), tile
+        assert torch.equal(got[inf], base[inf]), tile
+        assert torch.all((got[fin].double() - base[fin].double()).abs() <= bound[fin]), tile
