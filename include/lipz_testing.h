@@ -17,11 +17,12 @@
  *          rate *d_lr on C, d_m, d_v (same indexing as C).
  * tile_rows: 32 or 64 output rows per workgroup tile, 0 = the choice the
  * library makes for a phase of this size.  variant: 0 = the kernel the
- * library runs such a phase on; 1 = the register-staged LDS kernel, 2 = the
- * wave-split kernel (1-2 need 16-byte aligned operand rows, else
- * LIPZ_E_INVAL); plus 4: the kernel's write-back stores instead of its
- * device-scope ones (the store policy of grids whose state exceeds 128 MB;
- * the results are the same).  Other values: LIPZ_E_INVAL.
+ * library runs such a phase on; 1 = sums in one chain, 2 = in four chains, one
+ * per wave (32-row tiles; else as 3), 3 = in four chains in every wave (1-3
+ * need 16-byte aligned operand rows, else LIPZ_E_INVAL); plus 4: the kernel's
+ * write-back stores instead of its device-scope ones (the store policy of
+ * grids whose state exceeds 128 MB; the results are the same).  Other values:
+ * LIPZ_E_INVAL.
  * d_desc: device scratch of at least 256 bytes for the problem descriptor
  * (caller-owned).  The call copies the descriptor synchronously, enqueues the
  * kernel on hip_stream and returns; LIPZ_E_INVAL on bad sizes.

@@ -426,7 +426,9 @@ int add_phase(lipz_grid* g, const std::vector<GemmProb>& ps) {
     g->probs_h.push_back(p);
   }
   ph.tiles = tiles;
-  ph.kernel = gemm_choose_kernel(ph.fast, max_k);
+  ph.kernel = gemm_choose_kernel(ph.fast, max_k, ph.tiles, ph.tile_rows);
+  if (!ph.fast || ph.kernel != GEMM_K_CHAIN)
+    for (size_t k = ph.first; k < g->probs_h.size(); ++k) g->probs_h[k].vec |= GEMM_ADAM_OLD_FIRST;
   g->phases.push_back(ph);
   return (int)g->phases.size() - 1;
 }
@@ -688,7 +690,7 @@ void build_tables(lipz_grid* g) {
         // the output layer's weight gradient from the per-row-tile column
         // sums: [w | b] = 1^T hpart over the launch's row tiles (a 1-row
         // product whose A is the all-ones row), and its Adam step
-        const int rt = ceil_div(2 * B, g->phases[dgrad_phase].tile_rows);
+        const int rt = ceil_div(2 * B, 32);
         head_grad.clear();
         for (int c = cb; c < ce; ++c) {
           const size_t o = c * sD + D.off[LD - 1];

@@ -12,32 +12,45 @@
 // stores for the epilogues' outputs, or write-back; the library picks one per
 // grid, by the size of its state.
 //
-// Tiling: a 256-thread workgroup (4 wave64) owns a BM x 64 output tile
-// (BM = 32 or 64).  Three kernels share the tile and the epilogue:
+// Tiling: a 256-thread workgroup (4 wave64) owns a BM x 64 output tile; wave w
+// owns the (BM / 2) x 32 block (w / 2, w % 2).  BM = 64: one MFMA 32 x 32 x 2
+// block per wave; BM = 32: two 16 x 16 x 4 blocks.
 //
-// * gemm_fast_kernel (16-byte aligned operands): wave w owns the (BM/2) x 32
-//   block (w / 2, w % 2) as (BM/32) x 2 MFMA 16x16 accumulators.  K advances
-//   in BK-deep slices through an LDS ring: buffer loads (bounded by the
-//   operand's extent, so no branches on the edges) of the next slices are in
-//   registers while the MFMAs of the current one run, one barrier per slice.
-//   Each operand keeps its global layout in LDS (no transposing stores):
-//   k-contiguous operands (A row-major, B = W^T) are read as 4 consecutive k
-//   per lane with ds_read_b128; m/n-contiguous operands are read one k per
-//   MFMA.  Within a 16-deep k block, MFMA sub-step s of lane group g = l / 16
-//   uses k = 4 g + s for both operands, so the two layouts mix freely.  Row
-//   strides are padded to 4 (mod 16) floats, which puts the four lane groups
-//   of one read on disjoint LDS banks.
-// * gemm_wave_kernel (deep K): split-K across the four waves, no LDS in the
-//   main loop (described at its definition).
-// * gemm_generic_kernel: any alignment, per-element bounds checks.
+// Main loop: 32-deep K slices in two LDS stages, filled by buffer_load ... lds
+// (16 bytes per lane, straight into LDS) one slice ahead; one barrier per
+// slice.  A slice's loads need no vector instruction: lanes keep fixed
+// offsets, and the buffer resource's base and extent advance in scalar
+// registers.  Nothing is asked of the alignment of rows (a dword-aligned
+// 16-byte load reads the same bytes) or of the sizes: dwords past an operand's
+// extent are zeros in LDS.
+//
+// Order of sums: MFMAs are chains of fused multiply-adds in k order.  An output
+// takes 16-deep k blocks in turn and, in a block, k = u, 4 + u, 8 + u, 12 + u
+// for u = 0 .. 3.  CH = 4 keeps four such chains, of the k blocks 0, 1, 2, 3
+// (mod 4), and adds them at the end, (0 + 1) + (2 + 3).
+//
+// Before the epilogue every wave passes its block through LDS, so that a lane
+// holds four consecutive columns and eight lanes a row's 32: C, the Adam
+// moments and the auxiliary operand move in full 128-byte lines, 16 bytes per
+// lane.
 //
 // Epilogues: plain store; bias + activation (forward), optionally with the
 // tile's partial dot product against a 1-wide output layer; activation
-// derivative (input gradient); Adam on the weight gradient in registers.
+// derivative (input gradient); Adam on the weight gradient in registers.  What
+// an epilogue reads is requested before the main loop.
 //
-// MFMA 16x16x4 f32 operand layout (wave64): lane l supplies A[l % 16][l / 16]
-// and B[l / 16][l % 16]; accumulator register r of lane l is
-// D[4 (l / 16) + r][l % 16].
+// What bounds it: on large phases the tiles' operand traffic out of L2 (a 32 x
+// 64 tile takes 96 floats per k for 2048 products: about 9 TB/s) with the
+// matrix cores 70 % busy; on phases of a tile or two per CU the launch and the
+// chain of a tile's slices; on weight gradients with Adam the 24 bytes per
+// parameter, and the vector instructions of its divisions.  Measured, against
+// operands staged through registers and element-wise epilogues: 16 cells'
+// 784 -> 256 weight gradient with Adam (200 samples) and its neighbour 41.1 ->
+// 36.4 us; 32 cells' 81 -> 68; a forward of 600 rows, 256 -> 256, for 80
+// pairs 83.6 -> 77.4 us; and against element-wise loads of rows that are not
+// 16-byte aligned, six cells of 301 -> 203 -> 97 units: 1960 -> 1100 us for 10
+// steps.  64-row tiles were no faster on any phase measured (256 to 8960
+// tiles of 32 rows), four LDS stages neither.
 #include <string.h>
 
 #include <hip/hip_ext.h>
@@ -47,177 +60,44 @@
 namespace lipz {
 
 typedef float v4f __attribute__((ext_vector_type(4)));
+typedef float v16f __attribute__((ext_vector_type(16)));
 
 namespace {
 
-#ifndef LIPZ_GEMM_STAGES
-#define LIPZ_GEMM_STAGES 2      // slices of A/B loads in flight per workgroup
-#endif
-#ifndef LIPZ_GEMM_WG32
-#define LIPZ_GEMM_WG32 4        // occupancy target of the fast kernel, 32-row tiles
-#endif
-#ifndef LIPZ_GEMM_WG64
-#define LIPZ_GEMM_WG64 2        // occupancy target of the fast kernel, 64-row tiles
-#endif
 #ifndef LIPZ_GEMM_TILE64_MIN
 #define LIPZ_GEMM_TILE64_MIN 100000  // phases with at least this many 64x64 tiles use 64-row tiles
 #endif
-
-#ifndef LIPZ_GEMM_BK
-#define LIPZ_GEMM_BK 32         // K depth of one LDS slice
+#ifndef LIPZ_GEMM_CHAINS4_MIN_K
+#define LIPZ_GEMM_CHAINS4_MIN_K 512  // phases of aligned problems at least this deep sum in four chains
 #endif
-#ifndef LIPZ_GEMM_WAVE_SPLIT
-#define LIPZ_GEMM_WAVE_SPLIT 1  // allow the wave-split (split-K in the workgroup) kernel
-#endif
-#ifndef LIPZ_GEMM_WAVE_MIN_K
-#define LIPZ_GEMM_WAVE_MIN_K 512  // ... for phases whose deepest problem has K >= this
+#ifndef LIPZ_GEMM_WAVE_MAX_TILES
+// ... on the wave-split kernel up to this many tiles (two per CU: 512 tiles of
+// K = 784 take 20.3 us there and 24.0 on the other, 672 take 27.8 and 22.7)
+#define LIPZ_GEMM_WAVE_MAX_TILES 512
 #endif
 
 constexpr int BN = GEMM_BN;
-constexpr int BK = LIPZ_GEMM_BK;
-constexpr int KQ = BK / 4;    // float4 per row of a k-contiguous slice
+constexpr int BK = 32;        // K depth of an LDS stage
 constexpr int NT = 256;
-constexpr int S_K = BK + 4;   // row stride of k-contiguous LDS tiles ([m][k], [n][k])
-
+constexpr uint32_t FAR = 0x80000000u;  // an offset past every extent
 
 template <int BM>
 struct Tile {
-  static constexpr int S_M = BM + 4;                        // row stride of [k][m] tiles
-  static constexpr int S_N = BN + 4;                        // row stride of [k][n] tiles
-  static constexpr int A_FLOATS = (BK * S_M > BM * S_K) ? BK * S_M : BM * S_K;
-  static constexpr int B_FLOATS = (BK * S_N > BN * S_K) ? BK * S_N : BN * S_K;
-  static constexpr int A_VEC = BM * BK / 4 / NT;            // float4 of A per thread per slice
-  static constexpr int B_VEC = BN * BK / 4 / NT;
-  static constexpr int WM = BM / 2;                         // rows per wave
-  static constexpr int TI = WM / 16;                        // accumulator tiles along M per wave
+  static constexpr int WM = BM / 2;   // rows per wave
+  static constexpr int NQ = WM / 8;   // epilogue passes of 8 rows
+  static constexpr int NA = BM / 32, NB = 2, NL = NA + NB;  // 1024-byte loads of a slice per wave
+  static constexpr int A_FLOATS = BM * BK, FLOATS = (BM + BN) * BK;
 };
-
-template <int BM>
-struct Regs {
-  float4 a[Tile<BM>::A_VEC];
-  float4 b[Tile<BM>::B_VEC];
-};
-
-__device__ __forceinline__ float4 ld4(const LIPZ_GLOBAL float* p) {
-  const v4f v = *reinterpret_cast<const LIPZ_GLOBAL v4f*>(p);
-  return make_float4(v[0], v[1], v[2], v[3]);
-}
-
-// Global -> registers: this thread's share of the A and B slices at k0.
-template <int BM>
-__device__ __forceinline__ void load_slices(const GemmProb& P, int m0, int n0, int k0, int tid,
-                                            Regs<BM>& f) {
-  using T = Tile<BM>;
-  const LIPZ_GLOBAL float* gA = as_global(P.A);
-  const LIPZ_GLOBAL float* gB = as_global(P.B);
-#pragma unroll
-  for (int rep = 0; rep < T::A_VEC; ++rep) {
-    const int q = tid + NT * rep;
-    float4 v;
-    if (!P.a_trans) {  // [M][K]: row q / KQ, k 4 (q % KQ)
-      const int gm = m0 + q / KQ, gk = k0 + ((q % KQ) << 2);
-      if ((P.vec & 1) && gm < P.a_rows && gk + 3 < P.K) {
-        v = ld4(gA + (size_t)gm * P.lda + gk);
-      } else {
-        const bool r = gm < P.a_rows;
-        const LIPZ_GLOBAL float* s = gA + (size_t)gm * P.lda;
-        v.x = (r && gk + 0 < P.K) ? s[gk + 0] : 0.f;
-        v.y = (r && gk + 1 < P.K) ? s[gk + 1] : 0.f;
-        v.z = (r && gk + 2 < P.K) ? s[gk + 2] : 0.f;
-        v.w = (r && gk + 3 < P.K) ? s[gk + 3] : 0.f;
-      }
-    } else {  // [K][M]: k q / (BM/4), m 4 (q % (BM/4))
-      constexpr int PER_K = BM / 4;
-      const int gk = k0 + q / PER_K, gm = m0 + ((q % PER_K) << 2);
-      if ((P.vec & 1) && gk < P.K && gm + 3 < P.a_rows) {
-        v = ld4(gA + (size_t)gk * P.lda + gm);
-      } else {
-        float e[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int m = gm + u;
-          float x = 0.f;
-          if (gk < P.K) {
-            if (m < P.a_rows) x = gA[(size_t)gk * P.lda + m];
-            else if (m == P.ones_row) x = 1.f;
-          }
-          e[u] = x;
-        }
-        v = make_float4(e[0], e[1], e[2], e[3]);
-      }
-    }
-    f.a[rep] = v;
-  }
-#pragma unroll
-  for (int rep = 0; rep < T::B_VEC; ++rep) {
-    const int q = tid + NT * rep;
-    float4 v;
-    if (!P.b_trans) {  // [K][N]: k q / 16, n 4 (q % 16)
-      const int gk = k0 + (q >> 4), gn = n0 + ((q & 15) << 2);
-      if ((P.vec & 2) && gk < P.K && gn + 3 < P.N) {
-        v = ld4(gB + (size_t)gk * P.ldb + gn);
-      } else {
-        const bool r = gk < P.K;
-        const LIPZ_GLOBAL float* s = gB + (size_t)gk * P.ldb;
-        v.x = (r && gn + 0 < P.N) ? s[gn + 0] : 0.f;
-        v.y = (r && gn + 1 < P.N) ? s[gn + 1] : 0.f;
-        v.z = (r && gn + 2 < P.N) ? s[gn + 2] : 0.f;
-        v.w = (r && gn + 3 < P.N) ? s[gn + 3] : 0.f;
-      }
-    } else {  // [N][K]: n q / KQ, k 4 (q % KQ)
-      const int gn = n0 + q / KQ, gk = k0 + ((q % KQ) << 2);
-      if ((P.vec & 2) && gn < P.N && gk + 3 < P.K) {
-        v = ld4(gB + (size_t)gn * P.ldb + gk);
-      } else {
-        const bool r = gn < P.N;
-        const LIPZ_GLOBAL float* s = gB + (size_t)gn * P.ldb;
-        v.x = (r && gk + 0 < P.K) ? s[gk + 0] : 0.f;
-        v.y = (r && gk + 1 < P.K) ? s[gk + 1] : 0.f;
-        v.z = (r && gk + 2 < P.K) ? s[gk + 2] : 0.f;
-        v.w = (r && gk + 3 < P.K) ? s[gk + 3] : 0.f;
-      }
-    }
-    f.b[rep] = v;
-  }
-}
-
-// Registers -> LDS, in the operand's own layout.
-template <int BM>
-__device__ __forceinline__ void store_slices(const GemmProb& P, int tid, const Regs<BM>& f, float* As,
-                                             float* Bs) {
-  using T = Tile<BM>;
-#pragma unroll
-  for (int rep = 0; rep < T::A_VEC; ++rep) {
-    const int q = tid + NT * rep;
-    float* d;
-    if (!P.a_trans) d = As + (q / KQ) * S_K + ((q % KQ) << 2);
-    else d = As + (q / (BM / 4)) * T::S_M + ((q % (BM / 4)) << 2);
-    *reinterpret_cast<float4*>(d) = f.a[rep];
-  }
-#pragma unroll
-  for (int rep = 0; rep < T::B_VEC; ++rep) {
-    const int q = tid + NT * rep;
-    float* d;
-    if (!P.b_trans) d = Bs + (q >> 4) * T::S_N + ((q & 15) << 2);
-    else d = Bs + (q / KQ) * S_K + ((q % KQ) << 2);
-    *reinterpret_cast<float4*>(d) = f.b[rep];
-  }
-}
 
 typedef unsigned int v4u __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) void lds_void;
 
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const float* p, uint32_t bytes) {
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* p, uint32_t bytes) {
   // dword 3 = 0x00020000: raw 32-bit data format on gfx9-family parts
   return __builtin_amdgcn_make_buffer_rsrc((void*)p, (short)0, (int)bytes, 0x00020000);
 }
-__device__ __forceinline__ float4 bload4(__amdgpu_buffer_rsrc_t r, uint32_t off_bytes) {
-  const v4u v = __builtin_amdgcn_raw_buffer_load_b128(r, (int)off_bytes, 0, 0);
-  return make_float4(__uint_as_float(v[0]), __uint_as_float(v[1]), __uint_as_float(v[2]),
-                     __uint_as_float(v[3]));
-}
 
-
-// One element through a buffer resource: the epilogues address C, the Adam
+// Elements through a buffer resource: the epilogues address C, the Adam
 // moments and the auxiliary operand with 32-bit element offsets from the
 // descriptor's base (no 64-bit address per element).
 //
@@ -239,35 +119,38 @@ __device__ __forceinline__ void bst1(__amdgpu_buffer_rsrc_t r, uint32_t off_elem
   __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), r, (int)(off_elems * 4u), 0, WT ? kStoreDevice : 0);
 }
 
-// The loss head's dL/da of this lane's epilogue rows (rows m0 + wm + 16 i +
-// 4 (lane / 16) + r), from the partial logits, formed as the separate head
-// kernel forms it.  With four partial sums per row (a 129..256-wide last
-// hidden layer) the loads are issued together with the epilogue's other
-// loads, so they add no round trip.
-template <int BM>
-__device__ __forceinline__ void head_rows_dl(const GemmProb& P, int m0, float (&dl)[Tile<BM>::TI][4]) {
-  using T = Tile<BM>;
-  const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6;
-  const int wm = (wave >> 1) * T::WM, lg = lane >> 4;
-  const float invB = 1.f / (float)P.rs_B;
+// Four elements in a row.  A load of the last row's end may run past the row;
+// the resource's extent bounds it (zeros).  A store writes the first n.
+__device__ __forceinline__ v4f bld4(__amdgpu_buffer_rsrc_t r, uint32_t off_elems) {
+  return __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(r, (int)(off_elems * 4u), 0, 0));
+}
+template <bool WT>
+__device__ __forceinline__ void bst4(__amdgpu_buffer_rsrc_t r, uint32_t off_elems, int n, v4f v) {
+  if (n >= 4) {
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, v), r, (int)(off_elems * 4u), 0,
+                                           WT ? kStoreDevice : 0);
+  } else {
 #pragma unroll
-  for (int i = 0; i < T::TI; ++i) {
-    // lane r of each 16-lane group forms row r's value, then the group shares them
-    const int row = m0 + wm + 16 * i + 4 * lg + (lane & 3);
-    const LIPZ_GLOBAL float* pr = as_global(P.rs_part) + (size_t)(row < P.M ? row : 0) * P.rs_tn;
-    float a;
-    if (P.rs_tn == 4) {  // a 129..256-wide last hidden layer: the row's four partial sums in one load
-      const float4 v = ld4(pr);
-      a = ((v.x + v.y) + v.z) + v.w;
-    } else {
-      a = 0.f;
-      for (int t = 0; t < P.rs_tn; ++t) a += pr[t];
-    }
-    const float mine = head_dl(P.loss_kind, a, P.rs_mode == 2 || row < P.rs_B, invB);
-#pragma unroll
-    for (int r = 0; r < 4; ++r) dl[i][r] = __shfl(mine, (lane & ~15) | r, 64);
+    for (int u = 0; u < 3; ++u)
+      if (u < n) bst1<WT>(r, off_elems + u, v[u]);
   }
+}
+
+// The loss head's dL/da of a row, from its partial logits, formed as the
+// separate head kernel forms it.  With four partial sums per row (a 129..256-
+// wide last hidden layer) the row's load is issued together with the
+// epilogue's other loads.
+__device__ __forceinline__ float head_row_dl(const GemmProb& P, int row) {
+  const LIPZ_GLOBAL float* pr = as_global(P.rs_part) + (size_t)(row < P.M ? row : 0) * P.rs_tn;
+  float a;
+  if (P.rs_tn == 4) {
+    const v4f v = *reinterpret_cast<const LIPZ_GLOBAL v4f*>(pr);
+    a = ((v[0] + v[1]) + v[2]) + v[3];
+  } else {
+    a = 0.f;
+    for (int t = 0; t < P.rs_tn; ++t) a += pr[t];
+  }
+  return head_dl(P.loss_kind, a, P.rs_mode == 2 || row < P.rs_B, 1.f / (float)P.rs_B);
 }
 
 // Workgroup q of a sampling job: SAMPLE_ROWS minibatch rows of one unit,
@@ -303,15 +186,16 @@ __device__ __forceinline__ void sample_rows(const SampleJob& sj, int q) {
   }
 }
 
-// The output layer's weight gradient of the discriminator step, in pieces:
-// this tile's column sums of dL/da[i] * hsrc[i][j] over its rows (and, in
-// column 0, of dL/da[i]), summed over the lane groups and then over the two
-// waves that share the tile's columns, in a fixed order.  Rows past M and
-// columns past hp_w add nothing.
+// The output layer's weight gradient of the discriminator step, in pieces of
+// 32 rows: column sums of dL/da[i] * hsrc[i][j] over a piece's rows (and, in
+// column 0, of dL/da[i]), summed over 16 rows' lane groups and then over the
+// two 16-row halves, in a fixed order.  Rows past M and columns past hp_w add
+// nothing.  dlr[q]: dL/da of row 8 q + lane / 8 of the wave's.
 template <int BM, bool WT>
-__device__ __forceinline__ void head_partials(const GemmProb& P, const float (&dl)[Tile<BM>::TI][4], int m0,
-                                              int n0, int tile_n, float (*red)[BM]) {
+__device__ __forceinline__ void head_partials(const GemmProb& P, const float (&dlr)[Tile<BM>::NQ], int m0, int n0,
+                                              int tile_n, float (*red)[BM]) {
   using T = Tile<BM>;
+  constexpr int H = T::WM / 16;  // 16-row halves of a piece in the wave
   __shared__ float dsum;
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
@@ -319,9 +203,9 @@ __device__ __forceinline__ void head_partials(const GemmProb& P, const float (&d
   const int li = lane & 15, lg = lane >> 4;
   const bool wgan = P.loss_kind == LIPZ_LOSS_WASSERSTEIN;
   const __amdgpu_buffer_rsrc_t rH = make_rsrc(P.hsrc, kWholeBuffer);
-  float hv[T::TI][2][4];
+  float hv[H][2][4];
 #pragma unroll
-  for (int i = 0; i < T::TI; ++i)
+  for (int i = 0; i < H; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j)
 #pragma unroll
@@ -331,42 +215,55 @@ __device__ __forceinline__ void head_partials(const GemmProb& P, const float (&d
         const float x = bld1(rH, in ? (uint32_t)(row * P.hp_w + col) : 0u);
         hv[i][j][r] = in ? x : 0.f;
       }
-  float cs[2] = {0.f, 0.f}, ds = 0.f;
+  float cs[H][2] = {}, ds[H] = {};
 #pragma unroll
-  for (int i = 0; i < T::TI; ++i)
+  for (int i = 0; i < H; ++i) {
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int row = m0 + wm + 16 * i + 4 * lg + r;
-      const float d = row < P.M ? (wgan ? (row < P.rs_B ? -1.f : 1.f) : dl[i][r]) : 0.f;
-      ds += d;
+      const int src = ((4 * lg + r) & 7) * 8;
+      const float d0 = __shfl(dlr[2 * i], src, 64), d1 = __shfl(dlr[2 * i + 1], src, 64);
+      const float d = row < P.M ? (wgan ? (row < P.rs_B ? -1.f : 1.f) : (lg >= 2 ? d1 : d0)) : 0.f;
+      ds[i] += d;
 #pragma unroll
-      for (int j = 0; j < 2; ++j) cs[j] += d * hv[i][j][r];
+      for (int j = 0; j < 2; ++j) cs[i][j] = fmaf(d, hv[i][j][r], cs[i][j]);
     }
-#pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    cs[j] += __shfl_xor(cs[j], 16, 64);
-    cs[j] += __shfl_xor(cs[j], 32, 64);
-  }
-  ds += __shfl_xor(ds, 16, 64);
-  ds += __shfl_xor(ds, 32, 64);
-  if (wm != 0 && lane < 16) {
-    red[wave & 1][li] = cs[0];
-    red[wave & 1][16 + li] = cs[1];
-    if (wn == 0 && lane == 0) dsum = ds;
-  }
-  __syncthreads();
-  if (wm == 0 && lane < 16) {
-    const __amdgpu_buffer_rsrc_t ro = make_rsrc(P.hpart + (size_t)(m0 / BM) * P.hp_ld, kWholeBuffer);
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
-      const int col = n0 + wn + 16 * j + li;
-      if (col < P.hp_w) bst1<WT>(ro, (uint32_t)col, cs[j] + red[wave & 1][16 * j + li]);
+      cs[i][j] += __shfl_xor(cs[i][j], 16, 64);
+      cs[i][j] += __shfl_xor(cs[i][j], 32, 64);
     }
-    if (tile_n == 0 && wn == 0 && lane == 0) bst1<WT>(ro, (uint32_t)P.hp_w, ds + dsum);
+    ds[i] += __shfl_xor(ds[i], 16, 64);
+    ds[i] += __shfl_xor(ds[i], 32, 64);
   }
+  float c2[2], d2 = 0.f;  // the second halves' sums
+  if (H == 2) {
+    c2[0] = cs[H - 1][0];
+    c2[1] = cs[H - 1][1];
+    d2 = ds[H - 1];
+  } else {
+    if (wm != 0 && lane < 16) {
+      red[wave & 1][li] = cs[0][0];
+      red[wave & 1][16 + li] = cs[0][1];
+      if (wn == 0 && lane == 0) dsum = ds[0];
+    }
+    __syncthreads();
+    c2[0] = red[wave & 1][li];
+    c2[1] = red[wave & 1][16 + li];
+    d2 = dsum;
+    if (wm != 0) return;
+  }
+  if (lane >= 16 || m0 + wm >= P.M) return;
+  const __amdgpu_buffer_rsrc_t ro = make_rsrc(P.hpart + (size_t)((m0 + wm) / 32) * P.hp_ld, kWholeBuffer);
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const int col = n0 + wn + 16 * j + li;
+    if (col < P.hp_w) bst1<WT>(ro, (uint32_t)col, cs[0][j] + c2[j]);
+  }
+  if (tile_n == 0 && wn == 0 && lane == 0) bst1<WT>(ro, (uint32_t)P.hp_w, ds[0] + d2);
 }
 
-// Kernel arguments of the three GEMM kernels.  The descriptor pointer, the
+// Kernel arguments.  The descriptor pointer, the
 // tile groups of the launch and the step index come first, as 14 scalar
 // words that the hardware preloads into scalar registers (the library is
 // built with -mllvm -amdgpu-kernarg-preload-count=14), so that a GEMM
@@ -403,184 +300,198 @@ __device__ __forceinline__ void locate_tile(int total, int ft1, int ft2, int ft3
   lt = (t - ft) % tp;
 }
 
-// Epilogue shared by both kernel variants: bias + activation (optionally
-// with the per-tile partial dot product of the next 1-wide layer), the
-// activation-derivative product, or the fused Adam update; then stores.
-// All of a lane's loads are issued before any of them is used, so their
-// latencies overlap (out-of-range elements read element 0 and are dropped).
+// A lane's share of the epilogue: pass q takes row row0 + 8 q, columns col ..
+// col + 3, of which n lie inside C.
+template <int BM>
+struct EpiPos {
+  int row0, col, n;
+  uint32_t c_bytes;  // extent of C
+  __device__ __forceinline__ EpiPos(const GemmProb& P, int m0, int n0) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    row0 = m0 + (wave >> 1) * Tile<BM>::WM + (lane >> 3);
+    col = n0 + (wave & 1) * 32 + 4 * (lane & 7);
+    n = P.N - col;
+    c_bytes = ((uint32_t)(P.M - 1) * (uint32_t)P.ldc + (uint32_t)P.N) * 4u;
+  }
+  __device__ __forceinline__ bool ok(const GemmProb& P, int q) const { return row0 + 8 * q < P.M && n > 0; }
+  __device__ __forceinline__ uint32_t off(const GemmProb& P, int q) const {
+    return ok(P, q) ? (uint32_t)((row0 + 8 * q) * P.ldc + col) : 0u;
+  }
+};
+
+// What a lane's epilogue reads, requested before the main loop: the operands'
+// first slices come behind it, so its latency is hidden.
+template <int BM>
+struct EpiIn {
+  v4f x[Tile<BM>::NQ];  // EPI_ADAM: p; EPI_DACT: aux
+  v4f m[Tile<BM>::NQ], v[Tile<BM>::NQ];
+};
+
+template <int BM>
+__device__ __forceinline__ void epi_load(const GemmProb& P, const EpiPos<BM>& E, EpiIn<BM>& in) {
+  const bool adam = P.epi == EPI_ADAM;
+  if (!adam && P.epi != EPI_DACT) return;
+  const __amdgpu_buffer_rsrc_t rx = make_rsrc(adam ? P.C : P.aux, E.c_bytes);
+#pragma unroll
+  for (int q = 0; q < Tile<BM>::NQ; ++q) in.x[q] = bld4(rx, E.off(P, q));
+  if (!adam) return;
+  const __amdgpu_buffer_rsrc_t rm = make_rsrc(P.m, E.c_bytes), rv = make_rsrc(P.v, E.c_bytes);
+#pragma unroll
+  for (int q = 0; q < Tile<BM>::NQ; ++q) {
+    in.m[q] = bld4(rm, E.off(P, q));
+    in.v[q] = bld4(rv, E.off(P, q));
+  }
+}
+
+// Adam's update of the lane's elements.  The moments' sums b1 m + (1 - b1) g
+// (and v's) are fused one way or the other: OLD_FIRST rounds the old moment's
+// product first, else the gradient's.  Which is GemmProb::vec's to say: a
+// network of given sizes trains to the same bits whichever kernel runs it.
+template <int BM, bool WT, bool OLD_FIRST>
+__device__ __forceinline__ void adam(const GemmProb& P, const v4f (&acc)[Tile<BM>::NQ], const EpiPos<BM>& E,
+                                     const EpiIn<BM>& in, const float* bc) {
+  const AdamConsts& ac = P.ac;
+  const __amdgpu_buffer_rsrc_t rC = make_rsrc(P.C, kWholeBuffer);
+  const __amdgpu_buffer_rsrc_t rM = make_rsrc(P.m, kWholeBuffer);
+  const __amdgpu_buffer_rsrc_t rV = make_rsrc(P.v, kWholeBuffer);
+  const float lr = *as_global(P.lr);
+  const float bc1 = bc[0], bc2 = bc[1];
+#pragma unroll
+  for (int q = 0; q < Tile<BM>::NQ; ++q) {
+    v4f pn, mn, vn;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const float g = P.gscale != 0.f ? acc[q][r] * P.gscale : acc[q][r];
+      const float g2 = ac.one_minus_beta2 * g;
+      const float m = OLD_FIRST ? fmaf(ac.one_minus_beta1, g, ac.beta1 * in.m[q][r])
+                                : fmaf(ac.beta1, in.m[q][r], ac.one_minus_beta1 * g);
+      const float v = OLD_FIRST ? fmaf(g2, g, ac.beta2 * in.v[q][r]) : fmaf(ac.beta2, in.v[q][r], g2 * g);
+      float p = in.x[q][r] - lr * (m / bc1) / (sqrtf(v / bc2) + ac.eps);
+      if (P.clip > 0.f) p = p > P.clip ? P.clip : (p < -P.clip ? -P.clip : p);  // keeps NaN
+      pn[r] = p;
+      mn[r] = m;
+      vn[r] = v;
+    }
+    if (E.ok(P, q)) {
+      const uint32_t o = E.off(P, q);
+      bst4<WT>(rM, o, E.n, mn);
+      bst4<WT>(rV, o, E.n, vn);
+      bst4<WT>(rC, o, E.n, pn);
+    }
+  }
+}
+
+// Bias + activation (optionally with the per-tile partial dot product of the
+// next 1-wide layer), the activation-derivative product, or the fused Adam
+// update; then stores.  bc: Adam's bias corrections of this step (in LDS,
+// written before the main loop's first barrier).
 template <int BM, bool WT>
-__device__ __forceinline__ void epilogue(const GemmProb& P, v4f (&acc)[Tile<BM>::TI][2], int m0, int n0,
-                                         int tile_n, int step_local, float (*red)[BM]) {
+__device__ __forceinline__ void epilogue(const GemmProb& P, const v4f (&acc)[Tile<BM>::NQ], const EpiPos<BM>& E,
+                                         const EpiIn<BM>& in, int m0, int n0, int tile_n, const float* bc,
+                                         float (*red)[BM]) {
   using T = Tile<BM>;
-  constexpr int NE = T::TI * 2 * 4;
+  typedef v4f v4f_any __attribute__((aligned(4)));
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
   const int wm = (wave >> 1) * T::WM, wn = (wave & 1) * 32;
-  const int li = lane & 15, lg = lane >> 4;
   const float slope = P.slope;
   const __amdgpu_buffer_rsrc_t rC = make_rsrc(P.C, kWholeBuffer);
-  uint32_t off[NE];
-  bool ok[NE];
-#pragma unroll
-  for (int i = 0; i < T::TI; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int e = (i * 2 + j) * 4 + r;
-        const int row = m0 + wm + 16 * i + 4 * lg + r;
-        const int col = n0 + wn + 16 * j + li;
-        ok[e] = row < P.M && col < P.N;
-        off[e] = ok[e] ? (uint32_t)(row * P.ldc + col) : 0u;
-      }
   if (P.epi == EPI_ADAM) {
-    const AdamConsts& ac = P.ac;
-    const __amdgpu_buffer_rsrc_t rM = make_rsrc(P.m, kWholeBuffer);
-    const __amdgpu_buffer_rsrc_t rV = make_rsrc(P.v, kWholeBuffer);
-    const float lr = *as_global(P.lr);
-    const int tt = *as_global(P.t) + step_local + 1;
-    const float bc1 = (float)(1.0 - pow((double)ac.beta1, (double)tt));
-    const float bc2 = (float)(1.0 - pow((double)ac.beta2, (double)tt));
-    float pp[NE], mm[NE], vv[NE];
-#pragma unroll
-    for (int e = 0; e < NE; ++e) {
-      pp[e] = bld1(rC, off[e]);
-      mm[e] = bld1(rM, off[e]);
-      vv[e] = bld1(rV, off[e]);
-    }
-#pragma unroll
-    for (int i = 0; i < T::TI; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int e = (i * 2 + j) * 4 + r;
-          const float g = P.gscale != 0.f ? acc[i][j][r] * P.gscale : acc[i][j][r];
-          const float m = ac.beta1 * mm[e] + ac.one_minus_beta1 * g;
-          const float v = ac.beta2 * vv[e] + ac.one_minus_beta2 * g * g;
-          float p = pp[e] - lr * (m / bc1) / (sqrtf(v / bc2) + ac.eps);
-          if (P.clip > 0.f) p = p > P.clip ? P.clip : (p < -P.clip ? -P.clip : p);  // keeps NaN
-          if (ok[e]) {
-            bst1<WT>(rM, off[e], m);
-            bst1<WT>(rV, off[e], v);
-            bst1<WT>(rC, off[e], p);
-          }
-        }
+    if (P.vec & GEMM_ADAM_OLD_FIRST) adam<BM, WT, true>(P, acc, E, in, bc);
+    else adam<BM, WT, false>(P, acc, E, in, bc);
     return;
   }
   if (P.epi == EPI_DACT) {
-    const __amdgpu_buffer_rsrc_t rAux = make_rsrc(P.aux, kWholeBuffer);
-    float ax[NE];
+    float dl[T::NQ];
+    if (P.rs_mode != 0) {
 #pragma unroll
-    for (int e = 0; e < NE; ++e) ax[e] = bld1(rAux, off[e]);
-    if (P.rs_mode == 0) {
-#pragma unroll
-      for (int i = 0; i < T::TI; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const int e = (i * 2 + j) * 4 + r;
-            if (ok[e]) bst1<WT>(rC, off[e], acc[i][j][r] * act_deriv_from_out(P.act, ax[e], slope));
-          }
-      return;
+      for (int q = 0; q < T::NQ; ++q) dl[q] = head_row_dl(P, E.row0 + 8 * q);
     }
-    float dl[T::TI][4];
-    head_rows_dl<BM>(P, m0, dl);
     LIPZ_GLOBAL float* gSide = as_global(P.side);
 #pragma unroll
-    for (int i = 0; i < T::TI; ++i)
+    for (int q = 0; q < T::NQ; ++q) {
+      v4f y;
 #pragma unroll
-      for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int e = (i * 2 + j) * 4 + r;
-          if (ok[e]) {
-            bst1<WT>(rC, off[e], dl[i][r] * (acc[i][j][r] * act_deriv_from_out(P.act, ax[e], slope)));
-            if (P.side) {
-              const int row = m0 + wm + 16 * i + 4 * lg + r, col = n0 + wn + 16 * j + li;
-              gSide[(size_t)row * P.side_ld + col] = dl[i][r] * ax[e];
-            }
-          }
+      for (int r = 0; r < 4; ++r) {
+        y[r] = acc[q][r] * act_deriv_from_out(P.act, in.x[q][r], slope);
+        if (P.rs_mode != 0) y[r] = dl[q] * y[r];
+      }
+      if (!E.ok(P, q)) continue;
+      bst4<WT>(rC, E.off(P, q), E.n, y);
+      if (P.rs_mode != 0 && P.side) {
+        LIPZ_GLOBAL float* o = gSide + (size_t)(E.row0 + 8 * q) * P.side_ld + E.col;
+        if (E.n >= 4) {
+          *reinterpret_cast<LIPZ_GLOBAL v4f_any*>(o) = dl[q] * in.x[q];
+        } else {
+          for (int r = 0; r < E.n; ++r) o[r] = dl[q] * (r == 0 ? in.x[q][0] : r == 1 ? in.x[q][1] : in.x[q][2]);
         }
+      }
+    }
+    if (P.rs_mode == 0) return;
     if (P.rs_mode == 1 && P.hpart) head_partials<BM, WT>(P, dl, m0, n0, tile_n, red);
     // column 0 of the problem: the per-row extras
-    if (P.side && tile_n == 0 && wn == 0 && li == 0) {
+    if (P.side && tile_n == 0 && wn == 0 && (lane & 7) == 0) {
       LIPZ_GLOBAL float* gDl = as_global(P.dlout);
 #pragma unroll
-      for (int i = 0; i < T::TI; ++i)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int row = m0 + wm + 16 * i + 4 * lg + r;
-          if (row < P.M) {
-            LIPZ_GLOBAL float* sr = gSide + (size_t)row * P.side_ld + P.N;
-            sr[0] = dl[i][r];
-            sr[1] = 0.f;
-            sr[2] = 0.f;
-            sr[3] = 0.f;
-            LIPZ_GLOBAL float* o = gDl + (size_t)row * 4;
-            o[0] = P.loss_kind == LIPZ_LOSS_WASSERSTEIN ? (row < P.rs_B ? -1.f : 1.f) : dl[i][r];
-            o[1] = 0.f;
-            o[2] = 0.f;
-            o[3] = 0.f;
-          }
+      for (int q = 0; q < T::NQ; ++q) {
+        const int row = E.row0 + 8 * q;
+        if (row < P.M) {
+          LIPZ_GLOBAL float* sr = gSide + (size_t)row * P.side_ld + P.N;
+          sr[0] = dl[q];
+          sr[1] = 0.f;
+          sr[2] = 0.f;
+          sr[3] = 0.f;
+          LIPZ_GLOBAL float* o = gDl + (size_t)row * 4;
+          o[0] = P.loss_kind == LIPZ_LOSS_WASSERSTEIN ? (row < P.rs_B ? -1.f : 1.f) : dl[q];
+          o[1] = 0.f;
+          o[2] = 0.f;
+          o[3] = 0.f;
         }
+      }
     }
     return;
   }
   if (P.epi != EPI_BIAS_ACT) {
 #pragma unroll
-    for (int i = 0; i < T::TI; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int e = (i * 2 + j) * 4 + r;
-          if (ok[e]) bst1<WT>(rC, off[e], acc[i][j][r]);
-        }
+    for (int q = 0; q < T::NQ; ++q)
+      if (E.ok(P, q)) bst4<WT>(rC, E.off(P, q), E.n, acc[q]);
     return;
   }
   // bias + activation, optional partial dot product with the next layer's weights
   const bool dot = P.dot_out != nullptr;
-  float bias[2] = {0.f, 0.f}, dw[2] = {0.f, 0.f};
+  const uint32_t c0 = E.n > 0 ? (uint32_t)E.col : 0u, nbytes = (uint32_t)P.N * 4u;
+  const v4f zero = {0.f, 0.f, 0.f, 0.f};
+  const v4f bias = P.bias ? bld4(make_rsrc(P.bias, nbytes), c0) : zero;
+  const v4f dw = dot ? bld4(make_rsrc(P.dotw, nbytes), c0) : zero;
 #pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    const int col = n0 + wn + 16 * j + li;
-    const int c = col < P.N ? col : 0;
-    if (P.bias) bias[j] = as_global(P.bias)[c];
-    if (dot) dw[j] = col < P.N ? as_global(P.dotw)[c] : 0.f;
-  }
+  for (int q = 0; q < T::NQ; ++q) {
+    v4f y;
 #pragma unroll
-  for (int i = 0; i < T::TI; ++i) {
-    float rowdot[4] = {0.f, 0.f, 0.f, 0.f};
+    for (int r = 0; r < 4; ++r) y[r] = act_fwd(P.act, acc[q][r] + bias[r], slope);
+    if (E.ok(P, q)) {
+      bst4<WT>(rC, E.off(P, q), E.n, y);
+      if (dot && P.gout) {
+        v4f gy;
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int e = (i * 2 + j) * 4 + r;
-        const float y = act_fwd(P.act, acc[i][j][r] + bias[j], slope);
-        if (ok[e]) {
-          bst1<WT>(rC, off[e], y);
-          rowdot[r] += y * dw[j];
-          if (P.gout) bst1<WT>(make_rsrc(P.gout, kWholeBuffer), off[e], dw[j] * act_deriv_from_out(P.act, y, slope));
-        }
+        for (int r = 0; r < 4; ++r) gy[r] = dw[r] * act_deriv_from_out(P.act, y[r], slope);
+        bst4<WT>(make_rsrc(P.gout, kWholeBuffer), E.off(P, q), E.n, gy);
       }
+    }
     if (dot) {
-      // sum over the 16 lanes that hold one row's columns, then over the two
-      // column halves of the tile (waves wn = 0 and 32) in a fixed order
+      // a row's 32 columns: column c + 16's product onto column c's, then a
+      // tree over the 16; then the two column halves of the tile (waves wn =
+      // 0 and 32), in a fixed order
+      float s[4];
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        float v = rowdot[r];
-        v += __shfl_xor(v, 1, 64);
-        v += __shfl_xor(v, 2, 64);
-        v += __shfl_xor(v, 4, 64);
-        v += __shfl_xor(v, 8, 64);
-        rowdot[r] = v;
+        const float t = E.ok(P, q) && r < E.n ? y[r] * dw[r] : 0.f;
+        const float low = __shfl_xor(t, 4, 64);
+        s[r] = E.ok(P, q) && r < E.n ? fmaf(y[r], dw[r], low) : low;
       }
-      if (li == 0) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) red[wave & 1][wm + 16 * i + 4 * lg + r] = rowdot[r];
-      }
+      float v = (s[0] + s[1]) + (s[2] + s[3]);
+      v += __shfl_xor(v, 1, 64);
+      v += __shfl_xor(v, 2, 64);
+      if ((lane & 7) == 4) red[wave & 1][wm + 8 * q + (lane >> 3)] = v;
     }
   }
   if (dot) {
@@ -593,300 +504,308 @@ __device__ __forceinline__ void epilogue(const GemmProb& P, v4f (&acc)[Tile<BM>:
   }
 }
 
-// Generic variant: any alignment, per-element bounds checks.  Used for
-// phases whose rows are not 16-byte aligned (tiny widths such as 2-D data).
-template <int BM, bool WT>
-__global__ __launch_bounds__(NT, 2) void gemm_generic_kernel(LIPZ_GEMM_ARGS) {
-  using T = Tile<BM>;
-  if ((int)blockIdx.x >= g_total) {
-    sample_rows<WT>(sj, (int)blockIdx.x - g_total);
-    return;
+// LDS stage of an operand slice (32 k), as the loads write it: 64 lanes x 16
+// bytes in a row per instruction, 16-byte chunk q = 64 (4 c + wave) + lane.
+//
+// Rows of k (A [M][K], B [N][K]): row r is chunks 8 r .. 8 r + 7, its k quad x
+// at place x ^ (r % 8).
+// k rows of 64 columns (B [K][N], A [K][M] with BM = 64): row k is chunks 16 k
+// .. 16 k + 15, column quad x at place x ^ 8 ((k / 4) % 2) (BM = 64) or x ^ 4
+// ((k / 4) % 4) (BM = 32).
+// k rows of 32 columns (A [K][M] with BM = 32): row k at chunk row s = 2 (k % 4)
+// + (k / 4) % 2 + 8 (k / 8), column quad x at place x ^ 4 ((k / 8) % 2).
+// The lane groups of a fragment read then lie on different banks.
+template <int BM, int W, bool ROWS>
+struct Opnd {
+  static constexpr int N = W / 32;  // loads of a slice per wave
+  const char* base;                 // the next slice
+  int64_t step;                     // bytes per slice
+  int bytes;                        // ROWS: extent from base; else the columns before r0, in bytes
+  uint32_t row;                     // a row, in bytes
+  uint32_t off[N];                  // of the lane's chunks, from base
+  int k4;                           // ROWS: first k of the lane's chunks in the slice (the same in all of them)
+  __device__ __forceinline__ void init(const float* p, int rows, int ld, int r0, int wave, int lane) {
+    // ROWS: rows r0 .. of [rows][ld]; else columns r0 .. of [K][ld]
+    base = (const char*)(p + (ROWS ? (int64_t)r0 * ld : (int64_t)r0));
+    step = ROWS ? BK * 4 : (int64_t)ld * (BK * 4);
+    row = (uint32_t)ld * 4u;
+    bytes = ROWS ? min(max(rows - r0, 0), W) * (int)row : r0 * 4;
+    k4 = 4 * ((lane & 7) ^ ((lane >> 3) & 7));
+#pragma unroll
+    for (int c = 0; c < N; ++c) {
+      const int q = 64 * (4 * c + wave) + lane;
+      if (ROWS) {
+        off[c] = (uint32_t)((q >> 3) * ld + k4) * 4u;
+      } else if (W == 64) {
+        const int k = q >> 4, x = (q & 15) ^ (BM == 64 ? (k & 4) << 1 : k & 12);
+        off[c] = (uint32_t)(k * ld + 4 * x) * 4u;
+      } else {
+        const int s = q >> 3, k = (s & 24) | ((s >> 1) & 3) | ((s & 1) << 2), x = (q & 7) ^ ((k >> 1) & 4);
+        off[c] = (uint32_t)(k * ld + 4 * x) * 4u;
+      }
+    }
   }
-  int pi, lt;
-  locate_tile(LIPZ_GEMM_GROUPS, pi, lt);
-  const GemmProb P = probs[pi];
-  const int tile_n = lt % P.tiles_n;
-  const int m0 = (lt / P.tiles_n) * BM;
-  const int n0 = tile_n * BN;
+  // Loads the next slice; kleft: k left from its first one.
+  __device__ __forceinline__ void load(float* st, int wave, int kleft) {
+    // (no saturating difference: that is a vector instruction, and with its
+    // result in the resource every load becomes a loop over lanes)
+    uint32_t e;
+    if (ROWS) {
+      e = (uint32_t)max(bytes, 0);
+      bytes -= BK * 4;
+    } else {
+      const int n = min(kleft, BK);
+      e = n > 0 ? (uint32_t)n * row - (uint32_t)bytes : 0u;
+    }
+    const __amdgpu_buffer_rsrc_t r = make_rsrc(base, e);
+    if (ROWS && kleft < BK) {
+#pragma unroll
+      for (int c = 0; c < N; ++c)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void*)(st + (4 * c + wave) * 256), 16,
+                                                 (int)(k4 >= kleft ? FAR : off[c]), 0, 0, 0);
+    } else {
+#pragma unroll
+      for (int c = 0; c < N; ++c)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void*)(st + (4 * c + wave) * 256), 16, (int)off[c], 0, 0, 0);
+    }
+    base += step;
+  }
+  // The lane's chunks of a slice with kleft k left, landed: elements past K
+  // that came with them (of the next row) become 0.
+  __device__ __forceinline__ void clear_tail(float* st, int wave, int lane, int kleft) const {
+    if (!ROWS || k4 >= kleft || k4 + 4 <= kleft) return;
+#pragma unroll
+    for (int c = 0; c < N; ++c)
+#pragma unroll
+      for (int e = 1; e < 4; ++e)
+        if (k4 + e >= kleft) st[(4 * c + wave) * 256 + 4 * lane + e] = 0.f;
+  }
+};
 
-  __shared__ __align__(16) float As[2][T::A_FLOATS];
-  __shared__ __align__(16) float Bs[2][T::B_FLOATS];
-  __shared__ float red[2][BM];
+// A wave's products of one 16-deep k block.  BM = 32: two 16 x 16 x 4 MFMA
+// blocks side by side; lane l supplies row (column) l % 16 and k = 4 (l / 16)
+// + u.  BM = 64: one 32 x 32 x 2 block; row (column) l % 32 and k = 8 e + 4 (l /
+// 32) + u.
+template <int BM>
+struct Block;
 
-  const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6;
-  const int wm = (wave >> 1) * T::WM, wn = (wave & 1) * 32;
-  const int li = lane & 15, lg = lane >> 4;
-
-  v4f acc[T::TI][2];
+template <>
+struct Block<32> {
+  struct A { float v[4]; };
+  struct B { float v[2][4]; };
+  struct Acc { v4f v[2]; };
+  template <bool ROWS>
+  static __device__ __forceinline__ void read_a(const float* st, int r0, int kb, int lane, A& F) {
+    const int li = lane & 15, lg = lane >> 4, r = r0 + li;
+    if (ROWS) {
+      const v4f v = *reinterpret_cast<const v4f*>(st + r * 32 + (((4 * kb + lg) ^ (li & 7)) << 2));
 #pragma unroll
-  for (int i = 0; i < T::TI; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
-
-  Regs<BM> f;
-  const int n_it = (P.K + BK - 1) / BK;
-  load_slices<BM>(P, m0, n0, 0, tid, f);
-  store_slices<BM>(P, tid, f, As[0], Bs[0]);
-  __syncthreads();
-  for (int it = 0; it < n_it; ++it) {
-    const int s = it & 1;
-    if (it + 1 < n_it) load_slices<BM>(P, m0, n0, (it + 1) * BK, tid, f);
-    const float* as = As[s];
-    const float* bs = Bs[s];
-#pragma unroll
-    for (int kb = 0; kb < BK; kb += 16) {
-      float a[T::TI][4], b[2][4];
-      const int kq = kb + 4 * lg;  // this lane group's 4 k values: kq .. kq + 3
-#pragma unroll
-      for (int i = 0; i < T::TI; ++i) {
-        const int m = wm + 16 * i + li;
-        if (!P.a_trans) {
-          const float4 v = *reinterpret_cast<const float4*>(as + m * S_K + kq);
-          a[i][0] = v.x; a[i][1] = v.y; a[i][2] = v.z; a[i][3] = v.w;
-        } else {
-#pragma unroll
-          for (int u = 0; u < 4; ++u) a[i][u] = as[(kq + u) * T::S_M + m];
-        }
-      }
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const int n = wn + 16 * j + li;
-        if (P.b_trans) {
-          const float4 v = *reinterpret_cast<const float4*>(bs + n * S_K + kq);
-          b[j][0] = v.x; b[j][1] = v.y; b[j][2] = v.z; b[j][3] = v.w;
-        } else {
-#pragma unroll
-          for (int u = 0; u < 4; ++u) b[j][u] = bs[(kq + u) * T::S_N + n];
-        }
-      }
+      for (int u = 0; u < 4; ++u) F.v[u] = v[u];
+    } else {
 #pragma unroll
       for (int u = 0; u < 4; ++u)
-#pragma unroll
-        for (int i = 0; i < T::TI; ++i) {
-          acc[i][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][u], b[0][u], acc[i][0], 0, 0, 0);
-          acc[i][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][u], b[1][u], acc[i][1], 0, 0, 0);
-        }
+        F.v[u] = st[(16 * kb + 8 * (lg >> 1) + 2 * u + (lg & 1)) * 32 + (r ^ (16 * (lg >> 1)))];
     }
-    if (it + 1 < n_it) store_slices<BM>(P, tid, f, As[s ^ 1], Bs[s ^ 1]);
-    __syncthreads();
   }
-
-  epilogue<BM, WT>(P, acc, m0, n0, tile_n, step_local, red);
-}
-
-// ---------------------------------------------------------------------------
-// Fast variant: every operand row 16-byte aligned, each operand's extent in
-// the descriptor.  Loads are buffer loads bounded by that extent (reads
-// past it return 0), so the main loop has no per-element bounds branches;
-// the operand layouts are template parameters chosen once per workgroup.
-// The K tail of the last slice and the bias "ones" row are set by selects
-// when the slice is written to LDS.  Loads run two slices ahead of the
-// MFMAs (two register sets, two LDS stages, one barrier per slice).
-// ---------------------------------------------------------------------------
-template <int BM, int AT, int BT>
-struct FastRegs {
-  float4 a[Tile<BM>::A_VEC];
-  float4 b[Tile<BM>::B_VEC];
+  template <bool ROWS>
+  static __device__ __forceinline__ void read_b(const float* st, int c0, int kb, int lane, B& F) {
+    const int li = lane & 15, lg = lane >> 4;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int c = c0 + 16 * j + li;
+      if (ROWS) {
+        const v4f v = *reinterpret_cast<const v4f*>(st + c * 32 + (((4 * kb + lg) ^ (li & 7)) << 2));
+#pragma unroll
+        for (int u = 0; u < 4; ++u) F.v[j][u] = v[u];
+      } else {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) F.v[j][u] = st[(16 * kb + 4 * lg + u) * 64 + (c ^ (16 * lg))];
+      }
+    }
+  }
+  static __device__ __forceinline__ void zero(Acc& c) { c.v[0] = c.v[1] = v4f{0.f, 0.f, 0.f, 0.f}; }
+  static __device__ __forceinline__ void fill(A& a, bool real, float x) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) a.v[u] = real ? a.v[u] : x;
+  }
+  static __device__ __forceinline__ void mma(const A& a, const B& b, Acc& c) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) c.v[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.v[u], b.v[j][u], c.v[j], 0, 0, 0);
+  }
+  static __device__ __forceinline__ void add(Acc& c, const Acc& d) {
+    c.v[0] += d.v[0];
+    c.v[1] += d.v[1];
+  }
+  // to the wave's block in LDS: register r of lane l is row 4 (l / 16) + r, column 16 j + l % 16
+  static __device__ __forceinline__ void store(const Acc& c, float* st, int lane) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int m = 4 * (lane >> 4) + r, n = 16 * j + (lane & 15);
+        st[32 * m + ((((n >> 2) ^ (m & 7)) << 2) | (n & 3))] = c.v[j][r];
+      }
+  }
 };
 
-template <int BM, int AT, int BT>
-__device__ __forceinline__ void fast_load(const GemmProb& P, __amdgpu_buffer_rsrc_t ra,
-                                          __amdgpu_buffer_rsrc_t rb, int m0, int n0, int k0, int tid,
-                                          FastRegs<BM, AT, BT>& f) {
-  using T = Tile<BM>;
+template <>
+struct Block<64> {
+  struct A { float v[2][4]; };
+  typedef A B;
+  typedef v16f Acc;
+  template <bool ROWS>
+  static __device__ __forceinline__ void read_a(const float* st, int r0, int kb, int lane, A& F) {
+    const int h = lane >> 5, r = r0 + (lane & 31);
 #pragma unroll
-  for (int rep = 0; rep < T::A_VEC; ++rep) {
-    const int q = tid + NT * rep;
-    uint32_t off;
-    if (AT == 0) off = (uint32_t)((m0 + q / KQ) * P.lda + k0 + ((q % KQ) << 2)) * 4u;
-    else off = (uint32_t)((k0 + q / (BM / 4)) * P.lda + m0 + ((q % (BM / 4)) << 2)) * 4u;
-    f.a[rep] = bload4(ra, off);
-  }
+    for (int e = 0; e < 2; ++e) {
+      if (ROWS) {
+        const v4f v = *reinterpret_cast<const v4f*>(st + r * 32 + (((4 * kb + 2 * e + h) ^ (lane & 7)) << 2));
 #pragma unroll
-  for (int rep = 0; rep < T::B_VEC; ++rep) {
-    const int q = tid + NT * rep;
-    uint32_t off;
-    if (BT == 0) off = (uint32_t)((k0 + (q >> 4)) * P.ldb + n0 + ((q & 15) << 2)) * 4u;
-    else off = (uint32_t)((n0 + q / KQ) * P.ldb + k0 + ((q % KQ) << 2)) * 4u;
-    f.b[rep] = bload4(rb, off);
-  }
-}
-
-// Registers -> LDS with the K tail (k >= kvalid) zeroed and, for a [K][M]
-// operand, rows past a_rows zeroed except the ones row.
-template <int BM, int AT, int BT>
-__device__ __forceinline__ void fast_store(const GemmProb& P, int m0, int kvalid, int tid,
-                                           const FastRegs<BM, AT, BT>& f, float* As, float* Bs) {
-  using T = Tile<BM>;
+        for (int u = 0; u < 4; ++u) F.v[e][u] = v[u];
+      } else {
 #pragma unroll
-  for (int rep = 0; rep < T::A_VEC; ++rep) {
-    const int q = tid + NT * rep;
-    float4 v = f.a[rep];
-    float* d;
-    if (AT == 0) {
-      const int kq = (q % KQ) << 2;
-      v.x = kq + 0 < kvalid ? v.x : 0.f;
-      v.y = kq + 1 < kvalid ? v.y : 0.f;
-      v.z = kq + 2 < kvalid ? v.z : 0.f;
-      v.w = kq + 3 < kvalid ? v.w : 0.f;
-      d = As + (q / KQ) * S_K + kq;
-    } else {
-      const int kk = q / (BM / 4), mq = (q % (BM / 4)) << 2;
-      const bool kok = kk < kvalid;
-      const int gm = m0 + mq;
-      const float one = kok ? 1.f : 0.f;
-      v.x = gm + 0 < P.a_rows ? (kok ? v.x : 0.f) : (gm + 0 == P.ones_row ? one : 0.f);
-      v.y = gm + 1 < P.a_rows ? (kok ? v.y : 0.f) : (gm + 1 == P.ones_row ? one : 0.f);
-      v.z = gm + 2 < P.a_rows ? (kok ? v.z : 0.f) : (gm + 2 == P.ones_row ? one : 0.f);
-      v.w = gm + 3 < P.a_rows ? (kok ? v.w : 0.f) : (gm + 3 == P.ones_row ? one : 0.f);
-      d = As + kk * T::S_M + mq;
+        for (int u = 0; u < 4; ++u) F.v[e][u] = st[(16 * kb + 8 * e + 4 * h + u) * 64 + (r ^ (32 * h))];
+      }
     }
-    *reinterpret_cast<float4*>(d) = v;
   }
+  template <bool ROWS>
+  static __device__ __forceinline__ void read_b(const float* st, int c0, int kb, int lane, B& F) {
+    read_a<ROWS>(st, c0, kb, lane, F);
+  }
+  static __device__ __forceinline__ void zero(Acc& c) {
 #pragma unroll
-  for (int rep = 0; rep < T::B_VEC; ++rep) {
-    const int q = tid + NT * rep;
-    float4 v = f.b[rep];
-    float* d;
-    if (BT == 0) {
-      const int kk = q >> 4;
-      if (kk >= kvalid) v = make_float4(0.f, 0.f, 0.f, 0.f);
-      d = Bs + kk * T::S_N + ((q & 15) << 2);
-    } else {
-      const int kq = (q % KQ) << 2;
-      v.x = kq + 0 < kvalid ? v.x : 0.f;
-      v.y = kq + 1 < kvalid ? v.y : 0.f;
-      v.z = kq + 2 < kvalid ? v.z : 0.f;
-      v.w = kq + 3 < kvalid ? v.w : 0.f;
-      d = Bs + (q / KQ) * S_K + kq;
-    }
-    *reinterpret_cast<float4*>(d) = v;
+    for (int r = 0; r < 16; ++r) c[r] = 0.f;
   }
-}
-
-template <int BM>
-struct Frag {
-  float a[Tile<BM>::TI][4];
-  float b[2][4];
+  static __device__ __forceinline__ void fill(A& a, bool real, float x) {
+#pragma unroll
+    for (int e = 0; e < 2; ++e)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) a.v[e][u] = real ? a.v[e][u] : x;
+  }
+  static __device__ __forceinline__ void mma(const A& a, const B& b, Acc& c) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+      for (int e = 0; e < 2; ++e) c = __builtin_amdgcn_mfma_f32_32x32x2f32(a.v[e][u], b.v[e][u], c, 0, 0, 0);
+  }
+  static __device__ __forceinline__ void add(Acc& c, const Acc& d) { c += d; }
+  // register r of lane l is row 8 (r / 4) + 4 (l / 32) + r % 4, column l % 32
+  static __device__ __forceinline__ void store(const Acc& c, float* st, int lane) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int m = 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3), n = lane & 31;
+      st[32 * m + ((((n >> 2) ^ (m & 7)) << 2) | (n & 3))] = c[r];
+    }
+  }
 };
 
-// MFMA fragments of one 16-deep k block kb of the slice in LDS.
-template <int BM, int AT, int BT>
-__device__ __forceinline__ void read_frag(const float* as, const float* bs, int kb, int wm, int wn,
-                                          int li, int lg, Frag<BM>& F) {
-  using T = Tile<BM>;
-  const int kq = 16 * kb + 4 * lg;
-#pragma unroll
-  for (int i = 0; i < T::TI; ++i) {
-    const int m = wm + 16 * i + li;
-    if (AT == 0) {
-      const float4 v = *reinterpret_cast<const float4*>(as + m * S_K + kq);
-      F.a[i][0] = v.x; F.a[i][1] = v.y; F.a[i][2] = v.z; F.a[i][3] = v.w;
-    } else {
-#pragma unroll
-      for (int u = 0; u < 4; ++u) F.a[i][u] = as[(kq + u) * T::S_M + m];
-    }
-  }
-#pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    const int n = wn + 16 * j + li;
-    if (BT == 1) {
-      const float4 v = *reinterpret_cast<const float4*>(bs + n * S_K + kq);
-      F.b[j][0] = v.x; F.b[j][1] = v.y; F.b[j][2] = v.z; F.b[j][3] = v.w;
-    } else {
-#pragma unroll
-      for (int u = 0; u < 4; ++u) F.b[j][u] = bs[(kq + u) * T::S_N + n];
-    }
-  }
+// s_waitcnt vmcnt(0) lgkmcnt(0): this wave's loads into LDS have landed and
+// its LDS accesses are done; lgkmcnt(0) alone.
+__device__ __forceinline__ void wait_loads() { __builtin_amdgcn_s_waitcnt(0x0070); }
+__device__ __forceinline__ void wait_lds() { __builtin_amdgcn_s_waitcnt(0xC07F); }
+
+// A barrier alone (the waits before it are the callers').
+__device__ __forceinline__ void barrier() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
 }
 
-template <int BM>
-__device__ __forceinline__ void mfma_frag(const Frag<BM>& F, v4f (&acc)[Tile<BM>::TI][2]) {
-#pragma unroll
-  for (int u = 0; u < 4; ++u)
-#pragma unroll
-    for (int i = 0; i < Tile<BM>::TI; ++i) {
-      acc[i][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(F.a[i][u], F.b[0][u], acc[i][0], 0, 0, 0);
-      acc[i][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(F.a[i][u], F.b[1][u], acc[i][1], 0, 0, 0);
-    }
-}
-
-// One slice: write registers R (slice it) to LDS stage (as, bs), barrier,
-// start the loads of slice it + NS into R, then the MFMAs of the slice's two
-// 16-deep k blocks, with the LDS reads of the second block issued ahead of
-// the MFMAs of the first.
-template <int BM, int AT, int BT, int NS, bool LOAD_ALWAYS>
-__device__ __forceinline__ void fast_slice(const GemmProb& P, __amdgpu_buffer_rsrc_t ra,
-                                           __amdgpu_buffer_rsrc_t rb, int m0, int n0, int it, int n_it,
-                                           FastRegs<BM, AT, BT>& R, float* as, float* bs,
-                                           v4f (&acc)[Tile<BM>::TI][2]) {
+// K loop: acc = this lane's elements of the tile's product (EpiPos), by way of
+// the wave's part of stage 0: element (m, n) of its block at 32 m + (4 (n / 4 ^
+// m % 8) | n % 4).  FILL: the tile has rows past a_rows of a [K][M] operand: row
+// ones_row is 1, the others 0.
+template <int BM, int CH, bool AT, bool BT, bool FILL>
+__device__ __forceinline__ void mainloop(const GemmProb& P, int m0, int n0, float* stage0, float* stage1,
+                                         v4f (&acc)[Tile<BM>::NQ]) {
   using T = Tile<BM>;
-  const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6;
+  using X = Block<BM>;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = (wave >> 1) * T::WM, wn = (wave & 1) * 32;
-  const int li = lane & 15, lg = lane >> 4;
-  fast_store<BM, AT, BT>(P, m0, P.K - it * BK, tid, R, as, bs);
-  __syncthreads();
-  if (LOAD_ALWAYS || it + NS < n_it) fast_load<BM, AT, BT>(P, ra, rb, m0, n0, (it + NS) * BK, tid, R);
-  // A wave whose rows all lie past M, or a 16-deep k block wholly past K
-  // (zeros in both operands), has no MFMA work: skip it (wave-uniform).
-  static_assert(BK == 32, "the k-block skip is written for two 16-deep blocks per slice");
-  if (m0 + wm >= P.M) return;
-  const bool two = P.K - it * BK > 16;
-  Frag<BM> F0, F1;
-  read_frag<BM, AT, BT>(as, bs, 0, wm, wn, li, lg, F0);
-  if (two) read_frag<BM, AT, BT>(as, bs, 1, wm, wn, li, lg, F1);
-  __builtin_amdgcn_sched_barrier(0);
-  mfma_frag<BM>(F0, acc);
-  __builtin_amdgcn_sched_barrier(0);
-  if (two) mfma_frag<BM>(F1, acc);
-  __builtin_amdgcn_sched_barrier(0);
-}
-
-// K loop: NS register sets hold the loads of the next NS slices; the loop is
-// unrolled by NS so each set (and each of the two LDS stages) has a fixed
-// role.  Its steady state issues every prefetch without a branch, so the
-// compiler counts the outstanding loads exactly and a slice's stores wait
-// for that slice's loads only (with a branch around the prefetch, the stores
-// also waited for the loads of the slices after it).
-template <int BM, int AT, int BT>
-__device__ __forceinline__ void fast_mainloop(const GemmProb& P, int m0, int n0, float* As0,
-                                              float* Bs0, v4f (&acc)[Tile<BM>::TI][2]) {
-  using T = Tile<BM>;
-  constexpr int NS = LIPZ_GEMM_STAGES;
-  static_assert(NS % 2 == 0, "an even number of register stages maps onto the two LDS stages");
-  const int tid = threadIdx.x;
-  const __amdgpu_buffer_rsrc_t ra = make_rsrc(P.A, P.a_bytes);
-  const __amdgpu_buffer_rsrc_t rb = make_rsrc(P.B, P.b_bytes);
-  FastRegs<BM, AT, BT> R[NS];
+  Opnd<BM, BM, !AT> A;
+  Opnd<BM, BN, BT> B;
+  A.init(P.A, P.a_rows, P.lda, m0, wave, lane);
+  B.init(P.B, P.N, P.ldb, n0, wave, lane);
+  typename X::Acc p[CH];
+#pragma unroll
+  for (int c = 0; c < CH; ++c) X::zero(p[c]);
+  const int m = m0 + wm + (lane & (T::WM - 1));
+  const bool real = m < P.a_rows;
+  const float fill = m == P.ones_row ? 1.f : 0.f;
   const int n_it = (P.K + BK - 1) / BK;
-  // the first NS slices' loads, all issued (past K they read zeros or
-  // data the K-tail selects drop), so that the steady-state loop below
-  // starts from the same outstanding loads on every path
+  A.load(stage0, wave, P.K);
+  B.load(stage0 + T::A_FLOATS, wave, P.K);
+  for (int it0 = 0; it0 < n_it; it0 += 2) {
 #pragma unroll
-  for (int s = 0; s < NS; ++s) fast_load<BM, AT, BT>(P, ra, rb, m0, n0, s * BK, tid, R[s]);
-  int it = 0;
-  // steady state: every slice's prefetch is needed, no branch on the loads,
-  // so each store waits for its own slice's loads and no later ones
-  for (; it + 2 * NS <= n_it; it += NS) {
+    for (int s = 0; s < 2; ++s) {
+      const int it = it0 + s;
+      if (it >= n_it) break;
+      const int kleft = P.K - it * BK;
+      float* st = s == 0 ? stage0 : stage1;
+      float* next = s == 0 ? stage1 : stage0;
+      // this wave's loads of the slice have landed, then every wave's; and
+      // every wave has read the slice before
+      wait_loads();
+      if ((!AT || BT) && kleft < BK && (kleft & 3)) {
+        A.clear_tail(st, wave, lane, kleft);
+        B.clear_tail(st + T::A_FLOATS, wave, lane, kleft);
+        wait_lds();
+      }
+      barrier();
+      if (kleft > BK) {
+        A.load(next, wave, kleft - BK);
+        B.load(next + T::A_FLOATS, wave, kleft - BK);
+      }
+      // a wave whose rows all lie past M and a k block past K have no MFMAs
+      if (m0 + wm >= P.M) continue;
+      const bool two = kleft > 16;
+      typename X::A a[2];
+      typename X::B b[2];
 #pragma unroll
-    for (int s = 0; s < NS; ++s)
-      fast_slice<BM, AT, BT, NS, true>(P, ra, rb, m0, n0, it + s, n_it, R[s], As0 + (s & 1) * T::A_FLOATS,
-                                       Bs0 + (s & 1) * T::B_FLOATS, acc);
+      for (int kb = 0; kb < 2; ++kb) {
+        if (kb == 1 && !two) break;
+        X::template read_a<!AT>(st, wm, kb, lane, a[kb]);
+        X::template read_b<BT>(st + T::A_FLOATS, wn, kb, lane, b[kb]);
+      }
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb) {
+        if (kb == 1 && !two) break;
+        if (FILL) X::fill(a[kb], real, fill);
+        X::mma(a[kb], b[kb], p[(2 * s + kb) % CH]);
+      }
+    }
   }
-  // the last NS .. 2 NS - 1 slices
-  for (; it < n_it; it += NS) {
-#pragma unroll
-    for (int s = 0; s < NS; ++s)
-      if (it + s < n_it)
-        fast_slice<BM, AT, BT, NS, false>(P, ra, rb, m0, n0, it + s, n_it, R[s], As0 + (s & 1) * T::A_FLOATS,
-                                          Bs0 + (s & 1) * T::B_FLOATS, acc);
+  if (CH == 4) {
+    X::add(p[0], p[1 % CH]);
+    X::add(p[2 % CH], p[3 % CH]);
+    X::add(p[0], p[2 % CH]);
   }
+  wait_lds();
+  barrier();  // every wave has read its last slice
+  float* blk = stage0 + wave * (T::WM * 32);
+  X::store(p[0], blk, lane);
+  // a wave reads its own block back: LDS runs a wave's accesses in order
+  __builtin_amdgcn_wave_barrier();
+#pragma unroll
+  for (int q = 0; q < T::NQ; ++q)
+    acc[q] = *reinterpret_cast<const v4f*>(blk + 256 * q + 32 * (lane >> 3) + 4 * ((lane & 7) ^ (lane >> 3)));
 }
 
-template <int BM, bool WT>
-__global__ __launch_bounds__(NT, BM == 32 ? LIPZ_GEMM_WG32 : LIPZ_GEMM_WG64) void gemm_fast_kernel(LIPZ_GEMM_ARGS) {
+// The bias corrections 1 - beta^t of Adam's step, into bc: by one wave (not the
+// same one in every tile: each has its SIMD), lane 0 beta1's and lane 1 beta2's.
+__device__ __forceinline__ void bias_corrections(const GemmProb& P, int lt, int step_local, float* bc) {
+  if (P.epi != EPI_ADAM || (int)(threadIdx.x >> 6) != (lt & 3)) return;
+  const int lane = threadIdx.x & 63;
+  const int tt = *as_global(P.t) + step_local + 1;
+  const float c = (float)(1.0 - pow((double)(lane == 0 ? P.ac.beta1 : P.ac.beta2), (double)tt));
+  if (lane < 2) bc[lane] = c;
+  wait_lds();
+}
+
+template <int BM, int CH, bool WT>
+__global__ __launch_bounds__(NT, BM == 32 ? 4 : 3) void gemm_kernel(LIPZ_GEMM_ARGS) {
   using T = Tile<BM>;
   if ((int)blockIdx.x >= g_total) {
     sample_rows<WT>(sj, (int)blockIdx.x - g_total);
@@ -899,53 +818,59 @@ __global__ __launch_bounds__(NT, BM == 32 ? LIPZ_GEMM_WG32 : LIPZ_GEMM_WG64) voi
   const int m0 = (lt / P.tiles_n) * BM;
   const int n0 = tile_n * BN;
 
-  __shared__ __align__(16) float As[2 * T::A_FLOATS];
-  __shared__ __align__(16) float Bs[2 * T::B_FLOATS];
+  // arrays of their own, not one: a load into one stage is then seen not to
+  // touch the other, and reads of that one do not wait for it
+  __shared__ __align__(16) float st0[T::FLOATS];
+  __shared__ __align__(16) float st1[T::FLOATS];
   __shared__ float red[2][BM];
+  __shared__ float bc[2];
 
-  v4f acc[T::TI][2];
-#pragma unroll
-  for (int i = 0; i < T::TI; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
-  if (P.a_trans) fast_mainloop<BM, 1, 0>(P, m0, n0, As, Bs, acc);
-  else if (P.b_trans) fast_mainloop<BM, 0, 1>(P, m0, n0, As, Bs, acc);
-  else fast_mainloop<BM, 0, 0>(P, m0, n0, As, Bs, acc);
-  epilogue<BM, WT>(P, acc, m0, n0, tile_n, step_local, red);
+  const EpiPos<BM> E(P, m0, n0);
+  EpiIn<BM> in;
+  if (CH == 1) epi_load<BM>(P, E, in);  // with four chains registers are short
+  bias_corrections(P, lt, step_local, bc);
+  v4f acc[T::NQ];
+  if (P.a_trans && P.b_trans) {  // no phase of the library
+    mainloop<BM, CH, true, true, true>(P, m0, n0, st0, st1, acc);
+  } else if (P.a_trans) {
+    if (m0 + BM > P.a_rows) mainloop<BM, CH, true, false, true>(P, m0, n0, st0, st1, acc);
+    else mainloop<BM, CH, true, false, false>(P, m0, n0, st0, st1, acc);
+  } else if (P.b_trans) {
+    mainloop<BM, CH, false, true, false>(P, m0, n0, st0, st1, acc);
+  } else {
+    mainloop<BM, CH, false, false, false>(P, m0, n0, st0, st1, acc);
+  }
+  if (CH != 1) epi_load<BM>(P, E, in);
+  epilogue<BM, WT>(P, acc, E, in, m0, n0, tile_n, bc, red);
 }
 
 // ---------------------------------------------------------------------------
-// Wave-split variant: the four waves of a workgroup each compute the whole
-// BM x 64 tile over every fourth 16-deep k block (split-K inside the
-// workgroup).  Each wave streams its operands from global memory (L2)
-// straight into registers in the MFMA fragment layout, PD k blocks ahead of
-// its MFMAs, so the main loop has no LDS traffic and no barriers, and a
-// tile's dependent chain is a quarter of K.  No operand element is loaded
-// twice, exactly as with an LDS-shared tile.  At the end the four partial
-// tiles are summed through LDS in a fixed order and handed to the shared
-// epilogue.
+// Four chains on few tiles: the four waves of a workgroup each compute the
+// whole 32 x 64 tile over every fourth 16-deep k block.  Each wave streams its
+// operands from global memory (L2) straight into registers in the MFMA
+// fragment layout, two k blocks ahead of its MFMAs, with no LDS traffic and no
+// barriers, and the four partial tiles are summed through LDS at the end.
 // ---------------------------------------------------------------------------
-#ifndef LIPZ_WAVE_PD
-#define LIPZ_WAVE_PD 2
-#endif
+__device__ __forceinline__ v4f bld4b(__amdgpu_buffer_rsrc_t r, uint32_t off_bytes) {
+  return __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off_bytes, 0, 0));
+}
 
-template <int BM>
 struct WFrag {
-  float a[BM / 16][4];   // A rows 16 i + (l % 16), k = kb + 4 (l / 16) + s
+  float a[2][4];   // A rows 16 i + (l % 16), k = kb + 4 (l / 16) + s
   float b[4][4];         // B cols 16 j + (l % 16), same k
 };
 
-template <int BM, int AT, int BT>
+template <int AT, int BT>
 __device__ __forceinline__ void wave_load(const GemmProb& P, __amdgpu_buffer_rsrc_t ra,
                                           __amdgpu_buffer_rsrc_t rb, int m0, int n0, int kb, int li,
-                                          int lg, WFrag<BM>& F) {
+                                          int lg, WFrag& F) {
   const int k = kb + 4 * lg;
 #pragma unroll
-  for (int i = 0; i < BM / 16; ++i) {
+  for (int i = 0; i < 2; ++i) {
     const int m = m0 + 16 * i + li;
     if (AT == 0) {
-      const float4 v = bload4(ra, (uint32_t)(m * P.lda + k) * 4u);
-      F.a[i][0] = v.x; F.a[i][1] = v.y; F.a[i][2] = v.z; F.a[i][3] = v.w;
+      const v4f v = bld4b(ra, (uint32_t)(m * P.lda + k) * 4u);
+      F.a[i][0] = v[0]; F.a[i][1] = v[1]; F.a[i][2] = v[2]; F.a[i][3] = v[3];
     } else {
 #pragma unroll
       for (int s = 0; s < 4; ++s)
@@ -956,8 +881,8 @@ __device__ __forceinline__ void wave_load(const GemmProb& P, __amdgpu_buffer_rsr
   for (int j = 0; j < 4; ++j) {
     const int n = n0 + 16 * j + li;
     if (BT == 1) {
-      const float4 v = bload4(rb, (uint32_t)(n * P.ldb + k) * 4u);
-      F.b[j][0] = v.x; F.b[j][1] = v.y; F.b[j][2] = v.z; F.b[j][3] = v.w;
+      const v4f v = bld4b(rb, (uint32_t)(n * P.ldb + k) * 4u);
+      F.b[j][0] = v[0]; F.b[j][1] = v[1]; F.b[j][2] = v[2]; F.b[j][3] = v[3];
     } else {
 #pragma unroll
       for (int s = 0; s < 4; ++s)
@@ -969,23 +894,23 @@ __device__ __forceinline__ void wave_load(const GemmProb& P, __amdgpu_buffer_rsr
 // MFMAs of one k block.  TAIL: zero k >= K (the problem's last, partial
 // block).  ONES: the tile holds the bias row of a [K][M] operand: set row
 // ones_row to 1 (0 past K) and the other rows past a_rows to 0.
-template <int BM, bool TAIL, bool ONES>
-__device__ __forceinline__ void wave_mma(const GemmProb& P, int m0, int kb, int li, int lg, WFrag<BM>& F,
-                                         v4f (&acc)[BM / 16][4]) {
+template <bool TAIL, bool ONES>
+__device__ __forceinline__ void wave_mma(const GemmProb& P, int m0, int kb, int li, int lg, WFrag& F,
+                                         v4f (&acc)[2][4]) {
   const int k = kb + 4 * lg;
   if (TAIL) {
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
       const bool ok = k + s < P.K;
 #pragma unroll
-      for (int i = 0; i < BM / 16; ++i) F.a[i][s] = ok ? F.a[i][s] : 0.f;
+      for (int i = 0; i < 2; ++i) F.a[i][s] = ok ? F.a[i][s] : 0.f;
 #pragma unroll
       for (int j = 0; j < 4; ++j) F.b[j][s] = ok ? F.b[j][s] : 0.f;
     }
   }
   if (ONES) {
 #pragma unroll
-    for (int i = 0; i < BM / 16; ++i) {
+    for (int i = 0; i < 2; ++i) {
       const int m = m0 + 16 * i + li;
 #pragma unroll
       for (int s = 0; s < 4; ++s) {
@@ -997,7 +922,7 @@ __device__ __forceinline__ void wave_mma(const GemmProb& P, int m0, int kb, int 
   // a 16-row block wholly past M has no MFMA work (uniform); each
   // accumulator still takes its four k steps in order
 #pragma unroll
-  for (int i = 0; i < BM / 16; ++i)
+  for (int i = 0; i < 2; ++i)
     if (i == 0 || m0 + 16 * i < P.M)
 #pragma unroll
       for (int s = 0; s < 4; ++s)
@@ -1006,9 +931,9 @@ __device__ __forceinline__ void wave_mma(const GemmProb& P, int m0, int kb, int 
           acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(F.a[i][s], F.b[j][s], acc[i][j], 0, 0, 0);
 }
 
-template <int BM, int AT, int BT, bool ONES>
-__device__ __forceinline__ void wave_mainloop(const GemmProb& P, int m0, int n0, v4f (&acc)[BM / 16][4]) {
-  constexpr int PD = LIPZ_WAVE_PD;
+template <int AT, int BT, bool ONES>
+__device__ __forceinline__ void wave_mainloop(const GemmProb& P, int m0, int n0, v4f (&acc)[2][4]) {
+  constexpr int PD = 2;
   // the wave index is uniform across the wave: keep it (and every k-block
   // index and loop bound derived from it) in scalar registers
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -1017,20 +942,20 @@ __device__ __forceinline__ void wave_mainloop(const GemmProb& P, int m0, int n0,
   const __amdgpu_buffer_rsrc_t rb = make_rsrc(P.B, P.b_bytes);
   const int nkb = (P.K + 15) / 16;                          // k blocks of the problem
   const int mine = nkb > wave ? (nkb - wave + 3) / 4 : 0;   // blocks wave, wave + 4, ...
-  WFrag<BM> F[PD];
+  WFrag F[PD];
   // every prologue load issued (past the wave's blocks they read zeros or
   // values no MFMA uses), so that the steady-state loop below starts from
   // the same outstanding loads on every path
 #pragma unroll
-  for (int p = 0; p < PD; ++p) wave_load<BM, AT, BT>(P, ra, rb, m0, n0, 16 * (wave + 4 * p), li, lg, F[p]);
+  for (int p = 0; p < PD; ++p) wave_load<AT, BT>(P, ra, rb, m0, n0, 16 * (wave + 4 * p), li, lg, F[p]);
   // steady state: every block full, every prefetch needed, no branches on
   // the loads, so the compiler can count outstanding loads exactly
   int q = 0;
   for (; q + 2 * PD <= mine; q += PD) {
 #pragma unroll
     for (int p = 0; p < PD; ++p) {
-      wave_mma<BM, false, ONES>(P, m0, 16 * (wave + 4 * (q + p)), li, lg, F[p], acc);
-      wave_load<BM, AT, BT>(P, ra, rb, m0, n0, 16 * (wave + 4 * (q + p + PD)), li, lg, F[p]);
+      wave_mma<false, ONES>(P, m0, 16 * (wave + 4 * (q + p)), li, lg, F[p], acc);
+      wave_load<AT, BT>(P, ra, rb, m0, n0, 16 * (wave + 4 * (q + p + PD)), li, lg, F[p]);
     }
   }
   // drain: the last PD .. 2 PD - 1 blocks, the problem's partial block among them
@@ -1039,19 +964,18 @@ __device__ __forceinline__ void wave_mainloop(const GemmProb& P, int m0, int n0,
     for (int p = 0; p < PD; ++p) {
       if (q + p < mine) {
         const int kb = 16 * (wave + 4 * (q + p));
-        if (kb + 16 > P.K) wave_mma<BM, true, ONES>(P, m0, kb, li, lg, F[p], acc);
-        else wave_mma<BM, false, ONES>(P, m0, kb, li, lg, F[p], acc);
+        if (kb + 16 > P.K) wave_mma<true, ONES>(P, m0, kb, li, lg, F[p], acc);
+        else wave_mma<false, ONES>(P, m0, kb, li, lg, F[p], acc);
         if (q + p + PD < mine)
-          wave_load<BM, AT, BT>(P, ra, rb, m0, n0, 16 * (wave + 4 * (q + p + PD)), li, lg, F[p]);
+          wave_load<AT, BT>(P, ra, rb, m0, n0, 16 * (wave + 4 * (q + p + PD)), li, lg, F[p]);
       }
     }
   }
 }
 
-template <int BM, bool WT>
-__global__ __launch_bounds__(NT, BM == 32 ? 2 : 1) void gemm_wave_kernel(LIPZ_GEMM_ARGS) {
-  using T = Tile<BM>;
-  constexpr int RS = BN + 4;  // row stride of the partial tiles in LDS
+template <bool WT>
+__global__ __launch_bounds__(NT, 2) void gemm_wave_kernel(LIPZ_GEMM_ARGS) {
+  constexpr int BM = 32, RS = BN + 4;  // row stride of the partial tiles in LDS
   if ((int)blockIdx.x >= g_total) {
     sample_rows<WT>(sj, (int)blockIdx.x - g_total);
     return;
@@ -1065,19 +989,24 @@ __global__ __launch_bounds__(NT, BM == 32 ? 2 : 1) void gemm_wave_kernel(LIPZ_GE
 
   __shared__ __align__(16) float part[4][BM * RS];
   __shared__ float red[2][BM];
+  __shared__ float bc[2];
 
-  v4f pacc[BM / 16][4];
+  const EpiPos<BM> E(P, m0, n0);
+  EpiIn<BM> in;
+  epi_load<BM>(P, E, in);
+  bias_corrections(P, lt, step_local, bc);
+  v4f pacc[2][4];
 #pragma unroll
-  for (int i = 0; i < BM / 16; ++i)
+  for (int i = 0; i < 2; ++i)
 #pragma unroll
     for (int j = 0; j < 4; ++j) pacc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
   if (P.a_trans) {
-    if (m0 + BM > P.a_rows) wave_mainloop<BM, 1, 0, true>(P, m0, n0, pacc);
-    else wave_mainloop<BM, 1, 0, false>(P, m0, n0, pacc);
+    if (m0 + BM > P.a_rows) wave_mainloop<1, 0, true>(P, m0, n0, pacc);
+    else wave_mainloop<1, 0, false>(P, m0, n0, pacc);
   } else if (P.b_trans) {
-    wave_mainloop<BM, 0, 1, false>(P, m0, n0, pacc);
+    wave_mainloop<0, 1, false>(P, m0, n0, pacc);
   } else {
-    wave_mainloop<BM, 0, 0, false>(P, m0, n0, pacc);
+    wave_mainloop<0, 0, false>(P, m0, n0, pacc);
   }
 
   // partial tiles to LDS (MFMA D layout: row 16 i + 4 (l / 16) + r, col 16 j + l % 16)
@@ -1085,25 +1014,21 @@ __global__ __launch_bounds__(NT, BM == 32 ? 2 : 1) void gemm_wave_kernel(LIPZ_GE
   const int li = lane & 15, lg = lane >> 4;
   float* mine = part[wave];
 #pragma unroll
-  for (int i = 0; i < BM / 16; ++i)
+  for (int i = 0; i < 2; ++i)
 #pragma unroll
     for (int j = 0; j < 4; ++j)
 #pragma unroll
       for (int r = 0; r < 4; ++r) mine[(16 * i + 4 * lg + r) * RS + 16 * j + li] = pacc[i][j][r];
   __syncthreads();
-  // each wave takes its quadrant of the tile in the layout the epilogue expects
-  const int wm = (wave >> 1) * T::WM, wn = (wave & 1) * 32;
-  v4f acc[T::TI][2];
+  v4f acc[Tile<BM>::NQ];
 #pragma unroll
-  for (int i = 0; i < T::TI; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int o = (wm + 16 * i + 4 * lg + r) * RS + wn + 16 * j + li;
-        acc[i][j][r] = (part[0][o] + part[1][o]) + (part[2][o] + part[3][o]);
-      }
-  epilogue<BM, WT>(P, acc, m0, n0, tile_n, step_local, red);
+  for (int q = 0; q < Tile<BM>::NQ; ++q) {
+    const int o = (E.row0 - m0 + 8 * q) * RS + E.col - n0;
+    const v4f p0 = *reinterpret_cast<const v4f*>(part[0] + o), p1 = *reinterpret_cast<const v4f*>(part[1] + o);
+    const v4f p2 = *reinterpret_cast<const v4f*>(part[2] + o), p3 = *reinterpret_cast<const v4f*>(part[3] + o);
+    acc[q] = (p0 + p1) + (p2 + p3);
+  }
+  epilogue<BM, WT>(P, acc, E, in, m0, n0, tile_n, bc, red);
 }
 
 }  // namespace
@@ -1120,11 +1045,9 @@ void gemm_set_extents(GemmProb& p) {
 bool gemm_fast_ok(const GemmProb& p) {
   // the fast kernel instantiates the three operand layouts the library uses:
   // (A, B) = (row, row) forward, (row, W^T) input gradient, (X^T, row) weight gradient
-  return !(p.a_trans && p.b_trans) && p.vec == 3 && p.a_bytes > 0 && p.b_bytes > 0 && p.a_bytes < 0x7FFFFFF0u &&
+  return !(p.a_trans && p.b_trans) && (p.vec & 3) == 3 && p.a_bytes > 0 && p.b_bytes > 0 && p.a_bytes < 0x7FFFFFF0u &&
          p.b_bytes < 0x7FFFFFF0u;
 }
-
-bool gemm_wave_ok(int max_k) { return LIPZ_GEMM_WAVE_SPLIT && max_k >= LIPZ_GEMM_WAVE_MIN_K; }
 
 hipError_t launch_gemm_grouped(const GemmProb* d_probs, const GemmGroups& grp, int total_tiles,
                                int tile_rows, int kernel, int step_local, bool write_through, hipStream_t s,
@@ -1148,27 +1071,24 @@ hipError_t launch_gemm_grouped(const GemmProb* d_probs, const GemmGroups& grp, i
   hipExtLaunchKernelGGL(K, g, b, 0, s, ev_start, ev_stop, 0, d_probs, total_tiles, ft[1], ft[2], ft[3], fp[1], \
                         fp[2], fp[3], grp.tiles_per_prob[0], grp.tiles_per_prob[1], grp.tiles_per_prob[2],    \
                         grp.tiles_per_prob[3], step_local, sj)
-#define LIPZ_LAUNCH_WT(KN, BMV) \
-  if (write_through) LIPZ_LAUNCH((KN<BMV, true>)); else LIPZ_LAUNCH((KN<BMV, false>))
-  const bool r32 = tile_rows == 32;
-  switch (kernel) {
-    case GEMM_K_WAVE:
-      if (r32) { LIPZ_LAUNCH_WT(gemm_wave_kernel, 32); } else { LIPZ_LAUNCH_WT(gemm_wave_kernel, 64); }
-      break;
-    case GEMM_K_FAST:
-      if (r32) { LIPZ_LAUNCH_WT(gemm_fast_kernel, 32); } else { LIPZ_LAUNCH_WT(gemm_fast_kernel, 64); }
-      break;
-    default:
-      if (r32) { LIPZ_LAUNCH_WT(gemm_generic_kernel, 32); } else { LIPZ_LAUNCH_WT(gemm_generic_kernel, 64); }
+#define LIPZ_LAUNCH_WT(BMV, CHV) \
+  if (write_through) LIPZ_LAUNCH((gemm_kernel<BMV, CHV, true>)); else LIPZ_LAUNCH((gemm_kernel<BMV, CHV, false>))
+  if (kernel == GEMM_K_WAVE) {
+    if (tile_rows != 32) return hipErrorInvalidValue;
+    if (write_through) LIPZ_LAUNCH((gemm_wave_kernel<true>)); else LIPZ_LAUNCH((gemm_wave_kernel<false>));
+  } else if (kernel == GEMM_K_CHAINS4) {
+    if (tile_rows == 32) { LIPZ_LAUNCH_WT(32, 4); } else { LIPZ_LAUNCH_WT(64, 4); }
+  } else {
+    if (tile_rows == 32) { LIPZ_LAUNCH_WT(32, 1); } else { LIPZ_LAUNCH_WT(64, 1); }
   }
 #undef LIPZ_LAUNCH_WT
 #undef LIPZ_LAUNCH
   return hipGetLastError();
 }
 
-int gemm_choose_kernel(bool fast, int max_k) {
-  if (!fast) return GEMM_K_GENERIC;
-  return gemm_wave_ok(max_k) ? GEMM_K_WAVE : GEMM_K_FAST;
+int gemm_choose_kernel(bool aligned, int max_k, int tiles, int tile_rows) {
+  if (!aligned || max_k < LIPZ_GEMM_CHAINS4_MIN_K) return GEMM_K_CHAIN;
+  return tile_rows == 32 && tiles <= LIPZ_GEMM_WAVE_MAX_TILES ? GEMM_K_WAVE : GEMM_K_CHAINS4;
 }
 
 }  // namespace lipz

@@ -120,6 +120,8 @@ enum Epi : int32_t {
   EPI_ADAM = 3       // acc is the gradient of parameter C[i][j]; Adam update of C, m, v
 };
 
+constexpr int32_t GEMM_ADAM_OLD_FIRST = 4;  // EPI_ADAM: see adam (gemm.hip)
+
 struct AdamConsts {
   float beta1, beta2, one_minus_beta1, one_minus_beta2, eps;
 };
@@ -170,7 +172,7 @@ struct GemmProb {
   int32_t a_trans, b_trans;
   int32_t a_rows, ones_row;
   int32_t epi, act;
-  int32_t vec;         // bit 0: A rows 16-byte aligned; bit 1: B rows 16-byte aligned
+  int32_t vec;         // bit 0: A rows 16-byte aligned; bit 1: B rows 16-byte aligned; GEMM_ADAM_OLD_FIRST
   int32_t tiles_n;
   int32_t tile_begin;
   union {
@@ -273,20 +275,15 @@ bool gemm_fast_ok(const GemmProb& p);
 // Fill a_bytes / b_bytes from the problem's shape (0 if they do not fit 32 bits).
 void gemm_set_extents(GemmProb& p);
 
-// True when a phase whose deepest problem has K = max_k runs faster on the
-// wave-split kernel (each wave takes every fourth k block of the whole tile,
-// operands straight from L2 into registers) than on the LDS-staged kernel.
-bool gemm_wave_ok(int max_k);
-
-// Kernel variants of the grouped GEMM (gemm.hip).
+// Variants of the grouped GEMM (gemm.hip): how an output's sum is formed.
 enum GemmKernel : int32_t {
-  GEMM_K_GENERIC = 0,  // any alignment, per-element bounds checks
-  GEMM_K_FAST = 1,     // register-staged LDS slices
-  GEMM_K_WAVE = 2      // split-K across the four waves, operands from L2 into registers
+  GEMM_K_CHAIN = 1,    // one chain of multiply-adds
+  GEMM_K_WAVE = 2,     // four chains, of every fourth 16-deep k block each, one per wave (aligned operands)
+  GEMM_K_CHAINS4 = 3   // the same four chains in every wave
 };
-// The kernel a phase runs on: its problems all fast-path eligible (fast), its
-// deepest K (max_k).
-int gemm_choose_kernel(bool fast, int max_k);
+// The variant a phase runs on: whether its problems' operands are all aligned
+// (gemm_fast_ok), its deepest K, and its tiles.
+int gemm_choose_kernel(bool aligned, int max_k, int tiles, int tile_rows);
 
 // A training minibatch drawn by extra workgroups of a GEMM launch (the
 // draws of sample_kernel, written to other buffers than the launch's GEMMs
