@@ -72,7 +72,7 @@ namespace {
 #endif
 #ifndef LIPZ_GEMM_WAVE_MAX_TILES
 // ... on the wave-split kernel up to this many tiles (two per CU: 512 tiles of
-// K = 784 take 20.3 us there and 24.0 on the other, 672 take 27.8 and 22.7)
+// K = 784 take 20.3 us there and 21.1 on the other, 672 take 27.8 and 21.7)
 #define LIPZ_GEMM_WAVE_MAX_TILES 512
 #endif
 
@@ -735,9 +735,63 @@ __device__ __forceinline__ void mainloop(const GemmProb& P, int m0, int n0, floa
   const bool real = m < P.a_rows;
   const float fill = m == P.ones_row ? 1.f : 0.f;
   const int n_it = (P.K + BK - 1) / BK;
+  int it0 = 0, loaded = 1;  // slices begun, slices asked for
   A.load(stage0, wave, P.K);
   B.load(stage0 + T::A_FLOATS, wave, P.K);
-  for (int it0 = 0; it0 < n_it; it0 += 2) {
+  // Steady state of four chains (deep products): full slices with another one
+  // behind them, half a slice at a time: the second k block's fragments are read
+  // before the first one's MFMAs, and the next slice's first ones before the
+  // second's.  No branches: with one, the compiler no longer sees which stage a
+  // load in flight goes to, and waits for all of them before it reads either.
+  // (8960 tiles of K = 784: 283 us, 292 with whole slices; 672 tiles 21.7 and 23.3.)
+  const int steady = n_it - 1 - (P.K & 3 ? 1 : 0);
+  if (CH == 4 && steady >= 2) {
+    wait_loads();
+    barrier();
+    A.load(stage1, wave, P.K - BK);
+    B.load(stage1 + T::A_FLOATS, wave, P.K - BK);
+    if (m0 + wm < P.M) {
+      typename X::A a0, a1;
+      typename X::B b0, b1;
+      X::template read_a<!AT>(stage0, wm, 0, lane, a0);
+      X::template read_b<BT>(stage0 + T::A_FLOATS, wn, 0, lane, b0);
+      for (; it0 + 2 <= steady; it0 += 2) {
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+          float* st = s == 0 ? stage0 : stage1;
+          float* next = s == 0 ? stage1 : stage0;
+          X::template read_a<!AT>(st, wm, 1, lane, a1);
+          X::template read_b<BT>(st + T::A_FLOATS, wn, 1, lane, b1);
+          __builtin_amdgcn_sched_barrier(0);
+          if (FILL) X::fill(a0, real, fill);
+          X::mma(a0, b0, p[(2 * s) % CH]);
+          __builtin_amdgcn_sched_barrier(0);
+          wait_loads();
+          barrier();  // the next slice is in LDS, and every wave has read this one
+          A.load(st, wave, P.K - (it0 + s + 2) * BK);
+          B.load(st + T::A_FLOATS, wave, P.K - (it0 + s + 2) * BK);
+          X::template read_a<!AT>(next, wm, 0, lane, a0);
+          X::template read_b<BT>(next + T::A_FLOATS, wn, 0, lane, b0);
+          __builtin_amdgcn_sched_barrier(0);
+          if (FILL) X::fill(a1, real, fill);
+          X::mma(a1, b1, p[(2 * s + 1) % CH]);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+    } else {  // rows past M: the loads and barriers alone
+      for (; it0 + 2 <= steady; it0 += 2) {
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+          wait_loads();
+          barrier();
+          A.load(s == 0 ? stage0 : stage1, wave, P.K - (it0 + s + 2) * BK);
+          B.load((s == 0 ? stage0 : stage1) + T::A_FLOATS, wave, P.K - (it0 + s + 2) * BK);
+        }
+      }
+    }
+    loaded = it0 + 2;
+  }
+  for (; it0 < n_it; it0 += 2) {
 #pragma unroll
     for (int s = 0; s < 2; ++s) {
       const int it = it0 + s;
@@ -754,7 +808,7 @@ __device__ __forceinline__ void mainloop(const GemmProb& P, int m0, int n0, floa
         wait_lds();
       }
       barrier();
-      if (kleft > BK) {
+      if (it + 1 < n_it && it + 1 >= loaded) {
         A.load(next, wave, kleft - BK);
         B.load(next + T::A_FLOATS, wave, kleft - BK);
       }
