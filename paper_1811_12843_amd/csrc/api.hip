@@ -1575,8 +1575,7 @@ lipz_status lipz_train_step(lipz_grid* g, int32_t gen, int32_t step0, int32_t n_
   if (g->dc) {
     if ((st = dc_train(g, gen, step0, n_steps, d_losses))) return st;
     const StateBuf& S = g->st[g->cur];
-    hipError_t e = launch_add_i32(S.Gt, g->C, n_steps, s);
-    if (e == hipSuccess) e = launch_add_i32(S.Dt, g->C, n_steps, s);
+    const hipError_t e = launch_add_i32(S.Gt, S.Dt, g->C, n_steps, s);
     if ((st = check_hip(g, e, "step count"))) return st;
     g->fitness_valid = false;
     return LIPZ_OK;
@@ -1591,8 +1590,7 @@ lipz_status lipz_train_step(lipz_grid* g, int32_t gen, int32_t step0, int32_t n_
     nes_args(g, gen, par, na);
     for (int k = 0; k < n_steps; ++k)
       if ((st = enq_nes_step(g, gen, g->nes_ops[par], na, 0, C, k, step0 + k, d_losses, s))) return st;
-    hipError_t e = launch_add_i32(S.Gt, C, n_steps, s);
-    if (e == hipSuccess) e = launch_add_i32(S.Dt, C, n_steps, s);
+    const hipError_t e = launch_add_i32(S.Gt, S.Dt, C, n_steps, s);
     if ((st = check_hip(g, e, "step count"))) return st;
     g->fitness_valid = false;
     return LIPZ_OK;
@@ -1614,8 +1612,7 @@ lipz_status lipz_train_step(lipz_grid* g, int32_t gen, int32_t step0, int32_t n_
     if ((st = check_hip(g, hipEventRecord(g->join_ev[i], g->gstream[i]), "join"))) return st;
     if ((st = check_hip(g, hipStreamWaitEvent(s, g->join_ev[i], 0), "join"))) return st;
   }
-  hipError_t e = launch_add_i32(S.Gt, C, n_steps, s);
-  if (e == hipSuccess) e = launch_add_i32(S.Dt, C, n_steps, s);
+  const hipError_t e = launch_add_i32(S.Gt, S.Dt, C, n_steps, s);
   if ((st = check_hip(g, e, "step count"))) return st;
   g->fitness_valid = false;
   return LIPZ_OK;
@@ -1662,8 +1659,7 @@ static lipz_status enq_band_generations(lipz_grid* g, int gen0, int n_gens, int 
       const int c0 = g->band_c0[b], nc = g->band_c0[b + 1] - c0;
       const StateBuf& N = g->st[1 - par];
       if (n_steps > 0) {
-        hipError_t e = launch_add_i32(N.Gt + (size_t)c0 * sp, nc * sp, n_steps, bs);
-        if (e == hipSuccess) e = launch_add_i32(N.Dt + (size_t)c0 * sp, nc * sp, n_steps, bs);
+        const hipError_t e = launch_add_i32(N.Gt + (size_t)c0 * sp, N.Dt + (size_t)c0 * sp, nc * sp, n_steps, bs);
         if ((st = check_hip(g, e, "step count"))) return st;
       }
       if (g->cfg.elitism &&

@@ -675,7 +675,7 @@ struct CopyArgs {
   int U, C;
 };
 hipError_t launch_copy_winners(const CopyArgs& a, hipStream_t s);
-hipError_t launch_add_i32(int32_t* p, int n, int32_t v, hipStream_t s);
+hipError_t launch_add_i32(int32_t* a, int32_t* b, int n, int32_t v, hipStream_t s);
 
 // Feature moments in fp64 (mean f and mean f^2 per cell and feature: their
 // difference, the variance, cancels when the mean dominates).
