@@ -800,8 +800,7 @@ void build_tables(lipz_grid* g) {
     // with the head folded in, the step's losses (when asked for) come from a
     // small kernel over the partial logits at the end of the step
     if (fused) {
-      ops.push_back({OP_LOSS_D, -1});
-      ops.push_back({OP_LOSS_G, -1});
+      ops.push_back({OP_LOSSES, -1});
     }
     }  // groups and step parities
 
@@ -1069,10 +1068,21 @@ lipz_status enq_eval(lipz_grid* g, int gen, int c0, int nc, const std::vector<in
   ha.C = nc;
   ha.nn = nn;
   ha.loss_kind = g->cfg.loss_kind;
-  if ((st = check_hip(g, launch_head_eval(ha, s), "eval head"))) return st;
-  e = launch_fitness(g->L + c0 * n2, g->Lg + c0 * n2, nc, nn, g->cfg.fitness_mode, g->fit_g + (size_t)c0 * nn,
-                     g->fit_d + (size_t)c0 * nn, g->flags, d_L, d_Lg, d_fit_g, d_fit_d, s);
-  return check_hip(g, e, "fitness");
+  FitnessArgs fa;
+  memset(&fa, 0, sizeof(fa));
+  fa.L = ha.L;
+  fa.Lg = ha.Lg;
+  fa.C = nc;
+  fa.nn = nn;
+  fa.mode = g->cfg.fitness_mode;
+  fa.fit_g = g->fit_g + (size_t)c0 * nn;
+  fa.fit_d = g->fit_d + (size_t)c0 * nn;
+  fa.flags = g->flags;
+  fa.oL = d_L;
+  fa.oLg = d_Lg;
+  fa.ofg = d_fit_g;
+  fa.ofd = d_fit_d;
+  return check_hip(g, launch_head_eval_fitness(ha, fa, s), "eval head");
 }
 
 // Tournaments and copies of cells c0 .. c0 + nc - 1 from buffer par into 1 - par.
@@ -1276,8 +1286,7 @@ lipz_status enq_train_group_step(lipz_grid* g, int gen, int par, int grp, int k,
       case OP_GEMM: e = run_gemm_phase(g, op.phase, k, gs, op.sample_next && job.blocks ? &job : nullptr); break;
       case OP_HEAD_D: e = launch_head_d(gd, gs); break;
       case OP_HEAD_G: e = launch_head_g(gg, gs); break;
-      case OP_LOSS_D: if (d_losses) e = launch_loss_d(gd, gs); break;
-      case OP_LOSS_G: if (d_losses) e = launch_loss_g(gg, gs); break;
+      case OP_LOSSES: if (d_losses) e = launch_losses(gd, gg, gs); break;
       default: e = hipErrorInvalidValue; break;
     }
     if ((st = check_hip(g, e, "train step"))) return st;
@@ -1523,8 +1532,21 @@ lipz_status lipz_eval_neighborhoods(lipz_grid* g, int32_t gen, float* d_L, float
   hipStream_t s = g->stream;
   if (g->dc) {
     if ((st = dc_eval(g, gen))) return st;
-    hipError_t e = launch_fitness(g->L, g->Lg, g->C, g->nn, g->cfg.fitness_mode, g->fit_g, g->fit_d, g->flags,
-                                  d_L, d_Lg, d_fit_g, d_fit_d, s);
+    FitnessArgs fa;
+    memset(&fa, 0, sizeof(fa));
+    fa.L = g->L;
+    fa.Lg = g->Lg;
+    fa.C = g->C;
+    fa.nn = g->nn;
+    fa.mode = g->cfg.fitness_mode;
+    fa.fit_g = g->fit_g;
+    fa.fit_d = g->fit_d;
+    fa.flags = g->flags;
+    fa.oL = d_L;
+    fa.oLg = d_Lg;
+    fa.ofg = d_fit_g;
+    fa.ofd = d_fit_d;
+    const hipError_t e = launch_fitness(fa, s);
     if ((st = check_hip(g, e, "fitness"))) return st;
   } else if ((st = enq_eval(g, gen, 0, g->C, g->eval_phases[g->cur], s, d_L, d_Lg, d_fit_g, d_fit_d))) {
     return st;

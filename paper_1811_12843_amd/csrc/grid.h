@@ -68,7 +68,7 @@ struct Phase {
 
 // A training-step op: a GEMM phase, or a kernel of the step; for the NES ops
 // `phase` holds the role (LIPZ_ROLE_G / LIPZ_ROLE_D).
-enum OpKind { OP_SAMPLE, OP_GEMM, OP_HEAD_D, OP_HEAD_G, OP_LOSS_D, OP_LOSS_G, OP_NES_PERTURB, OP_NES_HEAD,
+enum OpKind { OP_SAMPLE, OP_GEMM, OP_HEAD_D, OP_HEAD_G, OP_LOSSES, OP_NES_PERTURB, OP_NES_HEAD,
               OP_NES_UPDATE };
 struct Op {
   OpKind kind;

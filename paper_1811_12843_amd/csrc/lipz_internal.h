@@ -540,7 +540,6 @@ hipError_t launch_sample(const float* data, int64_t N, int xd, int zd, int B, in
                          float* Z, int64_t z_cell_stride, hipStream_t s);
 
 struct HeadArgs {
-  int loss_only;         // only the per-cell losses (the loss head is folded into the GEMM launches)
   const float* part;     // per-tile partial logits [C][rows][tn] (bias included)
   int tn;
   const float* act;      // last hidden activations [C][rows][H] (cell stride act_cell_stride)
@@ -562,9 +561,8 @@ struct HeadArgs {
 hipError_t launch_head_d(const HeadArgs& a, hipStream_t s);
 // Generator step head: logits of B fake rows, non-saturating loss, delta.
 hipError_t launch_head_g(const HeadArgs& a, hipStream_t s);
-// The losses alone (a.losses) of the discriminator / generator step.
-hipError_t launch_loss_d(const HeadArgs& a, hipStream_t s);
-hipError_t launch_loss_g(const HeadArgs& a, hipStream_t s);
+// The losses alone (d.losses, g.losses) of the discriminator and generator step.
+hipError_t launch_losses(const HeadArgs& d, const HeadArgs& g, hipStream_t s);
 
 struct EvalHeadArgs {
   const float* part;     // partial logits [C][nn][(1 + nn) B][tn] (bias included)
@@ -576,6 +574,19 @@ struct EvalHeadArgs {
   int loss_kind;         // LIPZ_LOSS_BCE or LIPZ_LOSS_WASSERSTEIN
 };
 hipError_t launch_head_eval(const EvalHeadArgs& a, hipStream_t s);
+
+// Fitness of C cells' individuals from their losses, with copies of both.
+struct FitnessArgs {
+  const float* L;        // [C][nn][nn]
+  const float* Lg;
+  int C, nn, mode;
+  float* fit_g;          // [C][nn]
+  float* fit_d;
+  int32_t* flags;        // bit 0: a non-finite loss
+  float *oL, *oLg, *ofg, *ofd;  // copies, or null
+};
+// The evaluation head, then the fitness of the same cells' losses (f.L = a.L, f.Lg = a.Lg).
+hipError_t launch_head_eval_fitness(const EvalHeadArgs& a, const FitnessArgs& f, hipStream_t s);
 
 // NES trainer (one role): perturbed parameter sets, their losses, and the
 // estimate + Adam step.  Set q < n holds theta + sigma eps_q, set n + k holds
@@ -606,9 +617,7 @@ hipError_t launch_nes_perturb(const NesArgs& a, hipStream_t s);
 hipError_t launch_nes_head(const NesArgs& a, hipStream_t s);
 hipError_t launch_nes_update(const NesArgs& a, hipStream_t s);
 hipError_t launch_es_select(const NesArgs& a, hipStream_t s);
-hipError_t launch_fitness(const float* L, const float* Lg, int C, int nn, int mode, float* fit_g, float* fit_d,
-                          int32_t* flags, float* out_L, float* out_Lg, float* out_fg, float* out_fd,
-                          hipStream_t s);
+hipError_t launch_fitness(const FitnessArgs& f, hipStream_t s);
 
 struct SelectArgs {
   const float* fit_g;

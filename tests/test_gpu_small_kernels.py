@@ -1,7 +1,9 @@
-"""The mixture step with feature counts around the 64 lanes of a cell's wave."""
+"""The per-cell kernels at the edges of a wave: the mixture step's feature counts, the evaluation head's batches
+and neighbourhoods (one launch with the fitness up to seven individuals and 256 rows,
+two beyond)."""
 import numpy as np
 import pytest
-from test_gpu_parity import _setup, _warm_state
+from test_gpu_parity import _close, _setup, _warm_state
 
 from oracle import coevo, mixture
 
@@ -26,3 +28,16 @@ def test_mixture_matches_oracle_at_any_feature_count(features):
         gg.set_state(st)
         w, sc, acc = gg.mixture(0)
         check_mixture(S, st, stats, 0, w, sc, acc)
+
+
+@pytest.mark.parametrize("batch,pop,mode", [(1, 1, 0), (63, 1, 1), (64, 1, 0), (65, 1, 1), (256, 1, 0), (257, 1, 1), (3, 2, 1)])
+def test_eval_matches_oracle_at_any_batch(batch, pop, mode):
+    wl, data, _ = _setup("ragged_2x3")
+    wl = dict(wl, batch=batch, pop_size=pop, fitness_mode=mode)
+    S = coevo.Setup(wl, len(data))
+    st = _warm_state(S, data, steps=1)
+    print(f"[case] eval batch={batch} pop={pop} mode={mode}", flush=True)
+    with GpuGrid(wl, data) as gg:
+        gg.set_state(st)
+        for a, b in zip(gg.eval(1), coevo.evaluate(S, st, data, 1)):
+            assert _close(a, b, wl), np.max(np.abs(a - b) / np.abs(b))
