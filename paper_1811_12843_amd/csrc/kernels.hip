@@ -271,10 +271,9 @@ __global__ void fitness_kernel(FitnessArgs F) {
 }
 
 // Both in one launch, a workgroup per cell, for small neighbourhoods and
-// batches, where launches cost more than the work: an evaluation of four cells
-// of 64 rows takes 27.5 us with it and 29.2 without; of 16 cells of 600 rows
-// 319 and 317.
-constexpr int EVAL_FIT_NT = 1024, EVAL_FIT_MAX_NN = 7, EVAL_FIT_MAX_B = 256;
+// batches, where launches cost more than the work: four cells of 64 rows take
+// 7.0 us here and 4.7 + 3.2 apart, 16 cells of 100 rows 12.9 and 7.6 + 4.0.
+constexpr int EVAL_FIT_NT = 1024, EVAL_FIT_MAX_NN = 7, EVAL_FIT_MAX_B = 64;
 __global__ __launch_bounds__(EVAL_FIT_NT) void head_eval_fitness_kernel(EvalHeadArgs A, FitnessArgs F) {
   constexpr int N = EVAL_FIT_MAX_NN;
   __shared__ float mean[N * (1 + 2 * N)], sL[N * N], sLg[N * N];
