@@ -64,7 +64,8 @@ lipz_status lipz_test_gemm(void* hip_stream, void* d_desc, int32_t M, int32_t N,
  * the sums of 0; 2 = bf16 matrix cores at fp32 accuracy.  1 and 2: channels
  * multiples of 4, more than 16 output columns, grids of a weight gradient at
  * most 32 wide, tiles 128 x 128, 128 x 64 or 64 x 64; 2: kinds 0 and 1 only
- * (else LIPZ_E_INVAL).
+ * (else LIPZ_E_INVAL).  3 = as 2, the weights' pieces formed first, in d_aux
+ * (96 cin cout bytes, cout rounded up to 32; cin a multiple of 32).
  * d_desc: device scratch of at least 2048 bytes.
  */
 lipz_status lipz_test_conv(void* hip_stream, void* d_desc, int32_t kind, int32_t n_img, int32_t side_log, int32_t cin,

@@ -11,12 +11,18 @@
 // slice; the two or three workgroups of a CU fill each other's barriers), and
 // the six piece products go through v_mfma_f32_32x32x16_bf16.
 //
-// What bounds it: the split's VALU work beside the MFMAs (about 240 VALU
-// instructions per 48 MFMAs and wave).  Measured, 80 problems of 98304 x 128 x
-// 1024 (2.06 TFLOP): 12.4 ms (166 TFLOP/s) against 15.8 on fp32 MFMAs
-// (conv_wide_kernel) and 20.9 on conv_kernel; 24576 x 256 x 2048: 11.2 ms.  A
-// loop of these MFMAs alone on random data runs at 1.77 PFLOP/s, 295 for six
-// products.
+// PRE: the weights were split by split_weights_kernel into the order of the
+// MFMA's operand.  The waves read them from L2 straight into registers, half a
+// slice ahead, and only the gathered operand goes through LDS: the LDS traffic
+// of a slice, which comes between its MFMAs and the next one's, is halved.
+//
+// What bounds it: the bf16 matrix rate the card holds on real data (a large
+// bf16 product of the math library: 1.21 PFLOP/s, 202 for six products; the
+// clock drops to 1.9 GHz).  Measured, 80 problems of 98304 x 128 x 1024 (2.06
+// TFLOP): 11.5 ms (179 TFLOP/s) with PRE, 12.2 without, 15.8 on fp32 MFMAs
+// (conv_wide_kernel) and 20.9 on conv_kernel; 6144 x 512 x 4096: 9.9 ms (208)
+// with PRE, 10.2 without; all weights of 16 cells (44 million) are split in
+// 0.10 ms.  Splitting the weights ahead but staging them in LDS gained nothing.
 //
 // TAP1: the channels per tap are a multiple of 32, so a slice lies within one
 // tap and its shift and weight row are scalars; otherwise every float4
@@ -44,7 +50,8 @@ struct SplitTile {
 // (1024 / TN) h.
 template <int TM, int TN, bool TAP1>
 struct SplitCtx {
-  __amdgpu_buffer_rsrc_t ra, rb;
+  __amdgpu_buffer_rsrc_t ra, rb, rp;
+  int pb[TN / 64];                           // byte offsets of the wave's column blocks in the split weights
   int y[TM / 64], x[TM / 64], off[TM / 64];  // source coordinates and element offset of the thread's rows
   uint32_t va[TM / 64];                      // TAP1: byte offsets of the rows under the slice's tap
   KPos ka[2], kb[TN / 32];                   // not TAP1
@@ -53,11 +60,18 @@ struct SplitCtx {
   uint32_t bcol;                             // byte offset of the thread's B columns (TAP1: and k row), FAR past N
 };
 
-template <int TM, int TN, bool TAP1>
+template <int TM, int TN, bool TAP1, bool PRE>
 __device__ __forceinline__ void split_setup(const ConvProb& P, int m0, int n0, SplitCtx<TM, TN, TAP1>& X) {
   const int tid = threadIdx.x;
   X.ra = rsrc(P.S, P.s_bytes);
-  X.rb = rsrc(P.W, P.w_bytes);
+  if (PRE) {
+    X.rp = rsrc(reinterpret_cast<const float*>(P.Wp), (uint32_t)((P.N + 31) / 32) * (uint32_t)(P.wp_k * 192));
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+#pragma unroll
+    for (int j = 0; j < TN / 64; ++j) X.pb[j] = ((n0 + (wave & 1) * (TN / 2)) / 32 + j) * (P.wp_k * 192);
+  } else {
+    X.rb = rsrc(P.W, P.w_bytes);
+  }
 #pragma unroll
   for (int h = 0; h < TM / 64; ++h) {
     const int p = m0 + (tid >> 2) + 64 * h;
@@ -94,9 +108,10 @@ __device__ __forceinline__ float4 ld4s(__amdgpu_buffer_rsrc_t r, uint32_t off_by
   return make_float4(__uint_as_float(v[0]), __uint_as_float(v[1]), __uint_as_float(v[2]), __uint_as_float(v[3]));
 }
 
-template <int TM, int TN, bool TAP1>
+// kw: the slice's first weight row (TAP1).
+template <int TM, int TN, bool TAP1, bool PRE>
 __device__ __forceinline__ void split_load(const ConvProb& P, SplitCtx<TM, TN, TAP1>& X, int k0,
-                                           float4 (&fa)[TM / 32], float4 (&fb)[TN / 32]) {
+                                           float4 (&fa)[TM / 32], float4 (&fb)[TN / 32], int& kw) {
   const int tid = threadIdx.x, kg = (tid & 3) << 3;
   if (TAP1) {
     // within a tap only the scalar offsets move
@@ -111,6 +126,8 @@ __device__ __forceinline__ void split_load(const ConvProb& P, SplitCtx<TM, TN, T
       fa[2 * h + 1] = ld4s(X.ra, X.va[h], (uint32_t)X.c * 4u + 16u);
     }
     const int r0 = d.wt * P.cs + X.c;
+    kw = r0;
+    if (!PRE)
 #pragma unroll
     for (int h = 0; h < TN / 32; ++h) fb[h] = ld4s(X.rb, X.bcol, (uint32_t)((r0 + (1024 / TN) * h) * P.N) * 4u);
     X.c += SK_DEEP;
@@ -140,8 +157,9 @@ __device__ __forceinline__ void split_load(const ConvProb& P, SplitCtx<TM, TN, T
 }
 
 // The operand slices, split, into their three LDS tiles each.
-template <int TM, int TN, bool AGAIN>
-__device__ __forceinline__ void split_store(bool lead, const float4 (&fa)[TM / 32], const float4 (&fb)[TN / 32], char* lds) {
+template <int TM, int TN, bool AGAIN, bool PRE>
+__device__ __forceinline__ void split_store(bool lead, const float4 (&fa)[TM / 32], const float4 (&fb)[TN / 32],
+                                            char* lds) {
   using T = SplitTile<TM, TN>;
   const int tid = threadIdx.x;
 #pragma unroll
@@ -156,6 +174,7 @@ __device__ __forceinline__ void split_store(bool lead, const float4 (&fa)[TM / 3
 #pragma unroll
     for (int q = 0; q < 3; ++q) *reinterpret_cast<uint4*>(lds + q * T::A_PIECE + o) = p[q];
   }
+  if (PRE) return;
 #pragma unroll
   for (int h = 0; h < TN / 32; ++h) {
     uint2 p[3];
@@ -168,7 +187,7 @@ __device__ __forceinline__ void split_store(bool lead, const float4 (&fa)[TM / 3
 }
 
 // The K loop: acc = the tile's products (lead: only those of the first pieces).
-template <int TM, int TN, bool TAP1, bool AGAIN>
+template <int TM, int TN, bool TAP1, bool AGAIN, bool PRE>
 __device__ __forceinline__ void split_mainloop(const ConvProb& P, int m0, int n0, bool lead, char* lds,
                                                v16f (&acc)[TM / 64][TN / 64]) {
   using T = SplitTile<TM, TN>;
@@ -177,7 +196,7 @@ __device__ __forceinline__ void split_mainloop(const ConvProb& P, int m0, int n0
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int wm = (wave >> 1) * (TM / 2), wn = (wave & 1) * (TN / 2);
   SplitCtx<TM, TN, TAP1> X;
-  split_setup<TM, TN, TAP1>(P, m0, n0, X);
+  split_setup<TM, TN, TAP1, PRE>(P, m0, n0, X);
   v16f low[T::TI][T::TJ];  // the five smaller piece products (AGAIN: no registers for their own sums)
 #pragma unroll
   for (int i = 0; i < T::TI; ++i)
@@ -186,35 +205,71 @@ __device__ __forceinline__ void split_mainloop(const ConvProb& P, int m0, int n0
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = low[i][j][r] = 0.f;
   float4 fa[T::A_F4], fb[T::B_F4];
-  if (!AGAIN) split_load<TM, TN, TAP1>(P, X, 0, fa, fb);
-  for (int k0 = 0; k0 < P.K; k0 += SK_DEEP) {
-    if (AGAIN) split_load<TM, TN, TAP1>(P, X, k0, fa, fb);  // no registers for a slice in flight
-    __syncthreads();  // every wave has read the previous slice
-    split_store<TM, TN, AGAIN>(lead, fa, fb, lds);
-    if (!AGAIN && k0 + SK_DEEP < P.K) split_load<TM, TN, TAP1>(P, X, k0 + SK_DEEP, fa, fb);
-    __syncthreads();
+  int kw = 0;
+  auto products = [&](const v8bf (&a)[T::TI][3], const v8bf (&b)[T::TJ][3]) {
 #pragma unroll
-    for (int kk = 0; kk < 2; ++kk) {
-      v8bf a[T::TI][3], bq[T::TJ][3];
+    for (int s = 2; s >= 0; --s) {
+      if (AGAIN && lead && s) continue;
 #pragma unroll
-      for (int q = 0; q < 3; ++q) {
+      for (int q = 0; q <= s; ++q)
 #pragma unroll
-        for (int i = 0; i < T::TI; ++i) a[i][q] = rk_frag(At + q * T::A_PIECE, wm + 32 * i, kk, lane);
+        for (int i = 0; i < T::TI; ++i)
 #pragma unroll
-        for (int j = 0; j < T::TJ; ++j) bq[j][q] = km_frag<TN>(Bt + q * T::B_PIECE, wn + 32 * j, kk, lane);
-      }
+          for (int j = 0; j < T::TJ; ++j) {
+            v16f& to = s && !AGAIN ? low[i][j] : acc[i][j];
+            to = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i][q], b[j][s - q], to, 0, 0, 0);
+          }
+    }
+  };
+  auto a_frags = [&](int kk, v8bf (&a)[T::TI][3]) {
 #pragma unroll
-      for (int s = 2; s >= 0; --s) {
-        if (AGAIN && lead && s) continue;
+    for (int q = 0; q < 3; ++q)
 #pragma unroll
-        for (int q = 0; q <= s; ++q)
+      for (int i = 0; i < T::TI; ++i) a[i][q] = rk_frag(At + q * T::A_PIECE, wm + 32 * i, kk, lane);
+  };
+  if (PRE) {
+    // split weights: fragments as they are used, straight from memory, half a
+    // slice ahead; past the last slice those loads repeat it
+    auto b_frags = [&](int row, v8bf (&b)[T::TJ][3]) {
 #pragma unroll
-          for (int i = 0; i < T::TI; ++i)
+      for (int j = 0; j < T::TJ; ++j)
 #pragma unroll
-            for (int j = 0; j < T::TJ; ++j) {
-              v16f& to = s && !AGAIN ? low[i][j] : acc[i][j];
-              to = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i][q], bq[j][s - q], to, 0, 0, 0);
-            }
+        for (int q = 0; q < 3; ++q)
+          b[j][q] = __builtin_bit_cast(v8bf, __builtin_amdgcn_raw_buffer_load_b128(X.rp, lane * 16,
+                                                                                  X.pb[j] + row * 192 + q * 1024, 0));
+    };
+    v8bf a[T::TI][3], b0[T::TJ][3], b1[T::TJ][3];
+    split_load<TM, TN, TAP1, PRE>(P, X, 0, fa, fb, kw);
+    b_frags(kw, b0);
+    for (int k0 = 0; k0 < P.K; k0 += SK_DEEP) {
+      __syncthreads();  // every wave has read the previous slice
+      split_store<TM, TN, AGAIN, PRE>(lead, fa, fb, lds);
+      b_frags(kw + 16, b1);
+      if (k0 + SK_DEEP < P.K) split_load<TM, TN, TAP1, PRE>(P, X, k0 + SK_DEEP, fa, fb, kw);
+      __syncthreads();
+      a_frags(0, a);
+      products(a, b0);
+      a_frags(1, a);
+      b_frags(kw, b0);
+      products(a, b1);
+    }
+  } else {
+    if (!AGAIN) split_load<TM, TN, TAP1, PRE>(P, X, 0, fa, fb, kw);
+    for (int k0 = 0; k0 < P.K; k0 += SK_DEEP) {
+      if (AGAIN) split_load<TM, TN, TAP1, PRE>(P, X, k0, fa, fb, kw);  // no registers for a slice in flight
+      __syncthreads();  // every wave has read the previous slice
+      split_store<TM, TN, AGAIN, PRE>(lead, fa, fb, lds);
+      if (!AGAIN && k0 + SK_DEEP < P.K) split_load<TM, TN, TAP1, PRE>(P, X, k0 + SK_DEEP, fa, fb, kw);
+      __syncthreads();
+#pragma unroll
+      for (int kk = 0; kk < 2; ++kk) {
+        v8bf a[T::TI][3], b[T::TJ][3];
+        a_frags(kk, a);
+#pragma unroll
+        for (int q = 0; q < 3; ++q)
+#pragma unroll
+          for (int j = 0; j < T::TJ; ++j) b[j][q] = km_frag<TN>(Bt + q * T::B_PIECE, wn + 32 * j, kk, lane);
+        products(a, b);
       }
     }
   }
@@ -257,7 +312,7 @@ __device__ __forceinline__ void split_write(const ConvProb P, const v16f (&acc)[
   if (TM > 64) split_strip<TM, TN>(P, acc[TM / 64 - 1], 1, m0, n0, slope, rewrite, lds);
 }
 
-template <int TM, int TN, bool TAP1>
+template <int TM, int TN, bool TAP1, bool PRE>
 __global__ __launch_bounds__(NT, 2) void conv_split_kernel(const ConvProb* __restrict__ probs, ConvGroups grp,
                                                            float slope) {
   using T = SplitTile<TM, TN>;
@@ -275,7 +330,7 @@ __global__ __launch_bounds__(NT, 2) void conv_split_kernel(const ConvProb* __res
   const ConvProb P = probs[pi];
   const int m0 = (lt / P.tiles_n) * TM, n0 = (lt % P.tiles_n) * TN;
   v16f acc[T::TI][T::TJ];
-  split_mainloop<TM, TN, TAP1, false>(P, m0, n0, false, lds, acc);
+  split_mainloop<TM, TN, TAP1, false, PRE>(P, m0, n0, false, lds, acc);
   bool bad = false;
 #pragma unroll
   for (int i = 0; i < T::TI; ++i)
@@ -295,30 +350,68 @@ __global__ __launch_bounds__(NT, 2) void conv_split_kernel(const ConvProb* __res
   for (int lead = 0; lead < 2; ++lead) {
     asm volatile("" : "+s"(again));
     __syncthreads();
-    split_mainloop<TM, TN, TAP1, true>(*again, m0, n0, lead != 0, lds, acc);
+    split_mainloop<TM, TN, TAP1, true, false>(*again, m0, n0, lead != 0, lds, acc);
     __syncthreads();
     split_write<TM, TN>(*again, acc, m0, n0, slope, lead != 0, lds);
   }
 }
 
+// 32 x 32 elements of W per workgroup and step, transposed through LDS.
+__global__ __launch_bounds__(NT) void split_weights_kernel(const SplitWProb* __restrict__ probs) {
+  __shared__ float t[32][33];
+  const SplitWProb P = probs[blockIdx.y];
+  const int tid = threadIdx.x, r = tid >> 3, q = (tid & 7) << 2;
+  const int tk = P.K / 32, tiles = tk * ((P.N + 31) / 32);
+  for (int b = blockIdx.x; b < tiles; b += gridDim.x) {
+    const int k0 = 32 * (b % tk), nb = b / tk;
+    __syncthreads();
+    const bool ok = 32 * nb + q < P.N;
+    const float4 v = ok ? *reinterpret_cast<const float4*>(P.W + (size_t)(k0 + r) * P.N + 32 * nb + q)
+                        : make_float4(0.f, 0.f, 0.f, 0.f);
+    t[r][q] = v.x;
+    t[r][q + 1] = v.y;
+    t[r][q + 2] = v.z;
+    t[r][q + 3] = v.w;
+    __syncthreads();
+    // column r, k rows q .. q + 3 of the tile: lane r + 32 ((q / 8) % 2) of k
+    // block q / 16, half of its 16 bytes
+    uint2 p[3];
+    split2<false>(false, t[q][r], t[q + 1][r], p[0].x, p[1].x, p[2].x);
+    split2<false>(false, t[q + 2][r], t[q + 3][r], p[0].y, p[1].y, p[2].y);
+    char* o = reinterpret_cast<char*>(P.out) + ((size_t)nb * (P.K / 16) + k0 / 16 + (q >> 4)) * 3072 +
+              (r + 32 * ((q >> 3) & 1)) * 16 + (q & 4) * 2;
+#pragma unroll
+    for (int e = 0; e < 3; ++e) *reinterpret_cast<uint2*>(o + e * 1024) = p[e];
+  }
+}
+
 }  // namespace
+
+hipError_t launch_split_weights(const SplitWProb* d_probs, int count, int64_t max_elems, hipStream_t s) {
+  if (count <= 0) return hipSuccess;
+  const int64_t tiles = (max_elems + 1023) / 1024;
+  hipLaunchKernelGGL(split_weights_kernel, dim3(tiles < 1024 ? (unsigned)tiles : 1024u, count), dim3(NT), 0, s, d_probs);
+  return hipGetLastError();
+}
 
 hipError_t launch_conv_split(const ConvProb* d_probs, const ConvGroups& grp, int total_blocks, const ConvVariant& v,
                              float slope, hipStream_t s, hipEvent_t ev_start, hipEvent_t ev_stop) {
   if (grp.n <= 0 || total_blocks <= 0) return hipSuccess;
   if (v.mode != CONV_FWD || v.bt) return hipErrorInvalidValue;
-#define LIPZ_CS(TM, TN)                                                                                              \
-  if (v.tap1)                                                                                                        \
-    hipExtLaunchKernelGGL((conv_split_kernel<TM, TN, true>), dim3(total_blocks), dim3(NT), 0, s, ev_start, ev_stop, \
-                          0, d_probs, grp, slope);                                                                   \
-  else                                                                                                               \
-    hipExtLaunchKernelGGL((conv_split_kernel<TM, TN, false>), dim3(total_blocks), dim3(NT), 0, s, ev_start,         \
-                          ev_stop, 0, d_probs, grp, slope)
+#define LIPZ_CS1(TM, TN, T1, PR)                                                                                  \
+  hipExtLaunchKernelGGL((conv_split_kernel<TM, TN, T1, PR>), dim3(total_blocks), dim3(NT), 0, s, ev_start, ev_stop, \
+                        0, d_probs, grp, slope)
+#define LIPZ_CS(TM, TN)                          \
+  if (v.pre) LIPZ_CS1(TM, TN, true, true);       \
+  else if (v.tap1) LIPZ_CS1(TM, TN, true, false); \
+  else LIPZ_CS1(TM, TN, false, false)
+  if (v.pre && !v.tap1) return hipErrorInvalidValue;
   if (v.tm == 128 && v.tn == 128) { LIPZ_CS(128, 128); }
   else if (v.tm == 128 && v.tn == 64) { LIPZ_CS(128, 64); }
   else if (v.tm == 64 && v.tn == 64) { LIPZ_CS(64, 64); }
   else return hipErrorInvalidValue;
 #undef LIPZ_CS
+#undef LIPZ_CS1
   return hipGetLastError();
 }
 

@@ -70,7 +70,8 @@ struct ColOp {
 };
 
 enum DcOpKind {
-  DC_SAMPLE, DC_GEMM, DC_CONV, DC_BN_FWD, DC_BN_BWD, DC_REDUCE, DC_DOT, DC_HEAD_D, DC_HEAD_G, DC_IM2COL, DC_COL2IM
+  DC_SAMPLE, DC_GEMM, DC_CONV, DC_BN_FWD, DC_BN_BWD, DC_REDUCE, DC_DOT, DC_HEAD_D, DC_HEAD_G, DC_IM2COL, DC_COL2IM,
+  DC_SPLIT_W
 };
 struct DcOp {
   DcOpKind kind;
@@ -428,16 +429,19 @@ struct DcPlan {
   std::vector<RedProb> red_h;
   std::vector<DotProb> dot_h;
   std::vector<ColProb> col_h;
+  std::vector<SplitWProb> splitw_h;
   ConvProb* conv_d = nullptr;
   BnProb* bn_d = nullptr;
   RedProb* red_d = nullptr;
   DotProb* dot_d = nullptr;
   ColProb* col_d = nullptr;
+  SplitWProb* splitw_d = nullptr;
   std::vector<ConvPhase> cph;
   std::vector<BnOp> bnops;
   std::vector<RedOp> redops;
   std::vector<DotOp> dotops;
   std::vector<ColOp> colops;
+  std::vector<ColOp> splitops;  // DC_SPLIT_W: descriptors of splitw_h, max_work elements each
   std::vector<DcOp> train_ops[2], eval_ops[2];
 };
 
@@ -600,6 +604,7 @@ void dc_carve_tables(lipz_grid* g, Carver& cv) {
   P.red_d = cv.take<RedProb>(P.red_h.size());
   P.dot_d = cv.take<DotProb>(P.dot_h.size());
   P.col_d = cv.take<ColProb>(P.col_h.size());
+  P.splitw_d = cv.take<SplitWProb>(P.splitw_h.size());
 }
 
 namespace {
@@ -691,6 +696,7 @@ void add_conv_phase(DcPlan& P, const std::vector<ConvProb>& ps, std::vector<DcOp
       v.mode = p.mode;
       v.bt = bt;
       v.tap1 = p.mode == CONV_FWD && p.cs % 32 == 0;
+      v.pre = v.kernel == CONV_K_SPLIT && v.tap1 && p.Wp;
     }
     size_t k = 0;
     while (k < sets.size() && !(sets[k].first == v && (v.kernel == CONV_K_ANY || sets[k].second[0].N == p.N))) ++k;
@@ -809,11 +815,13 @@ void dc_build(lipz_grid* g) {
   P.red_h.clear();
   P.dot_h.clear();
   P.col_h.clear();
+  P.splitw_h.clear();
   P.cph.clear();
   P.bnops.clear();
   P.redops.clear();
   P.dotops.clear();
   P.colops.clear();
+  P.splitops.clear();
   const int C = g->C, B = g->B, zd = g->zd, xd = g->xd, n = P.n;
   const int64_t sG = g->G.stride, sD = g->D.stride;
   const DcNet &G = P.G, &D = P.D;
@@ -1113,6 +1121,44 @@ void dc_build(lipz_grid* g) {
     std::vector<DcOp>& ev = P.eval_ops[par];
     ev.clear();
     const int NIe = 6 * B;
+    // Weights the evaluation's convolutions take as bf16 pieces: every cell's are
+    // split once, for the five networks' worth of images that use them, into
+    // the idle gradient partials of their layer (6 bytes per weight; two or more
+    // splits have the room), where the layers' work is worth the launch (a 5 us
+    // launch against an eighth of 0.2 ms at 2^34 multiply-adds).
+    int64_t macs = 0;
+    auto room = [&](const DcLayer& L, int64_t part_cell) {
+      const int64_t w = 16 * (int64_t)L.cin * ((L.cout + 31) / 32 * 32);  // whole column blocks
+      return L.cin % 32 == 0 && L.cout % 4 == 0 && L.cout > 16 && part_cell % 4 == 0 && 2 * part_cell >= 3 * w &&
+             6 * w < ((int64_t)1 << 31);
+    };
+    for (int k = 1; k < n; ++k) {
+      if (room(G.L[k], P.gpart_cell[k])) macs += (int64_t)C * 5 * B * side_sq(G.L[k].in_log) * 16 * G.L[k].cin * G.L[k].cout;
+      if (room(D.L[k], P.dpart_cell[k])) macs += (int64_t)C * 5 * NIe * side_sq(D.L[k].out_log) * 16 * D.L[k].cin * D.L[k].cout;
+    }
+    const bool pre_split = macs >= ((int64_t)1 << 34);
+    auto pieces = [&](const DcLayer& L, float* part, int64_t part_cell, int c) {
+      return pre_split && room(L, part_cell) ? reinterpret_cast<uint16_t*>(part + c * part_cell) : nullptr;
+    };
+    if (pre_split) {
+      ColOp op;
+      op.first = (int)P.splitw_h.size();
+      op.max_work = 0;
+      auto add = [&](const float* W, const DcLayer& L, uint16_t* out) {
+        if (!out) return;
+        P.splitw_h.push_back({W, out, 16 * L.cin, L.cout});
+        const int64_t w = 16 * (int64_t)L.cin * ((L.cout + 31) / 32 * 32);
+        if (w > op.max_work) op.max_work = w;
+      };
+      for (int k = 1; k < n; ++k)
+        for (int c = 0; c < C; ++c) {
+          add(Gw(c, k), G.L[k], pieces(G.L[k], P.gpart[k], P.gpart_cell[k], c));
+          add(Dw(c, k), D.L[k], pieces(D.L[k], P.dpart[k], P.dpart_cell[k], c));
+        }
+      op.count = (int)P.splitw_h.size() - op.first;
+      P.splitops.push_back(op);
+      ev.push_back({DC_SPLIT_W, (int)P.splitops.size() - 1});
+    }
     auto egsz = [&](int k) { return (int64_t)B * side_sq(G.L[k].out_log) * G.L[k].nb; };
     {
       std::vector<GemmProb> ps;
@@ -1147,9 +1193,12 @@ void dc_build(lipz_grid* g) {
         for (int i = 0; i < 5; ++i) {
           const int own = g->nbr_h[c * 5 + i];
           for (int r = 0; r < 2; ++r)
-            for (int q = 0; q < 2; ++q)
+            for (int q = 0; q < 2; ++q) {
               ps.push_back(convT_phase(P.gex[k - 1] + (c * 5 + i) * egsz(k - 1), B, L.in_log, L.cin, Gw(own, k), L.cout,
                                        P.gex[k] + (c * 5 + i) * egsz(k), r, q, EPI_STORE, 0, nullptr));
+              ps.back().Wp = pieces(L, P.gpart[k], P.gpart_cell[k], own);
+              ps.back().wp_k = 16 * L.cin;
+            }
         }
       add_conv_phase(P, ps, ev, false);
       ebn(k);
@@ -1187,9 +1236,12 @@ void dc_build(lipz_grid* g) {
           if (k == 0)
             ps.push_back(dense_rows(P.epatch + c * NIe * pcols, NIe, gimg, 16 * P.ic, Dw(own, 0), L.cout, false, out,
                                     EPI_BIAS_ACT, L.act, S.Dp + own * sD + L.off_b));
-          else
+          else {
             ps.push_back(conv_fwd(P.dey[(k - 1) & 1] + (c * 5 + j) * NIe * dsz(k - 1), NIe, L.in_log, L.cin, Dw(own, k),
                                   L.cout, out, EPI_BIAS_ACT, L.act, S.Dp + own * sD + L.off_b));
+            ps.back().Wp = pieces(L, P.dpart[k], P.dpart_cell[k], own);
+            ps.back().wp_k = 16 * L.cin;
+          }
         }
       add_conv_phase(P, ps, ev, false);
     }
@@ -1226,6 +1278,8 @@ hipError_t dc_upload_tables(lipz_grid* g, hipStream_t s) {
     e = hipMemcpyAsync(P.col_d, P.col_h.data(), P.col_h.size() * sizeof(ColProb), hipMemcpyHostToDevice, s);
   if (e == hipSuccess && !P.dot_h.empty())
     e = hipMemcpyAsync(P.dot_d, P.dot_h.data(), P.dot_h.size() * sizeof(DotProb), hipMemcpyHostToDevice, s);
+  if (e == hipSuccess && !P.splitw_h.empty())
+    e = hipMemcpyAsync(P.splitw_d, P.splitw_h.data(), P.splitw_h.size() * sizeof(SplitWProb), hipMemcpyHostToDevice, s);
   return e;
 }
 
@@ -1299,6 +1353,10 @@ hipError_t run_op(lipz_grid* g, const DcOp& op, int step_local, hipStream_t s) {
     case DC_COL2IM: {
       const ColOp& c = P.colops[op.idx];
       return launch_col2im(P.col_d + c.first, c.count, c.max_work, g->slope, s);
+    }
+    case DC_SPLIT_W: {
+      const ColOp& c = P.splitops[op.idx];
+      return launch_split_weights(P.splitw_d + c.first, c.count, c.max_work, s);
     }
     case DC_DOT: {
       const DotOp& d = P.dotops[op.idx];
@@ -1459,6 +1517,7 @@ int dc_check_bounds(const lipz_grid* g, const char* const* lo, const char* const
     if (p.mode == CONV_FWD) {
       if (NI << (p.gh_log + p.gw_log) != p.M) ck.fail_("conv", idx, "M is not a whole number of images");
       ck.range(p.W, 0, p.w_bytes / 4 - 1, "conv W", idx);
+      if (p.Wp) ck.range(p.Wp, 0, (int64_t)((p.N + 31) / 32) * p.wp_k * 48 - 1, "conv split W", idx);
       // largest weight offset the kernel forms
       int64_t wmax = 0;
       for (int t = 0; t < p.taps; ++t) {
@@ -1570,9 +1629,25 @@ extern "C" lipz_status lipz_test_conv(void* hip_stream, void* d_desc, int32_t ki
       if (kind == 5)
         ps.push_back(convT_wgrad_phase(d_x, n_img, side_log, cin, d_w, cout, d_out, 16 * cin, r, q));
     }
+  const bool pre = kernel == 3;  // CONV_K_SPLIT with the weights' pieces, in d_aux
+  if (pre) {
+    if (kind > 1 || !d_aux || cin % 32 || cout % 4) return LIPZ_E_INVAL;
+    kernel = CONV_K_SPLIT;
+    for (ConvProb& p : ps) {
+      p.Wp = (const uint16_t*)d_aux;
+      p.wp_k = 16 * cin;
+    }
+    const SplitWProb sw = {d_w, (uint16_t*)d_aux, 16 * cin, cout};
+    static_assert(4 * sizeof(ConvProb) <= 2048 - 64, "room for the weights' descriptor");
+    SplitWProb* d_sw = reinterpret_cast<SplitWProb*>((char*)d_desc + 2048 - 64);
+    if (hipMemcpy(d_sw, &sw, sizeof(sw), hipMemcpyHostToDevice) != hipSuccess ||
+        launch_split_weights(d_sw, 1, 16 * (int64_t)cin * ((cout + 31) / 32 * 32), (hipStream_t)hip_stream) != hipSuccess)
+      return LIPZ_E_HIP;
+  }
   ConvVariant v;
   memset(&v, 0, sizeof(v));
   v.kernel = kernel;
+  v.pre = pre;
   if (kernel != CONV_K_ANY) {
     if (kernel != CONV_K_WIDE && kernel != CONV_K_SPLIT) return LIPZ_E_INVAL;
     if (!((tile_m == 128 && (tile_n == 128 || tile_n == 64)) || (tile_m == 64 && tile_n == 64))) return LIPZ_E_INVAL;

@@ -363,6 +363,8 @@ struct ConvProb {
   const float* W;
   int32_t wsc, wsn;
   uint32_t w_bytes;
+  const uint16_t* Wp;      // W's three bf16 pieces (SplitWProb), or null
+  int32_t wp_k;            // rows of W
   PosMap omap;             // grid -> C
   // CONV_WG
   const float* P;          // the plain operand (output gradient)
@@ -438,15 +440,28 @@ struct ConvGroups {
 // outputs, mode, transposed weights (bt), whole slices within one tap (tap1).
 enum ConvKernel : int32_t { CONV_K_ANY = 0, CONV_K_WIDE = 1, CONV_K_SPLIT = 2 };
 struct ConvVariant {
-  int32_t kernel, tm, tn, mode, bt, tap1;
+  int32_t kernel, tm, tn, mode, bt, tap1, pre;  // pre: the weights' pieces are there (CONV_K_SPLIT with tap1)
   bool operator==(const ConvVariant& o) const {
-    return kernel == o.kernel && tm == o.tm && tn == o.tn && mode == o.mode && bt == o.bt && tap1 == o.tap1;
+    return kernel == o.kernel && tm == o.tm && tn == o.tn && mode == o.mode && bt == o.bt && tap1 == o.tap1 &&
+           pre == o.pre;
   }
 };
 hipError_t launch_conv_wide(const ConvProb* d_probs, const ConvGroups& grp, int total_blocks, const ConvVariant& v,
                             float slope, hipStream_t s, hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);
 hipError_t launch_conv_split(const ConvProb* d_probs, const ConvGroups& grp, int total_blocks, const ConvVariant& v,
                              float slope, hipStream_t s, hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);
+
+// A weight matrix W [K][N] (K a multiple of 32, N of 4) as its three bf16 pieces
+// (split.h), in the order of v_mfma_f32_32x32x16_bf16's second operand: out
+// [ceil(N / 32)][K / 16][3 pieces][64 lanes][8], lane l's eight being column l %
+// 32 of the block, k 8 (l / 32) .. + 7 (zeros past N).
+struct SplitWProb {
+  const float* W;
+  uint16_t* out;
+  int32_t K, N;
+};
+// All of `count` matrices, K N at most max_elems.
+hipError_t launch_split_weights(const SplitWProb* d_probs, int count, int64_t max_elems, hipStream_t s);
 
 // Launch every problem of one phase (problems in device memory).
 hipError_t launch_conv_grouped(const ConvProb* d_probs, const ConvGroups& grp, int total_blocks, float slope,

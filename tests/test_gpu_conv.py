@@ -1,8 +1,9 @@
 """The convolution kernels on the GPU, one convolution at a time
 (lipz_test_conv), at sizes that leave tiles, slices and splits partly filled:
 against torch's fp64 convolutions on the CPU, and the wide fp32 tiles bit for
-bit against the 64 x 64 ones; infinities and NaNs of the bf16 kernel against
-fp32 products."""
+bit against the 64 x 64 ones; weights split beforehand bit for bit
+against weights split on the way; infinities and NaNs of the bf16 kernel
+against fp32 products."""
 import numpy as np
 import pytest
 
@@ -16,7 +17,7 @@ import torch.nn.functional as F  # noqa: E402
 
 import paper_1811_12843_amd as L  # noqa: E402
 
-ANY, WIDE, SPLIT = 0, 1, 2
+ANY, WIDE, SPLIT, PRE = 0, 1, 2, 3
 SLOPE = 0.2
 KINDS = ["conv", "convT", "conv_dgrad", "convT_dgrad", "conv_wgrad", "convT_wgrad"]
 # (images, log2 side, c_in, c_out): channels a multiple of 32 (a slice within one tap) and not, one and several
@@ -85,6 +86,8 @@ def _run(kind, shape, kernel, tile, x, w, bias, aux):
     size = {"conv": (n, 1 << h >> 1, 1 << h >> 1, co), "convT": (n, 2 << h, 2 << h, co), "conv_dgrad": (n, 1 << h, 1 << h, ci),
             "convT_dgrad": (n, 1 << h, 1 << h, ci), "conv_wgrad": (splits, 16 * ci + 1, co),
             "convT_wgrad": (splits, 16 * ci, co)}[kind]
+    if kernel == PRE:
+        aux = torch.full((24 * ci * -(-co // 32) * 32,), float("nan"))  # the weights' pieces
     dx, dw, db, da = (t.cuda().contiguous() for t in (x, w, bias, aux))
     out = torch.full(size, float("nan"), device="cuda")
     desc = torch.zeros(2048, dtype=torch.uint8, device="cuda")
@@ -121,10 +124,13 @@ def test_kernels_match_fp64(kind, shape):
             base = got
         elif kernel == WIDE:
             assert torch.equal(got, base), (tile, float((got - base).abs().max()))
+        elif kernel == SPLIT and ci % 32 == 0:
+            pre = _run(kind, shape, PRE, tile, x, w, bias, aux)
+            assert torch.equal(pre, got), (tile, float((pre - got).abs().max()))
 
 
 @pytest.mark.parametrize("kind", ["conv", "convT"])
-@pytest.mark.parametrize("shape", [(9, 3, 32, 64), (17, 2, 36, 132)])
+@pytest.mark.parametrize("shape", [(9, 3, 32, 64), (17, 2, 36, 132), (9, 3, 64, 132)])
 def test_split_kernel_keeps_infinities_and_nans(kind, shape):
     """Operands with infinities, NaNs, zeros and a value next to fp32's largest: the same outputs are infinite (with
     the same sign) and NaN as with fp32 products, and the others agree."""
@@ -143,7 +149,7 @@ def test_split_kernel_keeps_infinities_and_nans(kind, shape):
     inf, fin = torch.isinf(base), torch.isfinite(base)
     assert fin.any() and inf.any() and torch.isnan(base).any()
     for tile in TILES:
-        got = _run(kind, shape, SPLIT, tile, x, w, bias, aux)
+        got = _run(kind, shape, SPLIT if shape[2] % 32 else PRE, tile, x, w, bias, aux)
         assert torch.equal(torch.isnan(got), torch.isnan(base)), tile
         assert torch.equal(torch.isinf(got), inf), tile
         assert torch.equal(got[inf], base[inf]), tile
