@@ -41,3 +41,16 @@ def test_eval_matches_oracle_at_any_batch(batch, pop, mode):
         gg.set_state(st)
         for a, b in zip(gg.eval(1), coevo.evaluate(S, st, data, 1)):
             assert _close(a, b, wl), np.max(np.abs(a - b) / np.abs(b))
+
+
+@pytest.mark.parametrize("image_channels,g_hidden,d_hidden", [(1, [36, 20], [20, 36]), (4, [132, 12], [12, 132])])
+def test_dcgan_with_channels_off_every_power_of_two(image_channels, g_hidden, d_hidden, monkeypatch):
+    """Batch norm's and the patch kernels' walks over channels that do not divide their strides."""
+    import test_gpu_dcgan as dc
+
+    wl = dc._wl(rows=2, cols=2, img=(16, 16, image_channels), x_dim=256 * image_channels, z_dim=8, g_hidden=g_hidden,
+                d_hidden=d_hidden, batch=5, lr0_g=2e-3, lr0_d=2e-3,
+                data=dict(dc.WORKLOADS["dc16_2x2"]()["data"], c=image_channels, n=500 + image_channels))
+    monkeypatch.setitem(dc.WORKLOADS, "odd", lambda: wl)
+    dc.test_eval_matches_oracle("odd")
+    dc.test_train_step_matches_oracle("odd", 1)
