@@ -614,9 +614,11 @@ namespace {
 // slice's 32 positions being whole rows).  Their outputs (and auxiliary
 // operands) are addressed as float4 too.
 bool conv_tile_ok(const ConvProb& p) {
-  if (p.gen || p.N <= 16 || p.taps <= 0 || p.N % 4 || p.cs % 4 || !aligned16(p.C)) return false;
-  if (p.mode == CONV_WG) return p.ldc % 4 == 0 && p.split_stride % 4 == 0 && p.gw_log <= 5;
-  return p.omap.ld % 4 == 0 && (p.epi != EPI_DACT || aligned16(p.aux));
+  if (p.gen || p.N <= 16 || p.taps <= 0 || p.N % 4 || p.cs % 4) return false;
+  // column taps are stored element by element, at any address
+  if (p.mode == CONV_WG)
+    return p.gw_log <= 5 && (p.n_inner || (p.ldc % 4 == 0 && p.split_stride % 4 == 0 && aligned16(p.C)));
+  return aligned16(p.C) && p.omap.ld % 4 == 0 && (p.epi != EPI_DACT || aligned16(p.aux));
 }
 
 // Tile of a set of like problems: the largest one that still gives the chip
