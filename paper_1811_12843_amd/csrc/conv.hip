@@ -458,6 +458,61 @@ __global__ __launch_bounds__(NT, 2) void conv_kernel(const ConvProb* __restrict_
   else conv_tile<64>(P, m0, n0, split, kbeg, kend, slope, As, Bs);
 }
 
+// Column sums over the positions of a split (a bias gradient by itself: no
+// taps, ones_row 0, N <= 64), in conv_kernel's order: 16-deep blocks in turn
+// and, in a block, k = u, 4 + u, 8 + u, 12 + u for u = 0 .. 3.  The workgroup
+// brings the split's positions into LDS, then a lane per column adds them up:
+// one chain of additions is all the parallelism the order leaves, so the loads
+// must not be in it (9 cells, 3 columns, 16 splits of 4096: 150 us as tiles of
+// conv_kernel, 56 here; 16 cells, 64 splits: 209 and 126).
+constexpr int SUM_FLOATS = 12288;
+__global__ __launch_bounds__(NT) void conv_sum_kernel(const ConvProb* __restrict__ probs, ConvGroups grp) {
+  __shared__ __align__(16) float buf[SUM_FLOATS];
+  const int b = blockIdx.x, tid = threadIdx.x;
+  int gi = 0;
+#pragma unroll
+  for (int q = 1; q < GEMM_MAX_GROUPS; ++q)
+    if (q < grp.n && b >= grp.first_block[q]) gi = q;
+  const int rel = xcd_remap(b - grp.first_block[gi], grp.blocks[gi]);
+  if (rel >= grp.real_tiles[gi]) return;
+  const ConvProb P = probs[grp.first_prob[gi] + rel / grp.tiles_per_prob[gi]];
+  const int split = rel % grp.tiles_per_prob[gi];
+  const int kbeg = split * P.ksplit, kend = min(P.K, kbeg + P.ksplit), N = P.N;
+  // columns in LDS one after the other; a chain reads 16 of its positions while
+  // it adds the 16 before
+  const int rows = (SUM_FLOATS / N - 20) & ~15, pitch = rows + 20;
+  float s = 0.f;
+  for (int k0 = kbeg; k0 < kend; k0 += rows) {
+    const int nk = min(rows, kend - k0), pad = (nk + 15) & ~15;
+    __syncthreads();
+#pragma unroll 8
+    for (int i = tid; i < pad * N; i += NT) {
+      const int k = i / N, n = i - k * N;
+      buf[n * pitch + k] = k < nk ? P.P[(int64_t)map_off(P.pmap, grid_pos(k0 + k, P.gh_log, P.gw_log)) + n] : 0.f;
+    }
+    __syncthreads();
+    if (tid < N) {
+      const v4f* c = reinterpret_cast<const v4f*>(buf + tid * pitch);
+      v4f x[4];
+#pragma unroll
+      for (int g = 0; g < 4; ++g) x[g] = c[g];
+      for (int kb = 0; kb < pad; kb += 16) {
+        v4f y[4];
+#pragma unroll
+        for (int g = 0; g < 4; ++g) y[g] = c[kb / 4 + 4 + g];  // past the last block: unused
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+          for (int g = 0; g < 4; ++g) s += x[g][u];
+#pragma unroll
+        for (int g = 0; g < 4; ++g) x[g] = y[g];
+      }
+    }
+  }
+  if (tid < N) P.C[(int64_t)split * P.split_stride + (int64_t)P.brow * P.ldc + tid] = s;
+}
+
 // ---------------------------------------------------------------------------
 // Split-K sums + Adam: thread e of descriptor d sums the splits of its
 // gradient element in split order and takes the Adam step of the parameter.
@@ -858,6 +913,13 @@ hipError_t launch_conv_grouped(const ConvProb* d_probs, const ConvGroups& grp, i
                                hipStream_t s, hipEvent_t ev_start, hipEvent_t ev_stop) {
   if (grp.n <= 0 || total_blocks <= 0) return hipSuccess;
   hipExtLaunchKernelGGL(conv_kernel, dim3(total_blocks), dim3(NT), 0, s, ev_start, ev_stop, 0, d_probs, grp, slope);
+  return hipGetLastError();
+}
+
+hipError_t launch_conv_sum(const ConvProb* d_probs, const ConvGroups& grp, int total_blocks, hipStream_t s,
+                           hipEvent_t ev_start, hipEvent_t ev_stop) {
+  if (grp.n <= 0 || total_blocks <= 0) return hipSuccess;
+  hipExtLaunchKernelGGL(conv_sum_kernel, dim3(total_blocks), dim3(NT), 0, s, ev_start, ev_stop, 0, d_probs, grp);
   return hipGetLastError();
 }
 

@@ -650,10 +650,11 @@ int add_conv_launch(DcPlan& P, const std::vector<ConvProb>& ps, const ConvVarian
   int blocks = 0, prev = -1;
   for (size_t k = 0; k < ps.size(); ++k) {
     ConvProb p = ps[k];
-    p.tn = v.kernel != CONV_K_ANY ? v.tn : (p.N <= 16 ? 16 : 64);
-    const int tm = v.kernel != CONV_K_ANY ? v.tm : 64;
+    const bool tiled = v.kernel == CONV_K_WIDE || v.kernel == CONV_K_SPLIT;
+    p.tn = tiled ? v.tn : (p.N <= 16 ? 16 : 64);
+    const int tm = tiled ? v.tm : 64;
     // the wide tiles' first row tile adds up the ones row, which has no tile of its own there
-    const int rows = v.kernel != CONV_K_ANY && p.mode == CONV_WG ? p.taps * p.cs : p.M;
+    const int rows = tiled && p.mode == CONV_WG ? p.taps * p.cs : p.M;
     p.tiles_m = (rows + tm - 1) / tm;
     p.tiles_n = (p.N + p.tn - 1) / p.tn;
     if (p.mode != CONV_WG) p.splits = 1;
@@ -699,6 +700,8 @@ void add_conv_phase(DcPlan& P, const std::vector<ConvProb>& ps, std::vector<DcOp
       v.bt = bt;
       v.tap1 = p.mode == CONV_FWD && p.cs % 32 == 0;
       v.pre = v.kernel == CONV_K_SPLIT && v.tap1 && p.Wp;
+    } else if (p.mode == CONV_WG && p.taps == 0 && p.ones_row == 0 && p.N <= 64 && !p.n_inner) {
+      v.kernel = CONV_K_SUM;
     }
     size_t k = 0;
     while (k < sets.size() && !(sets[k].first == v && (v.kernel == CONV_K_ANY || sets[k].second[0].N == p.N))) ++k;
@@ -707,7 +710,7 @@ void add_conv_phase(DcPlan& P, const std::vector<ConvProb>& ps, std::vector<DcOp
   }
   for (auto& s : sets) {
     ConvVariant v = s.first;
-    if (v.kernel != CONV_K_ANY) conv_tile_size(s.second, v);
+    if (v.kernel == CONV_K_WIDE || v.kernel == CONV_K_SPLIT) conv_tile_size(s.second, v);
     ops.push_back({DC_CONV, add_conv_launch(P, s.second, v)});
   }
 }
@@ -1313,6 +1316,7 @@ hipError_t launch_conv(const ConvPhase& ph, const ConvProb* d, float slope, hipS
                        hipEvent_t e1 = nullptr) {
   switch (ph.var.kernel) {
     case CONV_K_SPLIT: return launch_conv_split(d, ph.grp, ph.tiles, ph.var, slope, s, e0, e1);
+    case CONV_K_SUM: return launch_conv_sum(d, ph.grp, ph.tiles, s, e0, e1);
     case CONV_K_WIDE: return launch_conv_wide(d, ph.grp, ph.tiles, ph.var, slope, s, e0, e1);
     default: return launch_conv_grouped(d, ph.grp, ph.tiles, slope, s, e0, e1);
   }

@@ -436,9 +436,11 @@ struct ConvGroups {
 //     conv_kernel in its order, bit for bit;
 //   CONV_K_SPLIT: conv_split_kernel (conv_split.hip), forward problems with
 //     row-major weights, fp32 products on the bf16 matrix cores.
-// The last two have one tile, mode and operand layout per launch: tm x tn
+//   CONV_K_SUM: conv_sum_kernel (conv.hip), column sums alone (a bias
+//     gradient's problem: no taps, at most 64 columns), conv_kernel's order.
+// CONV_K_WIDE and CONV_K_SPLIT have one tile, mode and operand layout per launch: tm x tn
 // outputs, mode, transposed weights (bt), whole slices within one tap (tap1).
-enum ConvKernel : int32_t { CONV_K_ANY = 0, CONV_K_WIDE = 1, CONV_K_SPLIT = 2 };
+enum ConvKernel : int32_t { CONV_K_ANY = 0, CONV_K_WIDE = 1, CONV_K_SPLIT = 2, CONV_K_SUM = 3 };
 struct ConvVariant {
   int32_t kernel, tm, tn, mode, bt, tap1, pre;  // pre: the weights' pieces are there (CONV_K_SPLIT with tap1)
   bool operator==(const ConvVariant& o) const {
@@ -450,6 +452,8 @@ hipError_t launch_conv_wide(const ConvProb* d_probs, const ConvGroups& grp, int 
                             float slope, hipStream_t s, hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);
 hipError_t launch_conv_split(const ConvProb* d_probs, const ConvGroups& grp, int total_blocks, const ConvVariant& v,
                              float slope, hipStream_t s, hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);
+hipError_t launch_conv_sum(const ConvProb* d_probs, const ConvGroups& grp, int total_blocks, hipStream_t s,
+                           hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);
 
 // A weight matrix W [K][N] (K a multiple of 32, N of 4) as its three bf16 pieces
 // (split.h), in the order of v_mfma_f32_32x32x16_bf16's second operand: out
