@@ -343,13 +343,13 @@ def run_workload(L, torch, name, steps, warmup, eval_reps, data_n=0, bands=0):
         cfg_desc.update(g=[wl["z_dim"]] + wl["g_hidden"] + [wl["x_dim"]], d=[wl["x_dim"]] + wl["d_hidden"] + [1])
         data_desc = (f"synthetic (seeded MNIST-shaped blobs, {len(data_np)} x {wl['x_dim']}); "
                      "random-init MLPs")
-        kernel = "grouped GEMM (gemm_fast_kernel + gemm_wave_kernel)"
+        kernel = "grouped GEMM (gemm_kernel + gemm_wave_kernel)"
     else:
         cfg_desc.update(image=list(wl["img"]), z=wl["z_dim"], g_channels=wl["g_hidden"],
                         d_channels=wl["d_hidden"], net="dcgan")
         data_desc = (f"synthetic (seeded colour fields + blobs, {len(data_np)} x {wl['img'][0]}x{wl['img'][1]}"
                      f"x{wl['img'][2]} NHWC); random-init DCGAN-style conv nets")
-        kernel = "implicit-GEMM convolution (conv_kernel) + grouped GEMM"
+        kernel = "implicit-GEMM convolution (conv_wide_kernel, conv_split_kernel, conv_kernel) + grouped GEMM"
     f_ev, f_tr, f_mix = gemm_flops_per_generation(wl)
     f_gen = f_ev + f_tr + f_mix
     avg_ms = gemm_ms / max(launches, 1)

@@ -1097,7 +1097,7 @@ void gemm_set_extents(GemmProb& p) {
 }
 
 bool gemm_fast_ok(const GemmProb& p) {
-  // the fast kernel instantiates the three operand layouts the library uses:
+  // the three operand layouts the library uses:
   // (A, B) = (row, row) forward, (row, W^T) input gradient, (X^T, row) weight gradient
   return !(p.a_trans && p.b_trans) && (p.vec & 3) == 3 && p.a_bytes > 0 && p.b_bytes > 0 && p.a_bytes < 0x7FFFFFF0u &&
          p.b_bytes < 0x7FFFFFF0u;

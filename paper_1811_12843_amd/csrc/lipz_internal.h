@@ -268,9 +268,9 @@ __host__ __device__ inline int xcd_group_tile(int b, int nb, const GemmGroups& g
 // Tile height (32 or 64 rows) for a phase that has `tiles64` tiles of 64x64.
 int gemm_tile_rows(int tiles64);
 
-// True when a problem can use the fast kernel: one of the three operand
-// layouts it instantiates, 16-byte aligned rows of both operands and extents
-// below 2 GiB (buffer-load offsets are 32-bit).
+// True for one of the library's three operand layouts with 16-byte aligned
+// rows of both operands and extents below 2 GiB (gemm_wave_kernel's offsets
+// are 32-bit): phases of such problems may sum in four chains.
 bool gemm_fast_ok(const GemmProb& p);
 // Fill a_bytes / b_bytes from the problem's shape (0 if they do not fit 32 bits).
 void gemm_set_extents(GemmProb& p);

@@ -54,3 +54,27 @@ def test_dcgan_with_channels_off_every_power_of_two(image_channels, g_hidden, d_
     monkeypatch.setitem(dc.WORKLOADS, "odd", lambda: wl)
     dc.test_eval_matches_oracle("odd")
     dc.test_train_step_matches_oracle("odd", 1)
+
+
+def test_evaluation_with_split_weights_leaves_training_alone():
+    """A DCGAN grid large enough that the evaluation splits its weights ahead (into the idle gradient partials): the
+    evaluation repeats bit for bit after a training step's partials went there, and the step's results are those of a
+    step without an evaluation before it."""
+    import synth
+
+    wl = synth.small_workload("celeba_dcgan_4x4", rows=2, cols=2, img=(64, 64, 3), x_dim=64 * 64 * 3, z_dim=16,
+                              g_hidden=[256, 128, 64, 32], d_hidden=[32, 64, 128, 256], batch=16,
+                              data=dict(n=256, h=64, w=64))
+    data = synth.make_dataset(wl["data"])
+    print("[case] dcgan 64x64 eval around a training step", flush=True)
+    with GpuGrid(wl, data) as a, GpuGrid(wl, data) as b:
+        first = a.eval(0)
+        st = a.get_state()
+        la, lb = a.train(0, 0, 1), b.train(0, 0, 1)
+        assert np.array_equal(la, lb)
+        sa, sb = a.get_state(), b.get_state()
+        for f in ("Gp", "Gm", "Gv", "Dp", "Dm", "Dv"):
+            assert np.array_equal(getattr(sa, f), getattr(sb, f)), f
+        a.set_state(st)
+        for x, y in zip(a.eval(0), first):
+            assert np.array_equal(x, y)
