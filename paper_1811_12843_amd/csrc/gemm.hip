@@ -347,6 +347,42 @@ __device__ __forceinline__ void epi_load(const GemmProb& P, const EpiPos<BM>& E,
 // (and v's) are fused one way or the other: OLD_FIRST rounds the old moment's
 // product first, else the gradient's.  Which is GemmProb::vec's to say: a
 // network of given sizes trains to the same bits whichever kernel runs it.
+//
+// Where it can, with the divisions and the square root without the scaling and special
+// cases of their IEEE sequences (a reciprocal refined once, the quotient
+// twice; a square root moved by an ulp where its residuals say so), for
+// operands in the range where those do nothing: the same bits in 35 vector
+// instructions per element instead of 58 (a training step of 16 MNIST cells:
+// 191 us without, 188 with; of four 2-D cells 69 and 66).
+__device__ __forceinline__ float refined_rcp(float d) {
+  const float y = __builtin_amdgcn_rcpf(d);
+  return fmaf(fmaf(-d, y, 1.f), y, y);
+}
+__device__ __forceinline__ float div_by(float n, float d, float y) {  // y = refined_rcp(d)
+  float q = n * y;
+  q = fmaf(fmaf(-d, q, n), y, q);
+  return fmaf(fmaf(-d, q, n), y, q);
+}
+__device__ __forceinline__ float root(float x) {
+  const float s = __builtin_amdgcn_sqrtf(x);
+  const float lo = __uint_as_float(__float_as_uint(s) - 1u), hi = __uint_as_float(__float_as_uint(s) + 1u);
+  const float r = fmaf(-lo, s, x) <= 0.f ? lo : s;
+  return fmaf(-hi, s, x) > 0.f ? hi : r;
+}
+// v zero, or of magnitude 2^lo .. 2^hi: the smallest of bits - 1 (zeros wrap to
+// the largest) and the largest of bits.
+struct Range {
+  uint32_t lo = 0xFFFFFFFFu, hi = 0u;
+  __device__ __forceinline__ void take(float v) {
+    const uint32_t b = __float_as_uint(v) & 0x7FFFFFFFu;
+    lo = min(lo, b - 1u);
+    hi = max(hi, b);
+  }
+  __device__ __forceinline__ bool inside(int lo_exp, int hi_exp) const {
+    return lo >= ((uint32_t)(127 + lo_exp) << 23) - 1u && hi <= ((uint32_t)(127 + hi_exp) << 23);
+  }
+};
+
 template <int BM, bool WT, bool OLD_FIRST>
 __device__ __forceinline__ void adam(const GemmProb& P, const v4f (&acc)[Tile<BM>::NQ], const EpiPos<BM>& E,
                                      const EpiIn<BM>& in, const float* bc) {
@@ -356,21 +392,38 @@ __device__ __forceinline__ void adam(const GemmProb& P, const v4f (&acc)[Tile<BM
   const __amdgpu_buffer_rsrc_t rV = make_rsrc(P.v, kWholeBuffer);
   const float lr = *as_global(P.lr);
   const float bc1 = bc[0], bc2 = bc[1];
+  // with these and m, v in the ranges below every quotient and every
+  // intermediate stays a normal number
+  const bool plain = lr >= 0x1p-20f && lr <= 1.f && bc1 >= 0x1p-20f && bc2 >= 0x1p-20f && ac.eps >= 0x1p-30f && ac.eps <= 1.f;
+  const float y1 = refined_rcp(bc1), y2 = refined_rcp(bc2);
 #pragma unroll
   for (int q = 0; q < Tile<BM>::NQ; ++q) {
     v4f pn, mn, vn;
+    Range rm, rv;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const float g = P.gscale != 0.f ? acc[q][r] * P.gscale : acc[q][r];
       const float g2 = ac.one_minus_beta2 * g;
-      const float m = OLD_FIRST ? fmaf(ac.one_minus_beta1, g, ac.beta1 * in.m[q][r])
-                                : fmaf(ac.beta1, in.m[q][r], ac.one_minus_beta1 * g);
-      const float v = OLD_FIRST ? fmaf(g2, g, ac.beta2 * in.v[q][r]) : fmaf(ac.beta2, in.v[q][r], g2 * g);
-      float p = in.x[q][r] - lr * (m / bc1) / (sqrtf(v / bc2) + ac.eps);
-      if (P.clip > 0.f) p = p > P.clip ? P.clip : (p < -P.clip ? -P.clip : p);  // keeps NaN
-      pn[r] = p;
-      mn[r] = m;
-      vn[r] = v;
+      mn[r] = OLD_FIRST ? fmaf(ac.one_minus_beta1, g, ac.beta1 * in.m[q][r])
+                        : fmaf(ac.beta1, in.m[q][r], ac.one_minus_beta1 * g);
+      vn[r] = OLD_FIRST ? fmaf(g2, g, ac.beta2 * in.v[q][r]) : fmaf(ac.beta2, in.v[q][r], g2 * g);
+      rm.take(mn[r]);
+      rv.take(vn[r]);
+    }
+    if (__all(plain && rm.inside(-80, 20) && rv.inside(-100, 20))) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const float den = root(div_by(vn[r], bc2, y2)) + ac.eps;
+        pn[r] = in.x[q][r] - div_by(lr * div_by(mn[r], bc1, y1), den, refined_rcp(den));
+      }
+    } else {
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        pn[r] = in.x[q][r] - lr * (mn[r] / bc1) / (sqrtf(vn[r] / bc2) + ac.eps);
+    }
+    if (P.clip > 0.f) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) pn[r] = pn[r] > P.clip ? P.clip : (pn[r] < -P.clip ? -P.clip : pn[r]);  // keeps NaN
     }
     if (E.ok(P, q)) {
       const uint32_t o = E.off(P, q);

@@ -66,3 +66,42 @@ def test_any_alignment_gives_the_same_sums(shape, trans):
                 aligned = not any((r + pad) % 4 for r in rows_len) and shift == 0
                 chains = 4 if v in (2, 3) or (v == 0 and aligned and K >= 512) else 1
                 assert np.array_equal(base.setdefault(chains, out), out), (tile_rows, pad, shift, v)
+
+
+@pytest.mark.parametrize("outlier", [1e10, 1e-30, float("inf"), float("nan")])
+@pytest.mark.parametrize("rows,fi,fo", [(100, 64, 64), (37, 45, 70)])
+def test_adam_short_and_full_divisions_agree(rows, fi, fo, outlier):
+    """The weight gradient's Adam step with moments in the range of the short division sequence, and with one element
+    per wave and pass outside it (the full sequence for the whole pass): every other element comes out the same."""
+    g = np.random.default_rng(rows)
+    X = torch.from_numpy(g.standard_normal((rows, fi)).astype(np.float32)).cuda()
+    dY = torch.from_numpy((g.standard_normal((rows, fo)) * 1e-2).astype(np.float32)).cuda()
+    P0 = g.standard_normal((fi + 1, fo)).astype(np.float32)
+    # magnitudes over the whole range, zeros among them
+    m0 = (g.standard_normal((fi + 1, fo)) * 10.0 ** g.uniform(-20, 3, (fi + 1, fo))).astype(np.float32)
+    v0 = (10.0 ** g.uniform(-25, 3, (fi + 1, fo))).astype(np.float32)
+    m0[::3, ::5] = 0.0
+    v0[::3, ::5] = 0.0
+    at = np.zeros((fi + 1, fo), bool)
+    at[::8, ::32] = True
+    out = []
+    for plant in (False, True):
+        m, v = m0.copy(), v0.copy()
+        if plant:
+            (v if outlier == 1e-30 else m)[at] = np.float32(outlier) * (1e-5 if outlier == 1e-30 else 1.0)
+        dX, dYp = X.clone(), dY.clone()
+        if outlier == 1e-30:  # no gradient in those rows, so that the moment stays as small
+            dX[:, ::8] = 0.0
+        t = [torch.from_numpy(a).cuda() for a in (P0.copy(), m, v)]
+        lr = torch.tensor([3e-4], device="cuda")
+        step = torch.tensor([6], dtype=torch.int32, device="cuda")
+        desc = torch.zeros(256, dtype=torch.uint8, device="cuda")
+        print(f"[case] adam {rows} {fi} {fo} outlier {outlier} planted {plant}", flush=True)
+        L.lipz_test_gemm(torch.cuda.current_stream().cuda_stream, desc.data_ptr(), fi + 1, fo, rows, dX.data_ptr(), fi, 1,
+                         fi, dYp.data_ptr(), fo, 0, t[0].data_ptr(), fo, 3, 0, 0.2, d_m=t[1].data_ptr(),
+                         d_v=t[2].data_ptr(), d_lr=lr.data_ptr(), d_t=step.data_ptr(), step_local=0, tile_rows=32)
+        torch.cuda.synchronize()
+        out.append([x.cpu().numpy() for x in t])
+    for a, b in zip(*out):
+        assert np.isfinite(a).all()
+        assert np.array_equal(a[~at], b[~at])
