@@ -24,25 +24,36 @@
 // with PRE, 10.2 without; all weights of 16 cells (44 million) are split in
 // 0.10 ms.  Splitting the weights ahead but staging them in LDS gained nothing.
 //
+// A tile with a non-finite sum (split.h) is multiplied again in fp32, as 64 x 64
+// tiles of conv_wide_kernel's loop: conv_kernel's sums, bit for bit, for its
+// finite outputs too.  A 64 x 64 tile's registers and LDS fit in what the bf16
+// loop holds anyway.  (4x4 grid of 64x64 images, evaluation 44.0 ms: 48.5 with
+// one discriminator all NaN, 59.5 when such tiles took two more bf16 passes and
+// were noticed at their end only; with every network NaN 66 and 115, on
+// conv_kernel 83.)
+//
 // TAP1: the channels per tap are a multiple of 32, so a slice lies within one
 // tap and its shift and weight row are scalars; otherwise every float4
 // carries its own (tap, channel), advanced without divisions.
 #include <hip/hip_ext.h>
 
-#include "conv_tile.h"
+#include "conv_wide_tile.h"
 
 namespace lipz {
 
 namespace {
+
+constexpr int max3(int a, int b, int c) { return a > b ? (a > c ? a : c) : (b > c ? b : c); }
 
 template <int TM, int TN>
 struct SplitTile {
   static constexpr int A_PIECE = TM * RK_PITCH, B_PIECE = SK_DEEP * km_pitch(TN);
   static constexpr int A_F4 = TM / 32, B_F4 = TN / 32;  // float4 of a slice per thread
   static constexpr int TI = TM / 64, TJ = TN / 64;      // 32 x 32 MFMA tiles per wave
-  static constexpr int SPLIT_BYTES = 3 * (A_PIECE + B_PIECE);
-  static constexpr int WRITE_BYTES = 4 * 32 * (TN / 2 + 4) * 4;  // the epilogue's strips
-  static constexpr int LDS = SPLIT_BYTES > WRITE_BYTES ? SPLIT_BYTES : WRITE_BYTES;
+  // A's pieces, then the stores' strips; B's pieces.  Tiles with non-finite sums
+  // use the two as the stages of 64 x 64 fp32 tiles.
+  static constexpr int STAGE = 4 * STAGE_FLOATS<64, 64>, STRIPS = 4 * 16 * (TN / 2 + 4) * 4;
+  static constexpr int LDS0 = max3(3 * A_PIECE, STRIPS, STAGE), LDS1 = max3(3 * B_PIECE, 0, STAGE);
 };
 
 // Operand loads of a slice.  A: thread t takes k 8 (t % 4) .. + 7 of rows
@@ -157,47 +168,46 @@ __device__ __forceinline__ void split_load(const ConvProb& P, SplitCtx<TM, TN, T
 }
 
 // The operand slices, split, into their three LDS tiles each.
-template <int TM, int TN, bool AGAIN, bool PRE>
-__device__ __forceinline__ void split_store(bool lead, const float4 (&fa)[TM / 32], const float4 (&fb)[TN / 32],
-                                            char* lds) {
+template <int TM, int TN, bool PRE>
+__device__ __forceinline__ void split_store(const float4 (&fa)[TM / 32], const float4 (&fb)[TN / 32], char* At, char* Bt) {
   using T = SplitTile<TM, TN>;
   const int tid = threadIdx.x;
 #pragma unroll
   for (int h = 0; h < TM / 64; ++h) {
     const float4 u = fa[2 * h], v = fa[2 * h + 1];
     uint4 p[3];
-    split2<AGAIN>(lead, u.x, u.y, p[0].x, p[1].x, p[2].x);
-    split2<AGAIN>(lead, u.z, u.w, p[0].y, p[1].y, p[2].y);
-    split2<AGAIN>(lead, v.x, v.y, p[0].z, p[1].z, p[2].z);
-    split2<AGAIN>(lead, v.z, v.w, p[0].w, p[1].w, p[2].w);
+    split2(u.x, u.y, p[0].x, p[1].x, p[2].x);
+    split2(u.z, u.w, p[0].y, p[1].y, p[2].y);
+    split2(v.x, v.y, p[0].z, p[1].z, p[2].z);
+    split2(v.z, v.w, p[0].w, p[1].w, p[2].w);
     const int o = rk_off((tid >> 2) + 64 * h, tid & 3);
 #pragma unroll
-    for (int q = 0; q < 3; ++q) *reinterpret_cast<uint4*>(lds + q * T::A_PIECE + o) = p[q];
+    for (int q = 0; q < 3; ++q) *reinterpret_cast<uint4*>(At + q * T::A_PIECE + o) = p[q];
   }
   if (PRE) return;
 #pragma unroll
   for (int h = 0; h < TN / 32; ++h) {
     uint2 p[3];
-    split2<AGAIN>(lead, fb[h].x, fb[h].y, p[0].x, p[1].x, p[2].x);
-    split2<AGAIN>(lead, fb[h].z, fb[h].w, p[0].y, p[1].y, p[2].y);
+    split2(fb[h].x, fb[h].y, p[0].x, p[1].x, p[2].x);
+    split2(fb[h].z, fb[h].w, p[0].y, p[1].y, p[2].y);
     const int o = (tid / (TN / 4) + (1024 / TN) * h) * km_pitch(TN) + ((tid % (TN / 4)) << 3);
 #pragma unroll
-    for (int q = 0; q < 3; ++q) *reinterpret_cast<uint2*>(lds + 3 * T::A_PIECE + q * T::B_PIECE + o) = p[q];
+    for (int q = 0; q < 3; ++q) *reinterpret_cast<uint2*>(Bt + q * T::B_PIECE + o) = p[q];
   }
 }
 
-// The K loop: acc = the tile's products (lead: only those of the first pieces).
-template <int TM, int TN, bool TAP1, bool AGAIN, bool PRE>
-__device__ __forceinline__ void split_mainloop(const ConvProb& P, int m0, int n0, bool lead, char* lds,
+// The K loop: acc = the tile's products.  Ends after the first slice where
+// that has an infinity or NaN in some wave's last rows, as it does all over for
+// a network that has diverged: the caller multiplies such a tile by fp32 MFMAs.
+template <int TM, int TN, bool TAP1, bool PRE>
+__device__ __forceinline__ void split_products(const ConvProb& P, int m0, int n0, char* At, char* Bt,
                                                v16f (&acc)[TM / 64][TN / 64]) {
   using T = SplitTile<TM, TN>;
-  const char* At = lds;
-  const char* Bt = lds + 3 * T::A_PIECE;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int wm = (wave >> 1) * (TM / 2), wn = (wave & 1) * (TN / 2);
   SplitCtx<TM, TN, TAP1> X;
   split_setup<TM, TN, TAP1, PRE>(P, m0, n0, X);
-  v16f low[T::TI][T::TJ];  // the five smaller piece products (AGAIN: no registers for their own sums)
+  v16f low[T::TI][T::TJ];  // the five smaller piece products
 #pragma unroll
   for (int i = 0; i < T::TI; ++i)
 #pragma unroll
@@ -208,24 +218,35 @@ __device__ __forceinline__ void split_mainloop(const ConvProb& P, int m0, int n0
   int kw = 0;
   auto products = [&](const v8bf (&a)[T::TI][3], const v8bf (&b)[T::TJ][3]) {
 #pragma unroll
-    for (int s = 2; s >= 0; --s) {
-      if (AGAIN && lead && s) continue;
+    for (int s = 2; s >= 0; --s)
 #pragma unroll
       for (int q = 0; q <= s; ++q)
 #pragma unroll
         for (int i = 0; i < T::TI; ++i)
 #pragma unroll
           for (int j = 0; j < T::TJ; ++j) {
-            v16f& to = s && !AGAIN ? low[i][j] : acc[i][j];
+            v16f& to = s ? low[i][j] : acc[i][j];
             to = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i][q], b[j][s - q], to, 0, 0, 0);
           }
-    }
   };
   auto a_frags = [&](int kk, v8bf (&a)[T::TI][3]) {
 #pragma unroll
     for (int q = 0; q < 3; ++q)
 #pragma unroll
       for (int i = 0; i < T::TI; ++i) a[i][q] = rk_frag(At + q * T::A_PIECE, wm + 32 * i, kk, lane);
+  };
+  // Every wave has read the previous slice; true: no further slice.
+  auto enough = [&](int k0) {
+    if (k0 != SK_DEEP) {
+      __syncthreads();
+      return false;
+    }
+    bool bad = false;
+#pragma unroll
+    for (int i = 0; i < T::TI; ++i)
+#pragma unroll
+      for (int j = 0; j < T::TJ; ++j) bad |= non_finite(acc[i][j][15]);
+    return __syncthreads_or(bad) != 0;
   };
   if (PRE) {
     // split weights: fragments as they are used, straight from memory, half a
@@ -242,8 +263,8 @@ __device__ __forceinline__ void split_mainloop(const ConvProb& P, int m0, int n0
     split_load<TM, TN, TAP1, PRE>(P, X, 0, fa, fb, kw);
     b_frags(kw, b0);
     for (int k0 = 0; k0 < P.K; k0 += SK_DEEP) {
-      __syncthreads();  // every wave has read the previous slice
-      split_store<TM, TN, AGAIN, PRE>(lead, fa, fb, lds);
+      if (enough(k0)) break;
+      split_store<TM, TN, PRE>(fa, fb, At, Bt);
       b_frags(kw + 16, b1);
       if (k0 + SK_DEEP < P.K) split_load<TM, TN, TAP1, PRE>(P, X, k0 + SK_DEEP, fa, fb, kw);
       __syncthreads();
@@ -254,12 +275,11 @@ __device__ __forceinline__ void split_mainloop(const ConvProb& P, int m0, int n0
       products(a, b1);
     }
   } else {
-    if (!AGAIN) split_load<TM, TN, TAP1, PRE>(P, X, 0, fa, fb, kw);
+    split_load<TM, TN, TAP1, PRE>(P, X, 0, fa, fb, kw);
     for (int k0 = 0; k0 < P.K; k0 += SK_DEEP) {
-      if (AGAIN) split_load<TM, TN, TAP1, PRE>(P, X, k0, fa, fb, kw);  // no registers for a slice in flight
-      __syncthreads();  // every wave has read the previous slice
-      split_store<TM, TN, AGAIN, PRE>(lead, fa, fb, lds);
-      if (!AGAIN && k0 + SK_DEEP < P.K) split_load<TM, TN, TAP1, PRE>(P, X, k0 + SK_DEEP, fa, fb, kw);
+      if (enough(k0)) break;
+      split_store<TM, TN, PRE>(fa, fb, At, Bt);
+      if (k0 + SK_DEEP < P.K) split_load<TM, TN, TAP1, PRE>(P, X, k0 + SK_DEEP, fa, fb, kw);
       __syncthreads();
 #pragma unroll
       for (int kk = 0; kk < 2; ++kk) {
@@ -273,50 +293,38 @@ __device__ __forceinline__ void split_mainloop(const ConvProb& P, int m0, int n0
       }
     }
   }
-  if (!AGAIN) {
 #pragma unroll
-    for (int i = 0; i < T::TI; ++i)
+  for (int i = 0; i < T::TI; ++i)
 #pragma unroll
-      for (int j = 0; j < T::TJ; ++j)
+    for (int j = 0; j < T::TJ; ++j)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[i][j][r] += low[i][j][r];
-  }
+      for (int r = 0; r < 16; ++r) acc[i][j][r] += low[i][j][r];
 }
 
-// Stores of the wave's 32-row strips.  Register r of lane l of a 32 x 32 MFMA
-// tile is row 8 (r / 4) + 4 (l / 32) + r % 4, column l % 32.
-template <int TM, int TN>
-__device__ __forceinline__ void split_strip(const ConvProb& P, const v16f (&acc)[TN / 64], int i, int m0, int n0,
-                                            float slope, bool rewrite, char* lds) {
-  constexpr int W = TN / 2, PITCH = W + 4;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  float* st = reinterpret_cast<float*>(lds) + wave * 32 * PITCH;
-  // the wave's own part of LDS: the previous strip's reads are issued before
-  // these writes, and LDS runs a wave's accesses in order
-  __builtin_amdgcn_wave_barrier();
-#pragma unroll
-  for (int j = 0; j < TN / 64; ++j)
-#pragma unroll
-    for (int r = 0; r < 16; ++r)
-      st[(8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)) * PITCH + 32 * j + (lane & 31)] = acc[j][r];
-  __builtin_amdgcn_wave_barrier();
-  const int m = m0 + (wave >> 1) * (TM / 2) + 32 * i, n = n0 + (wave & 1) * W;
-  if (rewrite) store_strip<32, W, CONV_FWD, true>(P, m, n, 0, slope, st);
-  else store_strip<32, W, CONV_FWD, false>(P, m, n, 0, slope, st);
-}
+// The lane's index in its wave; no register holds it over the K loop.
+__device__ __forceinline__ int lane_id() { return __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)); }
 
-template <int TM, int TN>
-__device__ __forceinline__ void split_write(const ConvProb P, const v16f (&acc)[TM / 64][TN / 64], int m0, int n0,
-                                            float slope, bool rewrite, char* lds) {
-  split_strip<TM, TN>(P, acc[0], 0, m0, n0, slope, rewrite, lds);
-  if (TM > 64) split_strip<TM, TN>(P, acc[TM / 64 - 1], 1, m0, n0, slope, rewrite, lds);
+// The descriptor, read again, into scalar registers: kept in them over the K
+// loop, it would spill.
+__device__ __forceinline__ ConvProb read_again(const ConvProb* p) {
+  typedef const __attribute__((address_space(4))) uint32_t* Words;
+  static_assert(sizeof(ConvProb) % 4 == 0, "whole words");
+  struct {
+    uint32_t w[sizeof(ConvProb) / 4];
+  } v;
+  uintptr_t a = (uintptr_t)p;
+  asm volatile("" : "+s"(a));
+#pragma unroll
+  for (size_t i = 0; i < sizeof(ConvProb) / 4; ++i) v.w[i] = ((Words)a)[i];
+  return __builtin_bit_cast(ConvProb, v);
 }
 
 template <int TM, int TN, bool TAP1, bool PRE>
 __global__ __launch_bounds__(NT, 2) void conv_split_kernel(const ConvProb* __restrict__ probs, ConvGroups grp,
                                                            float slope) {
   using T = SplitTile<TM, TN>;
-  __shared__ __align__(16) char lds[T::LDS];
+  __shared__ __align__(16) float lds0[T::LDS0 / 4];
+  __shared__ __align__(16) float lds1[T::LDS1 / 4];
   const int b = blockIdx.x;
   int gi = 0;
 #pragma unroll
@@ -329,8 +337,9 @@ __global__ __launch_bounds__(NT, 2) void conv_split_kernel(const ConvProb* __res
   const int lt = rel % grp.tiles_per_prob[gi];
   const ConvProb P = probs[pi];
   const int m0 = (lt / P.tiles_n) * TM, n0 = (lt % P.tiles_n) * TN;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   v16f acc[T::TI][T::TJ];
-  split_mainloop<TM, TN, TAP1, false, PRE>(P, m0, n0, false, lds, acc);
+  split_products<TM, TN, TAP1, PRE>(P, m0, n0, reinterpret_cast<char*>(lds0), reinterpret_cast<char*>(lds1), acc);
   bool bad = false;
 #pragma unroll
   for (int i = 0; i < T::TI; ++i)
@@ -338,21 +347,17 @@ __global__ __launch_bounds__(NT, 2) void conv_split_kernel(const ConvProb* __res
     for (int j = 0; j < T::TJ; ++j)
 #pragma unroll
       for (int r = 0; r < 16; ++r) bad |= non_finite(acc[i][j][r]);
-  // the descriptor is read again: kept in scalar registers over the K loop, it
-  // would spill
-  const ConvProb* again = probs + pi;
-  asm volatile("" : "+s"(again));
   if (__builtin_expect(__syncthreads_or(bad) == 0, 1)) {
-    split_write<TM, TN>(*again, acc, m0, n0, slope, false, lds);
+    wide_write<TM, TN, CONV_FWD>(read_again(probs + pi), acc, m0, n0, 0, slope, wave, lane_id(), lds0);
     return;
   }
 #pragma unroll 1
-  for (int lead = 0; lead < 2; ++lead) {
-    asm volatile("" : "+s"(again));
+  for (int q = 0; q < TM / 64 * (TN / 64); ++q) {
+    const ConvProb A = read_again(probs + pi);
+    const int m = m0 + q / (TN / 64) * 64, n = n0 + q % (TN / 64) * 64;
+    if (m >= A.M || n >= A.N) continue;
+    wide_tile<64, 64, CONV_FWD, 0, TAP1>(A, m, n, 0, 0, A.K, slope, wave, lds0, lds1);
     __syncthreads();
-    split_mainloop<TM, TN, TAP1, true, false>(*again, m0, n0, lead != 0, lds, acc);
-    __syncthreads();
-    split_write<TM, TN>(*again, acc, m0, n0, slope, lead != 0, lds);
   }
 }
 
@@ -376,8 +381,8 @@ __global__ __launch_bounds__(NT) void split_weights_kernel(const SplitWProb* __r
     // column r, k rows q .. q + 3 of the tile: lane r + 32 ((q / 8) % 2) of k
     // block q / 16, half of its 16 bytes
     uint2 p[3];
-    split2<false>(false, t[q][r], t[q + 1][r], p[0].x, p[1].x, p[2].x);
-    split2<false>(false, t[q + 2][r], t[q + 3][r], p[0].y, p[1].y, p[2].y);
+    split2(t[q][r], t[q + 1][r], p[0].x, p[1].x, p[2].x);
+    split2(t[q + 2][r], t[q + 3][r], p[0].y, p[1].y, p[2].y);
     char* o = reinterpret_cast<char*>(P.out) + ((size_t)nb * (P.K / 16) + k0 / 16 + (q >> 4)) * 3072 +
               (r + 32 * ((q >> 3) & 1)) * 16 + (q & 4) * 2;
 #pragma unroll

@@ -112,13 +112,11 @@ __device__ __forceinline__ void advance(const ConvProb& P, KPos& q, int dt, int 
 // Stores of a strip of ROWS rows of a wave's part of the tile, from the wave's
 // own part of LDS (rows of W + 4 floats), where the caller put its sums: as
 // float4, whole rows of the strip per instruction.  The wave takes rows
-// m0 .. m0 + ROWS - 1, columns n0 .. n0 + W - 1.  REWRITE: only the elements
-// whose sum is not finite.
-template <int ROWS, int W, int MODE, bool REWRITE>
-__device__ __forceinline__ void store_strip(const ConvProb& P, int m0, int n0, int split, float slope, const float* st) {
+// m0 .. m0 + ROWS - 1, columns n0 .. n0 + W - 1.
+template <int ROWS, int W, int MODE>
+__device__ __forceinline__ void store_strip(const ConvProb& P, int m0, int n0, int split, float slope, int lane, const float* st) {
   constexpr int PITCH = W + 4;
   constexpr int RQ = 64 / (W / 4);                    // rows one float4 pass of the wave covers
-  const int lane = threadIdx.x & 63;
   const int c4 = (lane % (W / 4)) * 4, rq = lane / (W / 4);
   const int n = n0 + c4;
   LIPZ_GLOBAL float* gC = as_global(P.C);
@@ -136,17 +134,16 @@ __device__ __forceinline__ void store_strip(const ConvProb& P, int m0, int n0, i
   for (int q = 0; q < ROWS / RQ; ++q) {
     const int row = m0 + RQ * q + rq;
     float4 v = *reinterpret_cast<const float4*>(st + (RQ * q + rq) * PITCH + c4);
-    const float4 raw = v;
     if (MODE == CONV_WG) {
       if (row < P.taps * P.cs && n < P.N) {
         int t, c;
         split_k(P, row, t, c);
         LIPZ_GLOBAL float* o = gC + (int64_t)(tap_of(P, t).wt * P.cs + c) * P.ldc;
-        if (P.n_inner || REWRITE) {
-          if (!REWRITE || non_finite(raw.x)) o[coff[0]] = v.x;
-          if (!REWRITE || non_finite(raw.y)) o[coff[1]] = v.y;
-          if (!REWRITE || non_finite(raw.z)) o[coff[2]] = v.z;
-          if (!REWRITE || non_finite(raw.w)) o[coff[3]] = v.w;
+        if (P.n_inner) {
+          o[coff[0]] = v.x;
+          o[coff[1]] = v.y;
+          o[coff[2]] = v.z;
+          o[coff[3]] = v.w;
         } else {
           *reinterpret_cast<LIPZ_GLOBAL v4f*>(o + n) = v4f{v.x, v.y, v.z, v.w};
         }
@@ -161,14 +158,7 @@ __device__ __forceinline__ void store_strip(const ConvProb& P, int m0, int n0, i
         v = make_float4(v.x * act_deriv_from_out(P.act, x[0], slope), v.y * act_deriv_from_out(P.act, x[1], slope),
                         v.z * act_deriv_from_out(P.act, x[2], slope), v.w * act_deriv_from_out(P.act, x[3], slope));
       }
-      if (REWRITE) {
-        if (non_finite(raw.x)) gC[o] = v.x;
-        if (non_finite(raw.y)) gC[o + 1] = v.y;
-        if (non_finite(raw.z)) gC[o + 2] = v.z;
-        if (non_finite(raw.w)) gC[o + 3] = v.w;
-      } else {
-        *reinterpret_cast<LIPZ_GLOBAL v4f*>(gC + o) = v4f{v.x, v.y, v.z, v.w};
-      }
+      *reinterpret_cast<LIPZ_GLOBAL v4f*>(gC + o) = v4f{v.x, v.y, v.z, v.w};
     }
   }
 }

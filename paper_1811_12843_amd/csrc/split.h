@@ -18,10 +18,10 @@
 // 5.8e-7, mean error 1e-9; six products into one accumulator 4.9e-7, -5.6e-8;
 // two accumulators 1.9e-7, -1e-9.
 //
-// A non-finite operand, and a finite one that rounds to bf16's infinity
-// (above 3.39e38), give non-finite pieces and NaN sums where fp32 products may
-// give an infinity or a number.  Kernels test their accumulators; a tile with
-// a non-finite one is multiplied again.
+// A non-finite operand, and a finite one that rounds to bf16's infinity, give
+// non-finite pieces and NaN sums where fp32 products may give an infinity or a
+// number.  Kernels test their accumulators; a tile with a non-finite one is
+// multiplied again, by fp32 MFMAs.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -38,32 +38,12 @@ __device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
   return __builtin_bit_cast(uint32_t, __builtin_convertvector((v2f{a, b}), v2bf));
 }
 
-// Their splits of a tile that is multiplied again (AGAIN): the first piece is
-// cut off instead of rounded, so that finite values have finite pieces, and
-// either non-finite values are left out and the sums are as above, or (lead)
-// only the first pieces are multiplied, which have the operands' infinities,
-// NaNs, zeros and signs: where such a sum is not finite it replaces the other.
 // True when v is an infinity or NaN (also under finite-math assumptions).
 __device__ __forceinline__ bool non_finite(float v) { return (__float_as_uint(v) & 0x7F800000u) == 0x7F800000u; }
 
-// The upper halves of two values, a's in the low half: bf16 by truncation.  A
-// NaN whose upper mantissa bits are zero would become an infinity: its quiet
-// bit is set.
-__device__ __forceinline__ uint32_t upper2(float a, float b) {
-  uint32_t ua = __float_as_uint(a), ub = __float_as_uint(b);
-  if ((ua & 0x7FFFFFFFu) > 0x7F800000u) ua |= 0x400000u;
-  if ((ub & 0x7FFFFFFFu) > 0x7F800000u) ub |= 0x400000u;
-  return (ua >> 16) | (ub & 0xFFFF0000u);
-}
-
 // The three pieces of two values, packed.
-template <bool AGAIN>
-__device__ __forceinline__ void split2(bool lead, float a, float b, uint32_t& p0, uint32_t& p1, uint32_t& p2) {
-  if (AGAIN && !lead) {
-    if (non_finite(a)) a = 0.f;
-    if (non_finite(b)) b = 0.f;
-  }
-  p0 = AGAIN ? upper2(a, b) : pack_bf16(a, b);
+__device__ __forceinline__ void split2(float a, float b, uint32_t& p0, uint32_t& p1, uint32_t& p2) {
+  p0 = pack_bf16(a, b);
   const float a1 = a - __uint_as_float(p0 << 16), b1 = b - __uint_as_float(p0 & 0xFFFF0000u);
   p1 = pack_bf16(a1, b1);
   p2 = pack_bf16(a1 - __uint_as_float(p1 << 16), b1 - __uint_as_float(p1 & 0xFFFF0000u));

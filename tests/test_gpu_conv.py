@@ -154,3 +154,43 @@ def test_split_kernel_keeps_infinities_and_nans(kind, shape):
         assert torch.equal(torch.isinf(got), inf), tile
         assert torch.equal(got[inf], base[inf]), tile
         assert torch.all((got[fin].double() - base[fin].double()).abs() <= bound[fin]), tile
+
+
+@pytest.mark.parametrize("kind", ["conv", "convT"])
+@pytest.mark.parametrize("shape", [(1, 3, 32, 64), (1, 3, 36, 20), (4, 3, 64, 128), (3, 4, 32, 132), (1, 2, 8, 64)])
+@pytest.mark.parametrize("plant", ["one", "huge", "weights"])
+def test_split_tiles_with_a_non_finite_sum_keep_fp32_precision(kind, shape, plant):
+    """A tile with an infinite or NaN sum has the fp32 kernel's sums bit for bit, its finite ones too; the others are
+    as without the planted values.  (Tiles whole and cut, one slice and many, and networks that are NaN all over.)"""
+    n, h, ci, co = shape
+    x, w, bias, aux = _problem(kind, shape, seed=11)
+    clean = _run(kind, shape, PRE if ci % 32 == 0 else SPLIT, (64, 64), x, w, bias, aux)
+    if plant == "weights":
+        w[:] = float("nan")
+    else:
+        x[0, x.shape[1] // 2, x.shape[2] // 2, ci // 3] = float("inf") if plant == "one" else 3.395e38
+    base = _run(kind, shape, ANY, (0, 0), x, w, bias, aux)
+    assert plant == "huge" or not torch.isfinite(base).all()
+    for kernel in [SPLIT] + ([PRE] if ci % 32 == 0 else []):
+        for tile in TILES:
+            print(f"[case] again {kind} {shape} {plant} kernel {kernel} tile {tile}", flush=True)
+            got = _run(kind, shape, kernel, tile, x, w, bias, aux)
+            same = (got.view(torch.int32) == base.view(torch.int32)) | (torch.isnan(got) & torch.isnan(base))
+            # outputs are rows of positions (of a parity class each, for the transposed kind) in tiles of tile[0] rows
+            g = x.shape[1] >> 1 if kind == "conv" else x.shape[1]
+            q = torch.arange(n * g * g).view(n, g, g)
+            if kind == "convT":
+                q = torch.stack([torch.stack([q + (2 * r + s) * 65536 for s in (0, 1)], -1) for r in (0, 1)], 2).reshape(
+                    n, 2 * g, 2 * g)
+            row = (q // 65536 * 65536 + q % 65536 // tile[0]).reshape(-1)
+            col = torch.arange(co) // tile[1]
+            f, s, u = got.reshape(-1, co), same.reshape(-1, co), clean.reshape(-1, co)
+            redone = 0
+            for r in row.unique():
+                for c in col.unique():
+                    at = (row == r)[:, None] & (col == c)[None]
+                    if not s[at].all():
+                        assert torch.equal(f[at], u[at]), (kernel, tile, int(r), int(c))
+                    else:
+                        redone += 1
+            assert redone > 0
