@@ -298,7 +298,7 @@ __device__ __forceinline__ void split_products(const ConvProb& P, int m0, int n0
 #pragma unroll
     for (int j = 0; j < T::TJ; ++j)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] += low[i][j][r];
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = (acc[i][j][r] + low[i][j][r]) * SPLIT_UNSCALE;
 }
 
 // The lane's index in its wave; no register holds it over the K loop.

@@ -2,26 +2,31 @@
 //
 // An fp32 value is the sum of three bf16 values, x = x0 + x1 + x2: x0 is x
 // rounded to nearest, x1 the remainder rounded to nearest, x2 what is left,
-// which fits bf16's 8 significand bits (|x1| <= 2^-9 |x|, |x2| <= 2^-18 |x|;
-// bf16 has fp32's exponent range, so pieces lose bits only below 2^-126).
+// which fits bf16's 8 significand bits (|x1| <= 2^-8 |x|, |x2| <= 2^-17 |x|).
 // A product is the six piece products x_i y_j with i + j <= 2, each exact in
-// fp32, summed into fp32 accumulators; the three left out are together
-// below 2^-25 |x y|, half an fp32 rounding.  Six bf16 MFMAs take 6/16 of the
-// matrix-core time of the fp32 MFMAs for the same product.
+// fp32, summed into fp32 accumulators; the three left out are together at most
+// (2^-24 + 2^-34) |x y|, what rounding the product to fp32 may take.  Six bf16
+// MFMAs take 6/16 of the matrix-core time of the fp32 MFMAs for the same product.
+//
+// Operands are scaled by 2^16 before they are split, and sums by 2^-32: bf16's
+// smallest subnormal is 2^-133, so a scaled operand's pieces hold all its bits
+// down to fp32's smallest subnormal (unscaled, those of |x| < 2^-110 do not: with
+// operands of 2^-120 the results' rms error was 3.5e-5).  Operands and sums too
+// large for the scale come out as non-finite ones do.
 //
 // x0 y0 has accumulators of its own, added to those of the five smaller
 // products at the end: a bf16 MFMA drops product bits below its accumulator's
-// last place, towards minus infinity, and one accumulator for all six loses
-// the small products' bits with a bias that sums over many outputs (bias
-// gradients) show.  Measured, one wave's 32 x 32 tiles of normal data, K =
+// last place, towards minus infinity, and in one accumulator for all six that
+// is a bias on every sum.  Measured, one wave's 32 x 32 tiles of normal data, K =
 // 1024, against fp64, relative to the rms result: fp32 MFMAs rms error
 // 5.8e-7, mean error 1e-9; six products into one accumulator 4.9e-7, -5.6e-8;
-// two accumulators 1.9e-7, -1e-9.
+// two accumulators 1.9e-7, -1e-9.  On sums of one sign, K = 16384, rms and mean
+// of fp32 MFMAs 1.7e-6 and 8e-8, of two accumulators 6.0e-7 and -6e-8.
 //
-// A non-finite operand, and a finite one that rounds to bf16's infinity, give
-// non-finite pieces and NaN sums where fp32 products may give an infinity or a
-// number.  Kernels test their accumulators; a tile with a non-finite one is
-// multiplied again, by fp32 MFMAs.
+// A non-finite operand, and a finite one that the scale or the rounding takes
+// past bf16's largest value, give non-finite pieces and NaN sums where fp32
+// products may give an infinity or a number.  Kernels test their accumulators;
+// a tile with a non-finite one is multiplied again, by fp32 MFMAs.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -41,8 +46,12 @@ __device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
 // True when v is an infinity or NaN (also under finite-math assumptions).
 __device__ __forceinline__ bool non_finite(float v) { return (__float_as_uint(v) & 0x7F800000u) == 0x7F800000u; }
 
-// The three pieces of two values, packed.
+constexpr float SPLIT_SCALE = 0x1p16f, SPLIT_UNSCALE = 0x1p-32f;
+
+// The three pieces of two scaled values, packed.
 __device__ __forceinline__ void split2(float a, float b, uint32_t& p0, uint32_t& p1, uint32_t& p2) {
+  a *= SPLIT_SCALE;
+  b *= SPLIT_SCALE;
   p0 = pack_bf16(a, b);
   const float a1 = a - __uint_as_float(p0 << 16), b1 = b - __uint_as_float(p0 & 0xFFFF0000u);
   p1 = pack_bf16(a1, b1);

@@ -194,3 +194,23 @@ def test_split_tiles_with_a_non_finite_sum_keep_fp32_precision(kind, shape, plan
                     else:
                         redone += 1
             assert redone > 0
+
+
+@pytest.mark.parametrize("kind", ["conv", "convT"])
+@pytest.mark.parametrize("ex,ew", [(-112, 0), (0, -118), (-122, 40), (40, -126), (-130, 30), (-60, -60)])
+def test_split_kernel_on_tiny_operands(kind, ex, ew):
+    """Operands whose bf16 pieces would be subnormal, and subnormal operands: against fp64, no further off than fp32
+    products are (root mean square; the split's is about a third of theirs)."""
+    shape = (8, 3, 32, 64)
+    x, w, bias, aux = _problem(kind, shape, seed=5)
+    x, w, bias = torch.ldexp(x, torch.tensor(ex)), torch.ldexp(w, torch.tensor(ew)), torch.zeros_like(bias)
+    ref = _reference(kind, x.double(), w.double(), aux.double(), bias.double())[0]
+
+    def rms(kernel, tile):
+        got = _run(kind, shape, kernel, tile, x, w, bias, aux)
+        return float((got.double() - ref).pow(2).mean().sqrt() / ref.pow(2).mean().sqrt())
+
+    base = rms(ANY, (0, 0))
+    for kernel in (SPLIT, PRE):
+        print(f"[case] tiny {kind} 2^{ex} 2^{ew} kernel {kernel}", flush=True)
+        assert rms(kernel, (64, 64)) <= base
