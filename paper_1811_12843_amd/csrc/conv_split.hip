@@ -79,7 +79,12 @@ __device__ __forceinline__ void split_setup(const ConvProb& P, int m0, int n0, S
     X.rp = rsrc(reinterpret_cast<const float*>(P.Wp), (uint32_t)((P.N + 31) / 32) * (uint32_t)(P.wp_k * 192));
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 #pragma unroll
-    for (int j = 0; j < TN / 64; ++j) X.pb[j] = ((n0 + (wave & 1) * (TN / 2)) / 32 + j) * (P.wp_k * 192);
+    for (int j = 0; j < TN / 64; ++j) {
+      // a block past N repeats the last one, for columns that are not stored: the extent of
+      // a resource does not bound a scalar offset past it
+      const int blk = min((n0 + (wave & 1) * (TN / 2)) / 32 + j, (P.N + 31) / 32 - 1);
+      X.pb[j] = blk * (P.wp_k * 192);
+    }
   } else {
     X.rb = rsrc(P.W, P.w_bytes);
   }

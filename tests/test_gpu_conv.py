@@ -79,7 +79,7 @@ def _problem(kind, shape, seed):
     return t[x[kind]], t[w.get(kind, "w")], t["bias"], t["aux"]
 
 
-def _run(kind, shape, kernel, tile, x, w, bias, aux):
+def _run(kind, shape, kernel, tile, x, w, bias, aux, pieces_tail=0):
     n, h, ci, co = shape
     K = KINDS.index(kind)
     splits = -(-(n << (2 * (h - 1 if kind == "conv_wgrad" else h))) // 1024)
@@ -87,7 +87,7 @@ def _run(kind, shape, kernel, tile, x, w, bias, aux):
             "convT_dgrad": (n, 1 << h, 1 << h, ci), "conv_wgrad": (splits, 16 * ci + 1, co),
             "convT_wgrad": (splits, 16 * ci, co)}[kind]
     if kernel == PRE:
-        aux = torch.full((24 * ci * -(-co // 32) * 32,), float("nan"))  # the weights' pieces
+        aux = torch.full((24 * ci * (-(-co // 32) + pieces_tail) * 32,), float("nan"))  # the weights' pieces
     dx, dw, db, da = (t.cuda().contiguous() for t in (x, w, bias, aux))
     out = torch.full(size, float("nan"), device="cuda")
     desc = torch.zeros(2048, dtype=torch.uint8, device="cuda")
@@ -214,3 +214,15 @@ def test_split_kernel_on_tiny_operands(kind, ex, ew):
     for kernel in (SPLIT, PRE):
         print(f"[case] tiny {kind} 2^{ex} 2^{ew} kernel {kernel}", flush=True)
         assert rms(kernel, (64, 64)) <= base
+
+
+@pytest.mark.parametrize("kind", ["conv", "convT"])
+@pytest.mark.parametrize("shape", [(3, 3, 32, 20), (3, 3, 32, 96), (1, 3, 64, 132)])
+def test_split_weights_are_read_within_their_extent(kind, shape):
+    """Columns of a tile past the last whole block of weights: NaNs behind the weights' pieces (a tile's whole width of
+    them) never reach a sum, which would send its tile to fp32 and change its bits."""
+    x, w, bias, aux = _problem(kind, shape, seed=17)
+    for tile in TILES:
+        print(f"[case] extent {kind} {shape} tile {tile}", flush=True)
+        got = _run(kind, shape, PRE, tile, x, w, bias, aux, pieces_tail=4)
+        assert torch.equal(got, _run(kind, shape, SPLIT, tile, x, w, bias, aux)), tile
