@@ -383,7 +383,11 @@ int add_phase(lipz_grid* g, const std::vector<GemmProb>& ps) {
   for (const GemmProb& p : ps) tiles64 += ceil_div(p.M, 64) * ceil_div(p.N, GEMM_BN);
   ph.tile_rows = gemm_tile_rows(tiles64);
   int max_k = 0;
-  for (const GemmProb& p : ps) max_k = p.K > max_k ? p.K : max_k;
+  bool b_trans = false;
+  for (const GemmProb& p : ps) {
+    max_k = p.K > max_k ? p.K : max_k;
+    b_trans = b_trans || p.b_trans;
+  }
   int tiles = 0;
   memset(&ph.grp, 0, sizeof(ph.grp));
   int prev_tpp = -1, prev_k = -1;
@@ -426,7 +430,7 @@ int add_phase(lipz_grid* g, const std::vector<GemmProb>& ps) {
     g->probs_h.push_back(p);
   }
   ph.tiles = tiles;
-  ph.kernel = gemm_choose_kernel(ph.fast, max_k, ph.tiles, ph.tile_rows);
+  ph.kernel = gemm_choose_kernel(ph.fast, b_trans, max_k, ph.tiles, ph.tile_rows);
   if (!ph.fast || ph.kernel != GEMM_K_CHAIN)
     for (size_t k = ph.first; k < g->probs_h.size(); ++k) g->probs_h[k].vec |= GEMM_ADAM_OLD_FIRST;
   g->phases.push_back(ph);

@@ -75,6 +75,15 @@ namespace {
 // K = 784 take 20.3 us there and 21.1 on the other, 672 take 27.8 and 21.7)
 #define LIPZ_GEMM_WAVE_MAX_TILES 512
 #endif
+#ifndef LIPZ_GEMM_WAVE_MIN_K
+// ... and from this depth on at any number of tiles, where no problem reads B
+// transposed: one product of 256 columns, K = 4096, 520 to 4096 tiles: 0.94 -
+// 0.96 of the other kernel's time, 8960 tiles 1.00; of 2048 columns, 4096 to
+// 32768 tiles 0.94 - 0.97; K = 8192 0.92 - 0.98.  At K = 2048 the two are even
+// (0.97 - 1.11), at K = 784 it takes 1.05 - 1.15, and with B transposed 1.2 - 1.4
+// at every depth (its columns are rows there, K apart).
+#define LIPZ_GEMM_WAVE_MIN_K 4096
+#endif
 
 constexpr int BN = GEMM_BN;
 constexpr int BK = 32;        // K depth of an LDS stage
@@ -1193,9 +1202,10 @@ hipError_t launch_gemm_grouped(const GemmProb* d_probs, const GemmGroups& grp, i
   return hipGetLastError();
 }
 
-int gemm_choose_kernel(bool aligned, int max_k, int tiles, int tile_rows) {
+int gemm_choose_kernel(bool aligned, bool b_trans, int max_k, int tiles, int tile_rows) {
   if (!aligned || max_k < LIPZ_GEMM_CHAINS4_MIN_K) return GEMM_K_CHAIN;
-  return tile_rows == 32 && tiles <= LIPZ_GEMM_WAVE_MAX_TILES ? GEMM_K_WAVE : GEMM_K_CHAINS4;
+  const bool wave = tiles <= LIPZ_GEMM_WAVE_MAX_TILES || (max_k >= LIPZ_GEMM_WAVE_MIN_K && !b_trans);
+  return tile_rows == 32 && wave ? GEMM_K_WAVE : GEMM_K_CHAINS4;
 }
 
 }  // namespace lipz

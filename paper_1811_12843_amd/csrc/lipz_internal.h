@@ -282,8 +282,8 @@ enum GemmKernel : int32_t {
   GEMM_K_CHAINS4 = 3   // the same four chains in every wave
 };
 // The variant a phase runs on: whether its problems' operands are all aligned
-// (gemm_fast_ok), its deepest K, and its tiles.
-int gemm_choose_kernel(bool aligned, int max_k, int tiles, int tile_rows);
+// (gemm_fast_ok), whether one has b_trans, its deepest K, and its tiles.
+int gemm_choose_kernel(bool aligned, bool b_trans, int max_k, int tiles, int tile_rows);
 
 // A training minibatch drawn by extra workgroups of a GEMM launch (the
 // draws of sample_kernel, written to other buffers than the launch's GEMMs

@@ -71,7 +71,7 @@ extern "C" lipz_status lipz_test_gemm(void* hip_stream, void* d_desc, int32_t M,
   // wave (aligned operands only); variant & 4: write-back stores (else
   // device-scope)
   const int kv = variant & 3;
-  int kernel = gemm_choose_kernel(gemm_fast_ok(p), K, tiles, tile_rows);
+  int kernel = gemm_choose_kernel(gemm_fast_ok(p), p.b_trans != 0, K, tiles, tile_rows);
   if (kv != 0) {
     if (!gemm_fast_ok(p)) return LIPZ_E_INVAL;
     kernel = kv == 1 ? GEMM_K_CHAIN : kv == 2 && tile_rows == 32 ? GEMM_K_WAVE : GEMM_K_CHAINS4;

@@ -68,6 +68,16 @@ def test_any_alignment_gives_the_same_sums(shape, trans):
                 assert np.array_equal(base.setdefault(chains, out), out), (tile_rows, pad, shift, v)
 
 
+@pytest.mark.parametrize("trans", [(0, 0), (0, 1), (1, 0)])
+def test_deep_products_take_four_chains_on_any_kernel(trans):
+    """Depths and tile counts on either side of the rule between the two four-chain kernels: the library's choice has
+    the bits of both."""
+    for M, N, K in ((64, 64, 4064), (64, 64, 4096), (1088, 1024, 4064), (1088, 1024, 4096)):
+        print(f"[case] deep {M} {N} {K} {trans}", flush=True)
+        out = [_run(M, N, K, *trans, 0, 0, 32, v, seed=K)[2] for v in (0, 2, 3)]
+        assert np.array_equal(out[0], out[1]) and np.array_equal(out[0], out[2])
+
+
 @pytest.mark.parametrize("outlier", [1e10, 1e-30, float("inf"), float("nan")])
 @pytest.mark.parametrize("rows,fi,fo", [(100, 64, 64), (37, 45, 70)])
 def test_adam_short_and_full_divisions_agree(rows, fi, fo, outlier):
