@@ -358,8 +358,8 @@ __device__ __forceinline__ void epi_load(const GemmProb& P, const EpiPos<BM>& E,
 // network of given sizes trains to the same bits whichever kernel runs it.
 //
 // Where it can, with the divisions and the square root without the scaling and special
-// cases of their IEEE sequences (a reciprocal refined once, the quotient
-// twice; a square root moved by an ulp where its residuals say so), for
+// cases of their IEEE sequences (LLVM's for this target: a reciprocal refined once, the
+// quotient twice; a square root moved by an ulp where its residuals say so), for
 // operands in the range where those do nothing: the same bits in 35 vector
 // instructions per element instead of 58 (a training step of 16 MNIST cells:
 // 191 us without, 188 with; of four 2-D cells 69 and 66).
@@ -378,17 +378,19 @@ __device__ __forceinline__ float root(float x) {
   const float r = fmaf(-lo, s, x) <= 0.f ? lo : s;
   return fmaf(-hi, s, x) > 0.f ? hi : r;
 }
-// v zero, or of magnitude 2^lo .. 2^hi: the smallest of bits - 1 (zeros wrap to
-// the largest) and the largest of bits.
+// +0, or of magnitude 2^lo .. 2^hi: of the bits with the sign moved to the low
+// end, the smallest of bits - 1 (+0 wraps to the largest, -0 is the smallest)
+// and the largest.  -0 stays with the full sequences: its short quotient is +0,
+// which takes the sign off a parameter of -0.
 struct Range {
   uint32_t lo = 0xFFFFFFFFu, hi = 0u;
   __device__ __forceinline__ void take(float v) {
-    const uint32_t b = __float_as_uint(v) & 0x7FFFFFFFu;
+    const uint32_t b = __builtin_rotateleft32(__float_as_uint(v), 1);
     lo = min(lo, b - 1u);
     hi = max(hi, b);
   }
   __device__ __forceinline__ bool inside(int lo_exp, int hi_exp) const {
-    return lo >= ((uint32_t)(127 + lo_exp) << 23) - 1u && hi <= ((uint32_t)(127 + hi_exp) << 23);
+    return lo >= ((uint32_t)(127 + lo_exp) << 24) - 1u && hi <= ((uint32_t)(127 + hi_exp) << 24) + 1u;
   }
 };
 
@@ -401,8 +403,11 @@ __device__ __forceinline__ void adam(const GemmProb& P, const v4f (&acc)[Tile<BM
   const __amdgpu_buffer_rsrc_t rV = make_rsrc(P.v, kWholeBuffer);
   const float lr = *as_global(P.lr);
   const float bc1 = bc[0], bc2 = bc[1];
-  // with these and m, v in the ranges below every quotient and every
-  // intermediate stays a normal number
+  // with these and m, v in the ranges below every quotient, root and reciprocal
+  // is a normal number (or 0), about 2^-120 at least.  The residuals need not be: of a
+  // numerator of 2^-100 they go down to 2^-147.  They are exact all the same,
+  // multiples of 2^-149, as long as subnormal numbers are kept (the target's
+  // default for fp32).
   const bool plain = lr >= 0x1p-20f && lr <= 1.f && bc1 >= 0x1p-20f && bc2 >= 0x1p-20f && ac.eps >= 0x1p-30f && ac.eps <= 1.f;
   const float y1 = refined_rcp(bc1), y2 = refined_rcp(bc2);
 #pragma unroll

@@ -115,3 +115,42 @@ def test_adam_short_and_full_divisions_agree(rows, fi, fo, outlier):
     for a, b in zip(*out):
         assert np.isfinite(a).all()
         assert np.array_equal(a[~at], b[~at])
+
+
+@pytest.mark.parametrize("ends", [False, True])
+def test_adam_has_the_bits_of_ieee_divisions(ends):
+    """Adam's step without a gradient against numpy's fp32 division and root, bit for bit: moments over the range of
+    the short sequences or at its ends (2^-80, 2^-100, 2^20), zeros of both signs, parameters of both zeros."""
+    g = np.random.default_rng(int(ends))
+    fi, fo, rows, f = 64, 64, 40, np.float32
+    shape = (fi + 1, fo)
+
+    def powers(lo, hi):
+        e = g.choice([lo, hi - 1], shape) if ends else g.integers(lo, hi, shape)
+        near = g.choice([0, 0, 1, 2, (1 << 23) - 1], shape) if ends else g.integers(0, 1 << 23, shape)
+        return np.ldexp(1.0 + near * 2.0 ** -23, e).astype(f)
+
+    m, v = powers(-80, 20) * g.choice([-1, 1], shape).astype(f), powers(-100, 20)
+    p = g.standard_normal(shape).astype(f) * (m * 0 + g.choice([1, 1e-30], shape).astype(f))
+    m[::7, ::3], v[::5, ::4], p[::3, ::5], p[1::3, ::5] = f(0.0), f(0.0), f(0.0), f(-0.0)
+    m0, v0 = m * f(2), v * f(2)  # halved exactly by beta = 0.5
+    below = np.zeros(shape, bool)
+    below[8:24, 32:] = g.random((16, 32)) < 0.3
+    p[8:24, 32:48] = f(-0.0)
+    m0[below], m[below] = f(-2.0 ** -149), f(-0.0)  # half the smallest subnormal rounds to -0
+    t = [torch.from_numpy(a.copy()).cuda() for a in (p, m0, v0)]
+    X, dY = torch.zeros(rows, fi, device="cuda"), torch.zeros(rows, fo, device="cuda")
+    lr, step = torch.tensor([3e-4], device="cuda"), torch.tensor([6], dtype=torch.int32, device="cuda")
+    desc = torch.zeros(256, dtype=torch.uint8, device="cuda")
+    print(f"[case] adam ieee ends {ends}", flush=True)
+    L.lipz_test_gemm(torch.cuda.current_stream().cuda_stream, desc.data_ptr(), fi + 1, fo, rows, X.data_ptr(), fi, 1, fi,
+                     dY.data_ptr(), fo, 0, t[0].data_ptr(), fo, 3, 0, 0.2, d_m=t[1].data_ptr(), d_v=t[2].data_ptr(),
+                     d_lr=lr.data_ptr(), d_t=step.data_ptr(), beta1=0.5, beta2=0.5, tile_rows=32)
+    torch.cuda.synchronize()
+    out = [a.cpu().numpy() for a in t]
+    bc = f(1.0 - 0.5 ** 7)
+    want = p - f(3e-4) * (m / bc) / (np.sqrt(v / bc) + f(1e-8))
+    assert want.dtype == f
+    bits = [a.view(np.int32) for a in (out[0], out[1], out[2], want, m, v)]
+    assert np.array_equal(bits[1], bits[4]) and np.array_equal(bits[2], bits[5])
+    assert np.array_equal(bits[0], bits[3])
