@@ -691,9 +691,9 @@ void build_tables(lipz_grid* g) {
       const int dgrad_phase = add_phase(g, ph);
       ops.push_back({OP_GEMM, dgrad_phase});
       if (g->hpart) {
-        // the output layer's weight gradient from the per-row-tile column
-        // sums: [w | b] = 1^T hpart over the launch's row tiles (a 1-row
-        // product whose A is the all-ones row), and its Adam step
+        // the output layer's weight gradient from the column sums of 32 rows
+        // each: [w | b] = 1^T hpart (a 1-row product whose A is the all-ones
+        // row), and its Adam step
         const int rt = ceil_div(2 * B, 32);
         head_grad.clear();
         for (int c = cb; c < ce; ++c) {
@@ -1007,7 +1007,7 @@ lipz_grid* plan_grid(const lipz_config* cfg, int64_t n_samples, char* base, cons
     g->fused_sample = LIPZ_FUSED_SAMPLE && cfg->trainer == LIPZ_TRAINER_GRADIENT;
     if (g->fused_head) g->aS_ld = (Dn.fi[Dn.nl - 2] + 4 + 3) / 4 * 4;
     if (g->fused_head && Dn.fi[Dn.nl - 1] <= Dn.fi[Dn.nl - 2]) {
-      g->hp_rows = (2 * g->B + 31) / 32;  // row tiles of the input-gradient launch (at most, 32-row tiles)
+      g->hp_rows = (2 * g->B + 31) / 32;  // pieces of 32 rows of the input-gradient launch
       g->hp_ld = (Dn.fi[Dn.nl - 1] + 1 + 3) / 4 * 4;
     }
   }
@@ -1978,7 +1978,7 @@ lipz_status lipz_test_plan_bounds(const lipz_config* cfg, int64_t n_samples, cha
       if (p.side && (p.side_ld < p.N + 4 || !inside(p.side, 0, (int64_t)(p.M - 1) * p.side_ld + p.N + 3) ||
                      !inside(p.dlout, 0, (int64_t)p.M * 4 - 1)))
         note("gemm head side outputs", i);
-      // row tile m0 / BM (BM >= 32) of the output layer's gradient pieces
+      // the output layer's gradient pieces, one per 32 rows
       if (p.rs_mode == 1 && p.hpart &&
           (p.hp_w < 1 || p.hp_w > p.N || p.hp_ld < p.hp_w + 1 ||
            !inside(p.hpart, 0, (int64_t)((p.M - 1) / 32) * p.hp_ld + p.hp_w) ||

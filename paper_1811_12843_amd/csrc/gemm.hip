@@ -39,18 +39,21 @@
 // derivative (input gradient); Adam on the weight gradient in registers.  What
 // an epilogue reads is requested before the main loop.
 //
-// What bounds it: on large phases the tiles' operand traffic out of L2 (a 32 x
-// 64 tile takes 96 floats per k for 2048 products: about 9 TB/s) with the
-// matrix cores 70 % busy; on phases of a tile or two per CU the launch and the
-// chain of a tile's slices; on weight gradients with Adam the 24 bytes per
-// parameter, and the vector instructions of its divisions.  Measured, against
+// What bounds it: on large phases the matrix cores are 70 % busy, while the
+// tiles' operands come out of L2 at about 9 TB/s (a 32 x 64 tile takes 96 floats
+// per k for 2048 products); which of the waits between holds them up is not
+// shown (64-row tiles move a third less and gain 4 - 8 %, on the largest
+// products only).  Phases of a tile or two per CU are bound by the launch and
+// the chain of a tile's slices; weight gradients with Adam by the 24 bytes per
+// parameter and the vector instructions of its divisions.  Measured, against
 // operands staged through registers and element-wise epilogues: 16 cells'
 // 784 -> 256 weight gradient with Adam (200 samples) and its neighbour 41.1 ->
 // 36.4 us; 32 cells' 81 -> 68; a forward of 600 rows, 256 -> 256, for 80
 // pairs 83.6 -> 77.4 us; and against element-wise loads of rows that are not
 // 16-byte aligned, six cells of 301 -> 203 -> 97 units: 1960 -> 1100 us for 10
-// steps.  64-row tiles were no faster on any phase measured (256 to 8960
-// tiles of 32 rows), four LDS stages neither.
+// steps.  64-row tiles were no faster on phases of 256 to 8960 tiles of 32
+// rows, four LDS stages neither.  Larger single products do run faster on them
+// (LIPZ_GEMM_TILE64_MIN).
 #include <string.h>
 
 #include <hip/hip_ext.h>
@@ -65,7 +68,12 @@ typedef float v16f __attribute__((ext_vector_type(16)));
 namespace {
 
 #ifndef LIPZ_GEMM_TILE64_MIN
-#define LIPZ_GEMM_TILE64_MIN 100000  // phases with at least this many 64x64 tiles use 64-row tiles
+// Phases with at least this many 64 x 64 tiles (outputs of 1.6 GB) use 64-row
+// tiles: one product of 102400 of them, time against 32-row tiles: K = 32 0.75 -
+// 0.89, 64 0.87 - 0.92, 128 0.92 - 0.96, 256 0.94 - 0.96, 384 0.93 - 0.96.  The line
+// is not where they begin to gain: products of 8192 to 65536 tiles have the
+// same ratios, grouped phases of that size were not measured.
+#define LIPZ_GEMM_TILE64_MIN 100000
 #endif
 #ifndef LIPZ_GEMM_CHAINS4_MIN_K
 #define LIPZ_GEMM_CHAINS4_MIN_K 512  // phases of aligned problems at least this deep sum in four chains
@@ -951,8 +959,8 @@ __global__ __launch_bounds__(NT, BM == 32 ? 4 : 3) void gemm_kernel(LIPZ_GEMM_AR
   if (CH == 1) epi_load<BM>(P, E, in);  // with four chains registers are short
   bias_corrections(P, lt, step_local, bc);
   v4f acc[T::NQ];
-  if (P.a_trans && P.b_trans) {  // no phase of the library
-    mainloop<BM, CH, true, true, true>(P, m0, n0, st0, st1, acc);
+  if (CH == 1 && P.a_trans && P.b_trans) {  // no phase of the library; never in four chains (gemm_fast_ok)
+    mainloop<BM, 1, true, true, true>(P, m0, n0, st0, st1, acc);
   } else if (P.a_trans) {
     if (m0 + BM > P.a_rows) mainloop<BM, CH, true, false, true>(P, m0, n0, st0, st1, acc);
     else mainloop<BM, CH, true, false, false>(P, m0, n0, st0, st1, acc);

@@ -132,7 +132,7 @@ struct lipz_grid {
   float* aS = nullptr;
   int aS_ld = 0;
   // ... and, when D's last hidden layer is at most as wide as the one below
-  // it, the output layer's weight gradient in per-row-tile column sums
+  // it, the output layer's weight gradient in column sums of 32 rows each,
   // hpart [U][hp_rows][hp_ld] written by the input-gradient launch
   float* hpart = nullptr;
   int hp_rows = 0, hp_ld = 0;

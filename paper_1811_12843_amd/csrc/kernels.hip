@@ -273,6 +273,10 @@ __global__ void fitness_kernel(FitnessArgs F) {
 // Both in one launch, a workgroup per cell, for small neighbourhoods and
 // batches, where launches cost more than the work: four cells of 64 rows take
 // 7.0 us here and 4.7 + 3.2 apart, 16 cells of 100 rows 12.9 and 7.6 + 4.0.
+// Whole evaluations of five individuals, 1 to 64 cells, together against apart:
+// 16 rows 0.95 - 0.98, 32 rows 0.96 - 0.99, 64 rows 0.97 - 0.99, 100 rows 0.99 -
+// 1.02, 128 rows 1.00 - 1.03, 256 rows 1.01 - 1.08.  Of ten individuals (two per
+// cell, the next size there is) 1.04 - 1.7 at every number of rows.
 constexpr int EVAL_FIT_NT = 1024, EVAL_FIT_MAX_NN = 7, EVAL_FIT_MAX_B = 64;
 __global__ __launch_bounds__(EVAL_FIT_NT) void head_eval_fitness_kernel(EvalHeadArgs A, FitnessArgs F) {
   constexpr int N = EVAL_FIT_MAX_NN;

@@ -203,12 +203,12 @@ struct GemmProb {
   //    at N + 1 .. N + 3, and dlout[4 i] = dL/da[i] (Wasserstein: the exact
   //    +-1 of the separate head, scaled by 1 / rs_B later), dlout[4 i + 1 .. 3] = 0.
   //  * EPI_DACT with rs_mode 1 and hpart set (hp_w <= N): the output layer's
-  //    weight gradient in per-row-tile pieces.  The tile of rows m0 .. m0+BM-1
-  //    writes, for its columns j < hp_w, hpart[(m0 / BM) * hp_ld + j] = sum
-  //    over its rows i of dL/da[i] * hsrc[i * hp_w + j] (hsrc: the last hidden
-  //    layer's activations), and the tile of column 0 also
-  //    hpart[(m0 / BM) * hp_ld + hp_w] = sum over its rows of dL/da[i]
-  //    (Wasserstein: the +-1 of dlout in both).
+  //    weight gradient in ceil(M / 32) pieces.  Piece p, of rows 32 p .. 32 p +
+  //    31 whatever the tile height (a 64-row tile writes two), is for each
+  //    column j < hp_w hpart[p * hp_ld + j] = sum over its rows i of dL/da[i] *
+  //    hsrc[i * hp_w + j] (hsrc: the last hidden layer's activations), and
+  //    hpart[p * hp_ld + hp_w] = sum over its rows of dL/da[i] (Wasserstein:
+  //    the +-1 of dlout in both).
   int16_t rs_mode, loss_kind;
   // The grid's constants of the epilogues, the same in every descriptor:
   // the leaky-ReLU slope and Adam's constants.  Carried here so that a GEMM
