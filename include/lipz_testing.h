@@ -60,12 +60,16 @@ lipz_status lipz_test_gemm(void* hip_stream, void* d_desc, int32_t M, int32_t N,
  *           last row the bias gradient, split s over positions 1024 s ..
  *   kind 5: weight gradient of kind 1, partial sums
  *           [ceil(n S^2 / 1024)][16 cin][cout]
+ *   kind 6: bias gradient of kind 1, x = its output gradient [n][S][S][cout] ->
+ *           column sums out [ceil(n S^2 / 4096)][cout] (cin and w not used, w not
+ *           NULL)
  * kernel: 0 = 64 x 64 fp32 tiles, any shape; 1 = wide fp32 tiles, bit for bit
  * the sums of 0; 2 = bf16 matrix cores at fp32 accuracy.  1 and 2: channels
  * multiples of 4, more than 16 output columns, grids of a weight gradient at
  * most 32 wide, tiles 128 x 128, 128 x 64 or 64 x 64; 2: kinds 0 and 1 only
  * (else LIPZ_E_INVAL).  3 = as 2, the weights' pieces formed first, in d_aux
- * (96 cin cout bytes, cout rounded up to 32; cin a multiple of 32).
+ * (96 cin cout bytes, cout rounded up to 32; cin a multiple of 32).  4: column
+ * sums (kind 6, cout at most 64; kind 6 takes 0 and 4).
  * d_desc: device scratch of at least 2048 bytes.
  */
 lipz_status lipz_test_conv(void* hip_stream, void* d_desc, int32_t kind, int32_t n_img, int32_t side_log, int32_t cin,

@@ -1129,8 +1129,10 @@ void dc_build(lipz_grid* g) {
     // Weights the evaluation's convolutions take as bf16 pieces: every cell's are
     // split once, for the five networks' worth of images that use them, into
     // the idle gradient partials of their layer (6 bytes per weight; two or more
-    // splits have the room), where the layers' work is worth the launch (a 5 us
-    // launch against an eighth of 0.2 ms at 2^34 multiply-adds).
+    // splits have the room), where the layers' work is worth the launch: 5 us
+    // against less LDS traffic.  Evaluations of 16 x 16 to 64 x 64 images, 1 to 9
+    // cells, with against without: 2^30 - 2^34 multiply-adds 1.00, 2^34.3 0.99,
+    // 2^34.7 0.97 - 1.00, 2^35 - 2^37 0.94 - 0.97, 2^38 - 2^39 0.91 - 0.94.
     int64_t macs = 0;
     auto room = [&](const DcLayer& L, int64_t part_cell) {
       const int64_t w = 16 * (int64_t)L.cin * ((L.cout + 31) / 32 * 32);  // whole column blocks
@@ -1566,6 +1568,13 @@ int dc_check_bounds(const lipz_grid* g, const char* const* lo, const char* const
       ck.range(p.C, 0, (int64_t)(p.splits - 1) * p.split_stride + crow_max * p.ldc + col_last, "conv partial", idx);
     }
   }
+  for (size_t i = 0; i < P.splitw_h.size(); ++i) {
+    const SplitWProb& w = P.splitw_h[i];
+    const int idx = (int)i;
+    if (w.K % 32 || w.N % 4 || !aligned16(w.W) || !aligned16(w.out)) ck.fail_("split W", idx, "not whole float4s");
+    ck.range(w.W, 0, (int64_t)w.K * w.N - 1, "split W", idx);
+    ck.range(w.out, 0, (int64_t)((w.N + 31) / 32) * w.K * 48 - 1, "split W pieces", idx);
+  }
   for (size_t i = 0; i < P.bn_h.size(); ++i) {
     const BnProb& b = P.bn_h[i];
     const int idx = (int)i;
@@ -1619,7 +1628,7 @@ extern "C" lipz_status lipz_test_conv(void* hip_stream, void* d_desc, int32_t ki
                                       int32_t cin, int32_t cout, const float* d_x, const float* d_w, float* d_out,
                                       const float* d_bias, const float* d_aux, int32_t act, float slope, int32_t kernel,
                                       int32_t tile_m, int32_t tile_n) {
-  if (!d_desc || !d_x || !d_w || !d_out || kind < 0 || kind > 5 || n_img < 1 || side_log < 1 || side_log > 6 || cin < 1 ||
+  if (!d_desc || !d_x || !d_w || !d_out || kind < 0 || kind > 6 || n_img < 1 || side_log < 1 || side_log > 6 || cin < 1 ||
       cout < 1 || cin > 1024 || cout > 1024 || act < LIPZ_ACT_LINEAR || act > LIPZ_ACT_TANH)
     return LIPZ_E_INVAL;
   if ((kind == 2 || kind == 3) && !d_aux) return LIPZ_E_INVAL;
@@ -1628,6 +1637,10 @@ extern "C" lipz_status lipz_test_conv(void* hip_stream, void* d_desc, int32_t ki
   if (kind == 0) ps.push_back(conv_fwd(d_x, n_img, side_log, cin, d_w, cout, d_out, EPI_BIAS_ACT, act, d_bias));
   if (kind == 3) ps.push_back(convT_dgrad(d_x, n_img, side_log, cin, cout, d_w, d_out, d_aux, act));
   if (kind == 4) ps.push_back(conv_wgrad(d_x, n_img, side_log, cin, d_w, cout, d_out));
+  if (kind == 6) {
+    if (kernel != CONV_K_ANY && (kernel != 4 || cout > 64)) return LIPZ_E_INVAL;
+    ps.push_back(convT_bias_grad(d_x, n_img, side_log, cout, d_out, 1, 0));
+  }
   for (int r = 0; r < 2; ++r)
     for (int q = 0; q < 2; ++q) {
       if (kind == 1) ps.push_back(convT_phase(d_x, n_img, side_log, cin, d_w, cout, d_out, r, q, EPI_STORE, 0, nullptr));
@@ -1654,7 +1667,9 @@ extern "C" lipz_status lipz_test_conv(void* hip_stream, void* d_desc, int32_t ki
   memset(&v, 0, sizeof(v));
   v.kernel = kernel;
   v.pre = pre;
-  if (kernel != CONV_K_ANY) {
+  if (kind == 6) {
+    v.kernel = kernel == 4 ? CONV_K_SUM : CONV_K_ANY;
+  } else if (kernel != CONV_K_ANY) {
     if (kernel != CONV_K_WIDE && kernel != CONV_K_SPLIT) return LIPZ_E_INVAL;
     if (!((tile_m == 128 && (tile_n == 128 || tile_n == 64)) || (tile_m == 64 && tile_n == 64))) return LIPZ_E_INVAL;
     for (const ConvProb& p : ps)

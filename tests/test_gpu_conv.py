@@ -17,7 +17,7 @@ import torch.nn.functional as F  # noqa: E402
 
 import paper_1811_12843_amd as L  # noqa: E402
 
-ANY, WIDE, SPLIT, PRE = 0, 1, 2, 3
+ANY, WIDE, SPLIT, PRE, SUM = 0, 1, 2, 3, 4
 SLOPE = 0.2
 KINDS = ["conv", "convT", "conv_dgrad", "convT_dgrad", "conv_wgrad", "convT_wgrad"]
 # (images, log2 side, c_in, c_out): channels a multiple of 32 (a slice within one tap) and not, one and several
@@ -226,3 +226,72 @@ def test_split_weights_are_read_within_their_extent(kind, shape):
         print(f"[case] extent {kind} {shape} tile {tile}", flush=True)
         got = _run(kind, shape, PRE, tile, x, w, bias, aux, pieces_tail=4)
         assert torch.equal(got, _run(kind, shape, SPLIT, tile, x, w, bias, aux)), tile
+
+
+# (images, log2 side): one split and several of 1024 positions, a last one of a few, splits that start inside an
+# image, grids 32 wide (one grid row per slice)
+@pytest.mark.parametrize("kind,shape", [("convT_wgrad", (5, 4, 32, 64)), ("conv_wgrad", (17, 4, 32, 64)),
+                                        ("conv_wgrad", (3, 6, 8, 36)), ("convT_wgrad", (3, 5, 12, 20)),
+                                        ("convT_wgrad", (67, 2, 36, 132)), ("conv_wgrad", (2051, 1, 8, 20))])
+def test_weight_gradients_of_several_splits(kind, shape):
+    x, w, bias, aux = _problem(kind, shape, seed=23)
+    ref, mag = _wgrad_reference(kind, x.double(), w.double())
+    n, h, ci, co = shape
+    pos = n << (2 * (h - 1 if kind == "conv_wgrad" else h))
+    assert pos > 1024
+    print(f"[case] splits {kind} {shape} kernel 0", flush=True)
+    base = _run(kind, shape, ANY, (0, 0), x, w, bias, aux)
+    assert torch.all((base.double().sum(0) - ref).abs() <= (1024 + pos / 1024 + 8) * 2.0 ** -24 * mag + 1e-30)
+    for tile in TILES:
+        print(f"[case] splits {kind} {shape} kernel 1 tile {tile}", flush=True)
+        assert torch.equal(_run(kind, shape, WIDE, tile, x, w, bias, aux), base), tile
+
+
+@pytest.mark.parametrize("n,h,co", [(1, 1, 1), (3, 3, 3), (5, 5, 3), (1, 6, 64), (3, 6, 64), (9, 5, 20), (33, 3, 17)])
+def test_column_sums_match_the_gemm_tile(n, h, co):
+    """The bias gradient as column sums: the tile kernel's sums bit for bit (one position to several splits of 4096, a
+    last one of a few; one to 64 columns, where a split takes many passes through LDS)."""
+    x = torch.from_numpy(np.random.default_rng(n * co).standard_normal((n, 1 << h, 1 << h, co)).astype(np.float32)).cuda()
+    splits = -(-(n << (2 * h)) // 4096)
+    out = []
+    for kernel in (ANY, SUM):
+        print(f"[case] sums {n} {h} {co} kernel {kernel}", flush=True)
+        o = torch.full((splits, co), float("nan"), device="cuda")
+        desc = torch.zeros(2048, dtype=torch.uint8, device="cuda")
+        L.lipz_test_conv(torch.cuda.current_stream().cuda_stream, desc.data_ptr(), 6, n, h, 1, co, x.data_ptr(),
+                         x.data_ptr(), o.data_ptr(), kernel=kernel)
+        torch.cuda.synchronize()
+        out.append(o.cpu())
+    ref = x.cpu().double().reshape(-1, co)
+    assert torch.all((out[0].double().sum(0) - ref.sum(0)).abs() <= (4096 + splits) * 2.0 ** -24 * ref.abs().sum(0))
+    assert torch.equal(out[0], out[1])
+
+
+@pytest.mark.parametrize("kind", ["conv", "convT"])
+@pytest.mark.parametrize("shape", [(8, 3, 8, 64), (8, 3, 32, 64), (8, 3, 64, 128), (3, 2, 512, 64), (3, 2, 1024, 32)])
+@pytest.mark.parametrize("signs", ["both", "one"])
+def test_split_kernel_is_as_accurate_as_fp32_products(kind, shape, signs):
+    """Against fp64, from 32 to 16384 products a sum: the bf16 pieces' rms error is no larger than the fp32 MFMAs',
+    and their mean error (they drop bits towards minus infinity) is a fraction of it, on sums of one sign too.  (The
+    worst-case bounds above leave room for a kernel without its smaller products.)"""
+    x, w, bias, aux = _problem(kind, shape, seed=31)
+    bias = torch.zeros_like(bias)
+    if signs == "one":
+        x, w = x.abs(), w.abs()
+    ref = _reference(kind, x.double(), w.double(), aux.double(), bias.double())[0]
+    scale = ref.pow(2).mean().sqrt()
+
+    def error(kernel, tile):
+        e = (_run(kind, shape, kernel, tile, x, w, bias, aux).double() - ref) / scale
+        if kind == "conv":  # the activation's slope on negative sums would fold their errors
+            e = e[ref > 0]
+        return float(e.pow(2).mean().sqrt()), float(e.mean())
+
+    base = error(ANY, (0, 0))
+    for kernel in [SPLIT] + ([PRE] if shape[2] % 32 == 0 else []):
+        for tile in TILES:
+            rms, mean = error(kernel, tile)
+            print(f"[case] accuracy {kind} {shape} {signs} kernel {kernel} tile {tile} rms {rms:.2e} mean {mean:.1e} "
+                  f"fp32 {base[0]:.2e} {base[1]:.1e}", flush=True)
+            assert rms <= base[0], (kernel, tile)
+            assert abs(mean) <= 0.25 * base[0], (kernel, tile)

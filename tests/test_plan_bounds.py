@@ -39,6 +39,16 @@ def test_small_dcgan_plans_stay_in_bounds(i):
     assert n_bad == 0, msg
 
 
+@pytest.mark.parametrize("d_hidden", [[8, 32, 64], [32, 64, 132]])
+def test_evaluation_weights_split_beforehand_stay_in_bounds(d_hidden):
+    """Evaluations large enough (2^34 multiply-adds) to split their weights first: layers with and without the room for
+    the pieces, a last block of columns that is not whole."""
+    wl = synth.small_workload("celeba_dcgan_4x4", rows=4, cols=4, img=(32, 32, 3), x_dim=3072, z_dim=16,
+                              g_hidden=[128, 64, 32], d_hidden=d_hidden, batch=64, data=dict(n=512, h=32, w=32))
+    n_bad, msg = L.lipz_test_plan_bounds(L.config_from_dict(wl), wl["data"]["n"])
+    assert n_bad == 0, msg
+
+
 SMALL_NES = [
     dict(rows=2, cols=3, z_dim=7, x_dim=37, g_hidden=[33, 70], d_hidden=[45, 19], batch=19, nes_pairs=3,
          data=dict(kind="mnist_like", n=300)),
